@@ -86,7 +86,8 @@ typedef struct omni_handle_s *omni_handle_t;
 
 /* Tuning keys for omni_set_tuning.  Defaults are chosen for 256 compute units. */
 typedef enum {
-    OMNI_TUNE_KERNEL = 0,           /* 0 = auto, 1 = vector-ALU kernel, 2 = matrix-core (MFMA) kernel (bf16, head_dim 128 only) */
+    OMNI_TUNE_KERNEL = 0,           /* 0 = auto, 1 = vector-ALU kernel, 2 = matrix-core (MFMA) kernel (value for bf16, head_dim 128
+                                       only: everywhere else auto takes the matrix cores by itself, with fp32-exact weights) */
     OMNI_TUNE_TARGET_WORKGROUPS = 1,/* workgroups the attention kernel is launched with (> 0; rounded down to a multiple of Hkv) */
     OMNI_TUNE_MIN_PARTITION = 2,    /* smallest range of context, in tokens, one workgroup may be given (multiple of 32) */
     OMNI_TUNE_FORCE_PARTITION = 3,  /* > 0: every workgroup range is exactly this many tokens (multiple of 32); 0 = plan decides */
@@ -211,7 +212,7 @@ omni_status_t omni_kv_append(omni_handle_t h,
  * forward step over the whole batch per iteration; Section 2.2: the AR decoding loop adds one token per request):
  * exactly omni_kv_append with
  * positions[b] = context_lens[b] - 1 (requests of length 0 are skipped) followed by omni_paged_decode_attn, but with
- * the append fused into the attention kernel where the hardware path allows it (bf16, head_dim 128): the wave that
+ * the append fused into the attention kernel (except under OMNI_TUNE_KERNEL = 1): the wave that
  * reads a request's last tile takes the new K/V row from k_new / v_new in place of that row of the page and writes it
  * into the page.  Same results, bit for bit, as the two separate calls; k_cache / v_cache hold the new rows when the
  * call has completed in stream order.
@@ -316,7 +317,8 @@ omni_status_t omni_kv_append_chunk(omni_handle_t h, const void *k_new, const voi
                                    const int32_t *block_table, const int32_t *context_lens, const int32_t *q_lens,
                                    const int64_t *q_offsets, int32_t max_q_len, void *stream);
 
-/* Host-known part of the launch plan: which kernel (OMNI_TUNE_KERNEL value actually used), the data-independent
+/* Host-known part of the launch plan: which kernel (2 = 16-bit matrix-core kernel, softmax weights kept to 2^-16; 1 = a
+ * kernel with fp32-exact weights: vector ALUs, or matrix cores for fp32 caches and head_dim 64), the data-independent
  * grid (workgroups) of the attention kernel, the grid of the merge kernel that follows it, the number of
  * partial-result slots the workspace is sized for, and threads per workgroup.  The range length itself is chosen on the device from
  * context_lens; omni_debug_last_plan reads it back. */
@@ -368,7 +370,7 @@ omni_status_t omni_debug_stream_read(const void *a, size_t a_bytes, const void *
  * dynamic shared memory, [1] = bytes of the kernel variant's static K staging area, [2] = online-softmax states the
  * ring holds (4 .. 16), [3] = 1 if K
  * tiles are staged through shared memory, [4] = 1 if two workgroups fit one compute unit's 160 KB, [5] = the most
- * dynamic shared memory any launch may ask for.  Errors: NULL, UNSUPPORTED (the handle runs the vector-ALU kernel). */
+ * dynamic shared memory any launch may ask for.  Errors: NULL, UNSUPPORTED (the handle runs the vector-ALU kernel: OMNI_TUNE_KERNEL = 1). */
 omni_status_t omni_debug_lds_layout(omni_handle_t h, int32_t host_out[6]);
 
 /* What the loaded code object says about a kernel of this handle (hipFuncGetAttributes; needs a device): which = 0 the

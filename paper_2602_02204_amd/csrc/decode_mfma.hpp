@@ -1,4 +1,5 @@
-// Matrix-core split-context decode kernel for bf16 q/K/V with head_dim 128 and group size <= 16.
+// Matrix-core split-context decode kernel, group size <= 16: bf16 and fp32 caches with head_dim 64 or 128, 8-bit (E4M3)
+// caches with head_dim 128.
 //
 // A workgroup takes the ranges the plan gives it (see plan.hpp) for one KV head; the 32-token tiles of a range are dealt
 // to its four waves in contiguous runs, a wave keeps one online-softmax state per request its run touches, and the
@@ -15,10 +16,18 @@
 //   - for V^T P^T the 8 k-slots of group j are tokens {4j..4j+3, 16+4j..16+4j+3}, exactly the tokens whose scores
 //     the S^T accumulators of that lane group hold, so P needs no data movement; V is loaded row-wise (a 256-byte
 //     row per 16 lanes) and an 8x8 in-lane transpose (v_perm_b32) turns 8 rows x 8 dims into 8 operands.
-// The weights go to the matrix core as bf16 hi + bf16 lo (two MFMAs), which keeps them to ~2^-16 relative.
+// The weights go to the matrix core as bf16 hi + bf16 lo (two MFMAs), which keeps them to ~2^-16 relative; for caches
+// with head_dim 64, whose products are half as many, as three bf16 parts that hold all 24 bits.  An fp32 cache uses
+// v_mfma_f32_16x16x4_f32 for both products (fp32 operands and sums): its k-slot j in step (kk, e) of K Q^T is dim
+// 4 (4kk + j) + e and in step r of V^T P^T token slot_token(j, r), so it loads and stages exactly as the 16-bit caches
+// do and V needs no transposing at all.
+// Measured against the vector-ALU kernel (fp32 FMAs and cross-lane sums: bound by the vector ALUs from four heads per KV
+// head on, by a barrier per request below): 64-dim bf16, 256 requests of a speech-token stage 81 -> 22.5 us per step
+// (77 MB); fp32, 64 requests of 500 .. 4000 tokens: 28/4 heads of 128 dims 354 -> 106 us (592 MB, 5.6 TB/s), 8/8 heads
+// 359 -> 187 us (1.18 GB, 6.3 TB/s), 8/8 heads of 64 dims 191 -> 99 us (591 MB, 6.0 TB/s).
 // With T query tokens per request (kernel variant MT, T * G <= 16) a column is a (query token, head) pair instead of
 // a head: it has its own query row, its own causal limit (tokens 0 .. L - T + i) and its own output row; everything
-// that is said of a head above holds per column.  An 8-bit cache (variant KV8) is widened to bf16 in registers.
+// that is said of a head above holds per column.  An 8-bit cache is widened to bf16 in registers.
 #pragma once
 #include "common.hpp"
 
@@ -47,73 +56,6 @@ constexpr int kAppendFlag = 1 << 30;   // in a slot's tile word: the tile holds 
 // token of k-slot r (0..7) of lane group j inside a 32-token tile
 __device__ __forceinline__ int slot_token(int j, int r) { return (r < 4) ? 4 * j + r : 16 + 4 * j + (r - 4); }
 
-template <int PS>
-struct MfmaTileLoader {
-    const char *kbase, *vbase;       // pool base + KV-head offset
-    size_t page_stride;              // bytes between pages
-    int koff;                        // byte offset of this lane's K chunk inside a 16-token block
-    int voff;                        // byte offset of this lane's first V row chunk inside a 16-token block
-
-    // The 8 K loads / 8 V loads of one 32-token tile.  pg0 / pg1 are the physical pages of its first / second 16
-    // tokens (wave-uniform; with 32-token pages only pg0 is used).
-    __device__ __forceinline__ void issue_k(int pg0, int pg1, uint4 (&K)[8]) const {
-        const size_t o0 = (size_t)pg0 * page_stride;
-        const size_t o1 = (PS == 16) ? (size_t)pg1 * page_stride : o0 + 16 * 256;
-        const char *k0 = kbase + o0 + koff, *k1 = kbase + o1 + koff;
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            K[kk] = nt_load16(k0 + kk * 64);
-            K[4 + kk] = nt_load16(k1 + kk * 64);
-        }
-    }
-    // K through shared memory: the loads above fetch 64 bytes of each of 16 rows per instruction, i.e. every cache line
-    // in two halves by two instructions, which keeps non-temporal loads from paying off for K.  Here a wave copies the
-    // tile's rows into its own 8 KB of shared memory with loads that cover four whole rows per instruction (lane l of
-    // instruction r: row 4r + l/16 of the 16-token block, 16-byte chunk (l % 16) ^ row, landing at 16 l behind the
-    // instruction's base: the xor spreads a column of chunks over the banks), and reads its MFMA operands back from
-    // there.  No register holds the tile while it is on its way.
-    int kst_goff[4];                 // per lane: byte offset of the chunk it fetches in instruction r, inside a block
-    int kst_roff[4];                 // per lane: byte offset of the operand of k-step kk inside a staged block
-    __device__ __forceinline__ void init_staging(int lane) {
-        const int sub = lane >> 4, p16 = lane & 15, i = lane & 15, j = lane >> 4;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int row = 4 * r + sub;
-            kst_goff[r] = row * 256 + ((p16 ^ row) << 4);
-        }
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) kst_roff[kk] = i * 256 + (((4 * kk + j) ^ i) << 4);
-    }
-    __device__ __forceinline__ void issue_k_staged(int pg0, int pg1, char *stage) const {
-        const size_t o0 = (size_t)pg0 * page_stride;
-        const size_t o1 = (PS == 16) ? (size_t)pg1 * page_stride : o0 + 16 * 256;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(kbase + o0 + kst_goff[r]),
-                                             (__attribute__((address_space(3))) void *)(stage + r * 1024), 16, 0, 2);
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(kbase + o1 + kst_goff[r]),
-                                             (__attribute__((address_space(3))) void *)(stage + 4096 + r * 1024), 16, 0, 2);
-        }
-    }
-    __device__ __forceinline__ void read_k_staged(const char *stage, uint4 (&K)[8]) const {
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            K[kk] = *reinterpret_cast<const uint4 *>(stage + kst_roff[kk]);
-            K[4 + kk] = *reinterpret_cast<const uint4 *>(stage + 4096 + kst_roff[kk]);
-        }
-    }
-    __device__ __forceinline__ void issue_v(int pg0, int pg1, uint4 (&V)[8]) const {
-        const size_t o0 = (size_t)pg0 * page_stride;
-        const size_t o1 = (PS == 16) ? (size_t)pg1 * page_stride : o0 + 16 * 256;
-        const char *v0 = vbase + o0 + voff, *v1 = vbase + o1 + voff;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            V[r] = nt_load16(v0 + r * 256);
-            V[4 + r] = nt_load16(v1 + r * 256);
-        }
-    }
-};
-
 // 8 E4M3 bytes (two dwords, dims ascending) -> 8 bf16 (exact: 4 significant bits fit in 8).
 __device__ __forceinline__ uint4 fp8x8_to_bf16x8(uint32_t lo, uint32_t hi) {
     uint4 r;
@@ -124,135 +66,242 @@ __device__ __forceinline__ uint4 fp8x8_to_bf16x8(uint32_t lo, uint32_t hi) {
     return r;
 }
 
-// Loads of one 32-token tile of an 8-bit KV cache (128-byte rows).  K: a lane (token = lane%16, group j) takes the 32
-// bytes of dims 32j .. 32j+31 as two 16-byte loads, and MFMA step kk of group j uses dims 32j + 8kk .. +8 (the query
-// operand is bound the same way).  V: a lane (chunk = lane%16, group j) takes 8 bytes = dims 8*chunk .. +8 of rows
-// 4j .. 4j+3 and 16+4j .. 16+4j+3.  The scales of the tile's pages ride along.
-template <int PS>
-struct Mfma8TileLoader {
-    const char *kbase, *vbase;
-    const float *k_scale, *v_scale;  // already offset by the KV head
-    size_t page_stride;
-    int Hkv, koff, voff;
+// What a KV cache holds: element type and head_dim, and what follows from them for one lane.
+enum CacheFormat { kBf16D128, kFp8D128, kBf16D64, kF32D64, kF32D128 };
 
-    __device__ __forceinline__ void issue_k(int pg0, int pg1, uint4 (&Kr)[4], float (&ks)[2]) const {
-        const int pgb = (PS == 16) ? pg1 : pg0;
-        const char *k0 = kbase + (size_t)pg0 * page_stride + koff;
-        const char *k1 = (PS == 16) ? kbase + (size_t)pg1 * page_stride + koff : k0 + 16 * 128;
-        Kr[0] = *reinterpret_cast<const uint4 *>(k0);
-        Kr[1] = *reinterpret_cast<const uint4 *>(k0 + 16);
-        Kr[2] = *reinterpret_cast<const uint4 *>(k1);
-        Kr[3] = *reinterpret_cast<const uint4 *>(k1 + 16);
-        ks[0] = k_scale[(size_t)pg0 * Hkv];
-        ks[1] = k_scale[(size_t)pgb * Hkv];
-    }
-    // K through shared memory, as in the 16-bit loader: a 16-token block is 2 KB = two instructions of eight whole rows
-    // (lane l of instruction r: row 8r + l/8, 16-byte chunk (l % 8) ^ (row % 8)); a lane reads its 32 bytes of a row back
-    // as two chunks.
-    int kst_goff[2], kst_roff[2];
-    __device__ __forceinline__ void init_staging(int lane) {
+template <CacheFormat F>
+struct CacheTraits {
+    static constexpr bool kFp8 = F == kFp8D128, kF32 = F == kF32D64 || F == kF32D128;
+    static constexpr int D = (F == kBf16D64 || F == kF32D64) ? 64 : 128;
+    static constexpr int ES = kFp8 ? 1 : (kF32 ? 4 : 2);         // bytes per cache element
+    static constexpr int kRowBytes = D * ES;                     // 128, 256 or 512
+    static constexpr int kChunks = kRowBytes / 16;               // 16-byte chunks of a row
+    static constexpr int kKRegs = kRowBytes / 64;                // chunks of one K row a lane takes
+    static constexpr int kVDwords = kRowBytes / 64;              // dwords of one V row a lane takes ...
+    static constexpr int kVWide = kFp8 ? 4 : kVDwords;           // ... and once widened to 16 bits
+    static constexpr int kQRegs = D * (kF32 ? 4 : 2) / 64;       // 16-byte chunks of the query row a lane takes
+    static constexpr int kBlocks = D / 16;                       // 16-dim blocks of output rows
+    static constexpr int kStageBytes = kTile * kRowBytes;        // one 32-token K tile
+};
+
+// Loads of one 32-token tile.  pg0 / pg1 are the physical pages of its first / second 16 tokens (wave-uniform; with
+// 32-token pages only pg0 is used).
+//   K: lane (token = lane%16, group j) takes the row's chunks 4n + j (n < kKRegs), or, of an 8-bit cache, the 32 bytes
+//      of dims 32j .. 32j+31 (MFMA step kk of group j then uses dims 32j + 8kk .. +8, and the query is bound the same way).
+//   V: lane (c = lane%16, group j) takes 1/16 of each of the rows 4j .. 4j+3 and 16+4j .. 16+4j+3: dims 8c .. (128-dim
+//      16-bit and 8-bit caches), 4c .. (64-dim caches), 4c .. and 64 + 4c .. (128-dim fp32).  Whole rows per instruction.
+// The scales of an 8-bit cache's two pages ride along.
+template <int PS, CacheFormat F>
+struct TileLoader {
+    using C = CacheTraits<F>;
+    static constexpr int RB = C::kRowBytes, CH = C::kChunks, NK = C::kKRegs;
+    const char *kbase, *vbase;       // pool base + KV-head offset
+    const float *k_scale, *v_scale;  // 8-bit cache only: already offset by the KV head
+    size_t page_stride;              // bytes between pages
+    int Hkv;
+    int koff;                        // byte offset of this lane's first K chunk inside a 16-token block
+    int voff;                        // byte offset of this lane's first V row piece inside a 16-token block
+    int kst_goff[NK];                // per lane: byte offset of the chunk it fetches in instruction r, inside a block
+    int kst_roff[NK];                // per lane: byte offset of its n-th operand chunk inside a staged block
+
+    __device__ __forceinline__ static int k_chunk(int n, int j) { return C::kFp8 ? 2 * j + n : 4 * n + j; }
+
+    __device__ __forceinline__ void init(const AttnParams &p, int kvh, int lane) {
         const int i = lane & 15, j = lane >> 4;
+        page_stride = (size_t)p.Hkv * PS * RB;
+        kbase = reinterpret_cast<const char *>(p.k_cache) + (size_t)kvh * PS * RB;
+        vbase = reinterpret_cast<const char *>(p.v_cache) + (size_t)kvh * PS * RB;
+        k_scale = C::kFp8 ? p.k_scale + kvh : nullptr;
+        v_scale = C::kFp8 ? p.v_scale + kvh : nullptr;
+        Hkv = p.Hkv;
+        koff = i * RB + k_chunk(0, j) * 16;
+        voff = i * (RB < 512 ? RB / 16 : 16) + (4 * j) * RB;
+        // K through shared memory: the operand layout puts four lanes on a token row, so loading it directly fetches every
+        // cache line in pieces by several instructions, which keeps non-temporal loads from paying off for K.  Instead a
+        // wave copies the tile's rows into its own part of shared memory with loads that cover whole rows (lane l of
+        // instruction r: row r * 64 / CH + l / CH of the 16-token block, chunk (l % CH) ^ (row % CH), landing at 16 l behind
+        // the instruction's base: the xor spreads a column of chunks over the banks), and reads its MFMA operands back from
+        // there.  No register holds the tile while it is on its way.
 #pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            const int row = 8 * r + (lane >> 3);
-            kst_goff[r] = row * 128 + (((lane & 7) ^ (row & 7)) << 4);
+        for (int r = 0; r < NK; ++r) {
+            const int row = r * (64 / CH) + lane / CH;
+            kst_goff[r] = row * RB + (((lane % CH) ^ (row % CH)) << 4);
+            kst_roff[r] = i * RB + ((k_chunk(r, j) ^ (i % CH)) << 4);
         }
+    }
+    __device__ __forceinline__ size_t second_half(int pg0, int pg1) const {
+        return PS == 16 ? (size_t)pg1 * page_stride : (size_t)pg0 * page_stride + 16 * RB;
+    }
+    __device__ __forceinline__ void load_k_scales(int pg0, int pg1, float (&ks)[2]) const {
+        if constexpr (C::kFp8) { ks[0] = k_scale[(size_t)pg0 * Hkv]; ks[1] = k_scale[(size_t)(PS == 16 ? pg1 : pg0) * Hkv]; }
+    }
+    __device__ __forceinline__ void issue_k(int pg0, int pg1, uint4 (&K)[2 * NK], float (&ks)[2]) const {
+        const char *k0 = kbase + (size_t)pg0 * page_stride + koff, *k1 = kbase + second_half(pg0, pg1) + koff;
 #pragma unroll
-        for (int e = 0; e < 2; ++e) kst_roff[e] = i * 128 + (((2 * j + e) ^ (i & 7)) << 4);
+        for (int n = 0; n < NK; ++n) {
+            const int off = (k_chunk(n, 0) - k_chunk(0, 0)) * 16;
+            if constexpr (C::kFp8) {                             // non-temporal loads lose on this pattern
+                K[n] = *reinterpret_cast<const uint4 *>(k0 + off);
+                K[NK + n] = *reinterpret_cast<const uint4 *>(k1 + off);
+            } else {
+                K[n] = nt_load16(k0 + off);
+                K[NK + n] = nt_load16(k1 + off);
+            }
+        }
+        load_k_scales(pg0, pg1, ks);
     }
     __device__ __forceinline__ void issue_k_staged(int pg0, int pg1, char *stage, float (&ks)[2]) const {
-        const int pgb = (PS == 16) ? pg1 : pg0;
-        const size_t o0 = (size_t)pg0 * page_stride;
-        const size_t o1 = (PS == 16) ? (size_t)pg1 * page_stride : o0 + 16 * 128;
+        const char *k0 = kbase + (size_t)pg0 * page_stride, *k1 = kbase + second_half(pg0, pg1);
 #pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(kbase + o0 + kst_goff[r]),
+        for (int r = 0; r < NK; ++r) {
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(k0 + kst_goff[r]),
                                              (__attribute__((address_space(3))) void *)(stage + r * 1024), 16, 0, 2);
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(kbase + o1 + kst_goff[r]),
-                                             (__attribute__((address_space(3))) void *)(stage + 2048 + r * 1024), 16, 0, 2);
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(k1 + kst_goff[r]),
+                                             (__attribute__((address_space(3))) void *)(stage + 16 * RB + r * 1024), 16, 0, 2);
         }
-        ks[0] = k_scale[(size_t)pg0 * Hkv];
-        ks[1] = k_scale[(size_t)pgb * Hkv];
+        load_k_scales(pg0, pg1, ks);
     }
-    __device__ __forceinline__ void read_k_staged(const char *stage, uint4 (&Kr)[4]) const {
+    __device__ __forceinline__ void read_k_staged(const char *stage, uint4 (&K)[2 * NK]) const {
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            Kr[e] = *reinterpret_cast<const uint4 *>(stage + kst_roff[e]);
-            Kr[2 + e] = *reinterpret_cast<const uint4 *>(stage + 2048 + kst_roff[e]);
+        for (int n = 0; n < NK; ++n) {
+            K[n] = *reinterpret_cast<const uint4 *>(stage + kst_roff[n]);
+            K[NK + n] = *reinterpret_cast<const uint4 *>(stage + 16 * RB + kst_roff[n]);
         }
     }
-    __device__ __forceinline__ void issue_v(int pg0, int pg1, uint2 (&Vr)[8], float (&vs)[2]) const {
-        const int pgb = (PS == 16) ? pg1 : pg0;
-        const char *v0 = vbase + (size_t)pg0 * page_stride + voff;
-        const char *v1 = (PS == 16) ? vbase + (size_t)pg1 * page_stride + voff : v0 + 16 * 128;
+    __device__ __forceinline__ void read_k_staged_half(const char *stage, int half, uint4 *K) const {
+#pragma unroll
+        for (int n = 0; n < NK; ++n) K[n] = *reinterpret_cast<const uint4 *>(stage + half * (16 * RB) + kst_roff[n]);
+    }
+    __device__ __forceinline__ static void load_v_piece(const char *src, uint32_t (&v)[C::kVDwords]) {
+        if constexpr (C::kVDwords == 2) {
+            const uint2 x = nt_load8(src);
+            v[0] = x.x; v[1] = x.y;
+        } else {
+#pragma unroll
+            for (int h = 0; h < C::kVDwords / 4; ++h) {
+                const uint4 x = nt_load16(src + h * 256);
+                v[4 * h] = x.x; v[4 * h + 1] = x.y; v[4 * h + 2] = x.z; v[4 * h + 3] = x.w;
+            }
+        }
+    }
+    __device__ __forceinline__ void issue_v(int pg0, int pg1, uint32_t (&V)[8][C::kVDwords], float (&vs)[2]) const {
+        const char *v0 = vbase + (size_t)pg0 * page_stride + voff, *v1 = vbase + second_half(pg0, pg1) + voff;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            Vr[r] = nt_load8(v0 + r * 128);
-            Vr[4 + r] = nt_load8(v1 + r * 128);
+            load_v_piece(v0 + r * RB, V[r]);
+            load_v_piece(v1 + r * RB, V[4 + r]);
         }
-        vs[0] = v_scale[(size_t)pg0 * Hkv];
-        vs[1] = v_scale[(size_t)pgb * Hkv];
+        if constexpr (C::kFp8) { vs[0] = v_scale[(size_t)pg0 * Hkv]; vs[1] = v_scale[(size_t)(PS == 16 ? pg1 : pg0) * Hkv]; }
     }
 };
 
-// Scores of a tile of an 8-bit cache: bytes are widened to bf16 right before each MFMA step; the K scale of each
-// 16-token half joins the softmax scale.
-__device__ __forceinline__ void mfma_scores_fp8(const uint4 (&Kr)[4], const uint4 (&Q)[4], float (&sv)[8],
-                                                float scale_log2, const float (&ks)[2]) {
+__device__ __forceinline__ f32x4_t mfma_f32(uint32_t a, uint32_t b, f32x4_t c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a), __uint_as_float(b), c, 0, 0, 0);
+}
+
+template <CacheFormat F>
+struct MfmaState {
+    float m, l;
+    f32x4_t acc[CacheTraits<F>::kBlocks];    // acc[e][i] = O^T[dim of output row 4j + i of block e][column lane%16]
+};
+
+// First half of a 32-token tile: the scores S^T = K Q^T of the tile, in the log2 domain.  Bytes of an 8-bit cache are
+// widened to bf16 right before each MFMA step, and the K scale of each 16-token half (ks) joins the softmax scale.
+template <CacheFormat F>
+__device__ __forceinline__ void mfma_scores(const uint4 (&K)[2 * CacheTraits<F>::kKRegs], const uint4 (&Q)[CacheTraits<F>::kQRegs],
+                                            float (&sv)[8], float scale_log2, const float (&ks)[2]) {
+    // Scores are rounded before the running max is subtracted (no fused multiply-subtract): s - max is then exactly
+    // 0 for the maximal score, and a length-1 context returns its V row bit for bit.
 #pragma clang fp contract(off)
+    using C = CacheTraits<F>;
+    constexpr int NK = C::kKRegs;
     f32x4_t s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-        const uint4 &a = Kr[kk >> 1], &b = Kr[2 + (kk >> 1)];
-        const uint4 A0 = (kk & 1) ? fp8x8_to_bf16x8(a.z, a.w) : fp8x8_to_bf16x8(a.x, a.y);
-        const uint4 A1 = (kk & 1) ? fp8x8_to_bf16x8(b.z, b.w) : fp8x8_to_bf16x8(b.x, b.y);
-        s0 = mfma_bf16(A0, Q[kk], s0);
-        s1 = mfma_bf16(A1, Q[kk], s1);
+    for (int n = 0; n < C::kQRegs; ++n) {
+        if constexpr (C::kFp8) {
+            const uint4 &a = K[n >> 1], &b = K[NK + (n >> 1)];
+            const uint4 A0 = (n & 1) ? fp8x8_to_bf16x8(a.z, a.w) : fp8x8_to_bf16x8(a.x, a.y);
+            const uint4 A1 = (n & 1) ? fp8x8_to_bf16x8(b.z, b.w) : fp8x8_to_bf16x8(b.x, b.y);
+            s0 = mfma_bf16(A0, Q[n], s0);
+            s1 = mfma_bf16(A1, Q[n], s1);
+        } else if constexpr (C::kF32) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                s0 = mfma_f32(dword_of(K[n], e), dword_of(Q[n], e), s0);
+                s1 = mfma_f32(dword_of(K[NK + n], e), dword_of(Q[n], e), s1);
+            }
+        } else {
+            s0 = mfma_bf16(K[n], Q[n], s0);
+            s1 = mfma_bf16(K[NK + n], Q[n], s1);
+        }
     }
-    const float c0 = ks[0] * scale_log2, c1 = ks[1] * scale_log2;
+    const float c0 = C::kFp8 ? ks[0] * scale_log2 : scale_log2, c1 = C::kFp8 ? ks[1] * scale_log2 : scale_log2;
 #pragma unroll
     for (int i = 0; i < 4; ++i) { sv[i] = s0[i] * c0; sv[4 + i] = s1[i] * c1; }
 }
 
-struct MfmaState {
-    float m, l;
-    f32x4_t acc[8];          // acc[e][i] = O^T[dim 32j + 8i + e][head lane%16]
-};
-
-// First half of a 32-token tile: the scores S^T = K Q^T of the tile, in the log2 domain.
-__device__ __forceinline__ void mfma_scores(const uint4 (&K)[8], const uint4 (&Q)[4], float (&sv)[8], float scale_log2) {
-    // Scores are rounded before the running max is subtracted (no fused multiply-subtract): s - max is then exactly
-    // 0 for the maximal score, and a length-1 context returns its V row bit for bit.
-#pragma clang fp contract(off)
-    f32x4_t s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+// The raw scores of one 16-token half of an fp32 tile.
+template <CacheFormat F>
+__device__ __forceinline__ void mfma_scores_f32_half(const uint4 *K, const uint4 (&Q)[CacheTraits<F>::kQRegs], f32x4_t &s) {
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-        s0 = mfma_bf16(K[kk], Q[kk], s0);
-        s1 = mfma_bf16(K[4 + kk], Q[kk], s1);
+    for (int n = 0; n < CacheTraits<F>::kQRegs; ++n)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s = mfma_f32(dword_of(K[n], e), dword_of(Q[n], e), s);
+}
+
+// Two floats' upper halves as a pair of bf16 (truncated).
+__device__ __forceinline__ uint32_t upper_halves(float lo, float hi) {
+    return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
+}
+__device__ __forceinline__ float below_upper_half(float x) { return x - __uint_as_float(__float_as_uint(x) & 0xffff0000u); }
+
+// The eight weights of a lane as bf16 MFMA operands whose sum is the weight: two parts to ~2^-16 relative (rounded), or
+// three that hold all 24 bits (each the upper half of what the parts before it left, so nothing is rounded).
+template <int kParts>
+__device__ __forceinline__ void split_weights(const float (&pw)[8], uint4 (&P)[kParts]) {
+#pragma clang fp contract(off)
+    uint32_t d[kParts][4];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        const float a = pw[2 * w], b = pw[2 * w + 1];
+        if constexpr (kParts == 2) {
+            d[0][w] = pack_bf16x2(a, b);
+            d[1][w] = pack_bf16x2(a - bf16_bits_to_float(d[0][w] & 0xffffu), b - __uint_as_float(d[0][w] & 0xffff0000u));
+        } else {
+            d[0][w] = upper_halves(a, b);
+            const float a1 = below_upper_half(a), b1 = below_upper_half(b);
+            d[1][w] = upper_halves(a1, b1);
+            d[2][w] = upper_halves(below_upper_half(a1), below_upper_half(b1));
+        }
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) { sv[i] = s0[i] * scale_log2; sv[4 + i] = s1[i] * scale_log2; }
+    for (int i = 0; i < kParts; ++i) P[i] = make_uint4(d[i][0], d[i][1], d[i][2], d[i][3]);
 }
 
 // Second half: online softmax over the tile's scores and the weighted V accumulation O^T += V^T P^T.
 // `vs0` / `vs1` scale the weights of the tile's first / second 16 tokens on their way into the product (the V scales of
-// an 8-bit cache; 1 otherwise): the sum of weights stays unscaled.
+// an 8-bit cache): the sum of weights stays unscaled.
 // t1: the request's length; t1col: tokens this lane's column may see (t1 less the query tokens after its own; = t1 in
 // plain decode); t1min: the smallest t1col of the wave's columns.
 // kMulti (several query tokens per request): the three differ; otherwise all are t1.
-template <bool kScaled = false, bool kMulti = false>
-__device__ __forceinline__ void mfma_softmax_pv(float (&sv)[8], uint4 (&V)[8], MfmaState &st, int tb, int t1, int t1col,
-                                                int t1min, int j, float vs0 = 1.f, float vs1 = 1.f) {
+template <CacheFormat F, bool kMulti>
+__device__ __forceinline__ void mfma_softmax_pv(float (&sv)[8], uint32_t (&V)[8][CacheTraits<F>::kVWide], MfmaState<F> &st,
+                                                int tb, int t1, int t1col, int t1min, int j, float vs0, float vs1) {
 #pragma clang fp contract(off)
+    using C = CacheTraits<F>;
+    auto drop_v = [&](int r) __attribute__((always_inline)) {
+#pragma unroll
+        for (int w = 0; w < C::kVWide; ++w) V[r][w] = 0;
+    };
     if (tb + 32 > (kMulti ? t1min : t1)) {               // last tiles of the request (uniform branch)
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
             if (kMulti) {
                 if (tb + slot_token(j, r) >= t1col) sv[r] = -INFINITY;      // not visible to this column
-                if (tb + slot_token(j, r) >= t1) V[r] = make_uint4(0, 0, 0, 0);
+                if (tb + slot_token(j, r) >= t1) drop_v(r);
             } else if (tb + slot_token(j, r) >= t1) {    // unowned slot: its K/V bits are arbitrary, possibly NaN
                 sv[r] = -INFINITY;
-                V[r] = make_uint4(0, 0, 0, 0);
+                drop_v(r);
             }
         }
     }
@@ -270,43 +319,42 @@ __device__ __forceinline__ void mfma_softmax_pv(float (&sv)[8], uint4 (&V)[8], M
     for (int r = 0; r < 8; ++r) { pw[r] = fast_exp2(sv[r] - mn); psum += pw[r]; }
     st.l = st.l * alpha + psum;
     st.m = mn;
-    if (kScaled) {
+    if constexpr (C::kFp8) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) { pw[r] *= vs0; pw[4 + r] *= vs1; }
     }
-    uint4 Ph, Pl;
-    {
-        uint32_t h[4], lo[4];
+    if constexpr (C::kF32) {
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            h[w] = pack_bf16x2(pw[2 * w], pw[2 * w + 1]);
-            const float r0 = pw[2 * w] - bf16_bits_to_float(h[w] & 0xffffu);
-            const float r1 = pw[2 * w + 1] - __uint_as_float(h[w] & 0xffff0000u);
-            lo[w] = pack_bf16x2(r0, r1);
+        for (int e = 0; e < C::kBlocks; ++e) st.acc[e] *= alpha;
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+#pragma unroll
+            for (int e = 0; e < C::kBlocks; ++e) st.acc[e] = mfma_f32(V[r][e], __float_as_uint(pw[r]), st.acc[e]);
+    } else {
+        constexpr int kParts = C::D == 64 ? 3 : 2;
+        uint4 P[kParts];
+        split_weights<kParts>(pw, P);
+#pragma unroll
+        for (int e = 0; e < C::kBlocks; ++e) st.acc[e] *= alpha;
+        // in-lane transpose: operand e holds dim e of the lane's chunk for the 8 tokens of its lane group
+        // (dword w of V[r] holds dims 2w and 2w+1 of token slot r)
+#pragma unroll
+        for (int e = 0; e < C::kBlocks; ++e) {
+            const int w = e >> 1;
+            const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
+            uint4 A;
+            A.x = __builtin_amdgcn_perm(V[1][w], V[0][w], sel);
+            A.y = __builtin_amdgcn_perm(V[3][w], V[2][w], sel);
+            A.z = __builtin_amdgcn_perm(V[5][w], V[4][w], sel);
+            A.w = __builtin_amdgcn_perm(V[7][w], V[6][w], sel);
+#pragma unroll
+            for (int i = 0; i < kParts; ++i) st.acc[e] = mfma_bf16(A, P[i], st.acc[e]);
         }
-        Ph = make_uint4(h[0], h[1], h[2], h[3]);
-        Pl = make_uint4(lo[0], lo[1], lo[2], lo[3]);
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) st.acc[e] *= alpha;
-    // 8x8 transpose: operand e holds dim e of the lane's 8-dim chunk for the 8 tokens of its lane group
-    // (dword w of V[r] holds dims 2w and 2w+1 of token slot r)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const int w = e >> 1;
-        const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
-        uint4 A;
-        A.x = __builtin_amdgcn_perm(dword_of(V[1], w), dword_of(V[0], w), sel);
-        A.y = __builtin_amdgcn_perm(dword_of(V[3], w), dword_of(V[2], w), sel);
-        A.z = __builtin_amdgcn_perm(dword_of(V[5], w), dword_of(V[4], w), sel);
-        A.w = __builtin_amdgcn_perm(dword_of(V[7], w), dword_of(V[6], w), sel);
-        st.acc[e] = mfma_bf16(A, Ph, st.acc[e]);
-        st.acc[e] = mfma_bf16(A, Pl, st.acc[e]);
     }
 }
 
 constexpr int kMaxStates = 16;                         // states the ring holds at most
-constexpr int kKStageBytes = 8192;                     // one 32-token K tile of a 16-bit cache (D = 128)
+constexpr int kKStageBytes = 8192;                     // one 32-token K tile of 256-byte rows
 
 // Shared-memory layout for a batch of B requests and G columns per KV head: as many states (up to sixteen) as fit
 // while two workgroups still share the 160 KB of a compute unit.  Four is the least the kernel works with (one state
@@ -314,12 +362,11 @@ constexpr int kKStageBytes = 8192;                     // one 32-token K tile of
 // columns), the layout keeps four and `two_per_cu` is false: the launch is still valid, with one workgroup per
 // compute unit.
 constexpr int kLdsPerWorkgroup = 80 * 1024 - 512;      // half a compute unit's shared memory less the kernel's own variables
-inline MfmaLds mfma_lds_layout(int B, int G, bool kv8, bool staged, bool query_counts = false) {
-    constexpr int D = 128;
+inline MfmaLds mfma_lds_layout(int B, int G, int D, int row_bytes, bool staged, bool query_counts = false) {
     MfmaLds L;
     L.ring_off = (((query_counts ? 3 : 2) * B + 1) * 4 + 15) & ~15;      // E[B + 1], Lc[B] and, if asked for, Nc[B]
     L.state_floats = G * (D + 4) + 2 * kMaxGroup;
-    L.static_bytes = staged ? kWaves * (kv8 ? kKStageBytes / 2 : kKStageBytes) : 0;   // the waves' K tiles
+    L.static_bytes = staged ? kWaves * kTile * row_bytes : 0;          // the waves' K tiles
     const int budget = kLdsPerWorkgroup - L.ring_off - L.static_bytes;
     const int cap = budget / (L.state_floats * 4);
     L.two_per_cu = cap >= kWaves;
@@ -397,19 +444,19 @@ __device__ __forceinline__ void mfma_combine_states(const float *first, int cnt,
 // request, the one to four consecutive states that belong to it.  A range that holds more requests than the states'
 // area has room for (all but three of its states) is taken in chunks of that many requests, with the same meeting
 // after each chunk.
-// KV8: the pools hold 8-bit E4M3 bytes with one scale per (page, KV head); queries stay bf16.
+// F: what the pools hold (an 8-bit cache has one scale per (page, KV head); its queries stay bf16).
 // KST: K tiles go through the per-wave staging area in shared memory (the host chooses it where room for enough
 // states is left beside it); otherwise they are loaded straight into the operand registers.
 // MT: several query tokens per request (the columns are (query token, head) pairs with a causal limit each); the
 // one-token kernel is compiled without any of it.
-template <int PS, bool KV8 = false, bool KST = true, bool MT = false>
+template <int PS, CacheFormat F, bool KST, bool MT>
 __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(AttnParams p) {
-    constexpr int D = 128;
-    constexpr int ES = KV8 ? 1 : 2;                          // bytes per cache element
+    using C = CacheTraits<F>;
+    constexpr int D = C::D, RB = C::kRowBytes;
     constexpr int kLog2Ps = (PS == 16) ? 4 : 5;
     __shared__ PlanSmem ps;
     extern __shared__ __align__(16) int E[];                 // E[B + 1] tile offsets, then Lc[B] lengths, then the ring
-    __shared__ __align__(16) char kstage_all[KST ? kWaves * (KV8 ? kKStageBytes / 2 : kKStageBytes) : 16];  // a K tile per wave
+    __shared__ __align__(16) char kstage_all[KST ? kWaves * C::kStageBytes : 16];  // a K tile per wave
     float *ring = reinterpret_cast<float *>(reinterpret_cast<char *>(E) + p.lds.ring_off);
     const int state_floats = p.lds.state_floats;
     const int max_seg = p.lds.ring_states - (kWaves - 1);    // requests a chunk may hold: the states then fit
@@ -427,32 +474,20 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(AttnParams p) 
     const int t_off = MT ? p.t_off : 0;
     const int col_tok = t_off + col_qi;                          // which of the request's query tokens
 
-    MfmaTileLoader<PS> ld;
-    ld.page_stride = (size_t)p.Hkv * PS * D * ES;
-    ld.kbase = reinterpret_cast<const char *>(p.k_cache) + (size_t)kvh * PS * D * ES;
-    ld.vbase = reinterpret_cast<const char *>(p.v_cache) + (size_t)kvh * PS * D * ES;
-    ld.koff = col * 256 + j * 16;
-    ld.voff = col * 16 + (4 * j) * 256;
-    ld.init_staging(lane);
-    char *kstage = kstage_all + (KST ? wave * (KV8 ? kKStageBytes / 2 : kKStageBytes) : 0);
-    Mfma8TileLoader<PS> ld8;
-    ld8.page_stride = ld.page_stride; ld8.kbase = ld.kbase; ld8.vbase = ld.vbase;
-    ld8.k_scale = KV8 ? p.k_scale + kvh : nullptr; ld8.v_scale = KV8 ? p.v_scale + kvh : nullptr;
-    ld8.Hkv = p.Hkv;
-    ld8.koff = col * 128 + j * 32;
-    ld8.voff = col * 8 + (4 * j) * 128;
-    ld8.init_staging(lane);
+    TileLoader<PS, F> ld;
+    ld.init(p, kvh, lane);
+    char *kstage = kstage_all + (KST ? wave * C::kStageBytes : 0);
 
     // Several query tokens per request: Nc[b] = how many request b brings (behind E[] and Lc[] in shared memory).
     int *Nc = E + 2 * p.plan.B + 1;
-    auto load_q = [&](int b, uint4 (&Q)[4]) {                    // B operand of K Q^T for request b
+    auto load_q = [&](int b, uint4 (&Q)[C::kQRegs]) {            // B operand of K Q^T for request b
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) Q[kk] = make_uint4(0, 0, 0, 0);
+        for (int n = 0; n < C::kQRegs; ++n) Q[n] = make_uint4(0, 0, 0, 0);
         if (col < Gq && (!MT || t_off + col_qi < Nc[b])) {       // a column no query token stands behind keeps zeros
-            const char *qrow = reinterpret_cast<const char *>(p.q) + (((size_t)b * tokens + t_off + col_qi) * p.Hq + head0 + col_g) * (D * 2);
+            const char *qrow = reinterpret_cast<const char *>(p.q) + (((size_t)b * tokens + t_off + col_qi) * p.Hq + head0 + col_g) * (D * (C::kF32 ? 4 : 2));
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk)                      // dims of step kk: (4kk + j) * 8 .., or 32j + 8kk .. (KV8)
-                Q[kk] = *reinterpret_cast<const uint4 *>(qrow + (KV8 ? 4 * j + kk : 4 * kk + j) * 16);
+            for (int n = 0; n < C::kQRegs; ++n)                 // the dims that meet the lane's K chunks
+                Q[n] = *reinterpret_cast<const uint4 *>(qrow + (C::kFp8 ? 4 * j + n : 4 * n + j) * 16);
         }
     };
 
@@ -555,7 +590,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(AttnParams p) 
         // row, the next ones the V row, 16 bytes each) before the tile is requested; the wave waits for the write to be
         // acknowledged, so the loads that follow see it.  With several query tokens per request the new rows are
         // [B, T, Hkv, D] and each tile takes those of the request's last T positions that fall into it.
-        constexpr int kRowPieces = D * ES / 16;                  // 16-byte pieces of a row: 16 (16-bit cache) or 8
+        constexpr int kRowPieces = C::kChunks;                   // 16-byte pieces of a row
         auto append_row = [&](const SlotInfo &si) {
             const int L = Lc[si.req];
             const int n_new = MT ? Nc[si.req] : 1;               // rows 0 .. n_new - 1 of the request's new rows
@@ -564,12 +599,12 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(AttnParams p) 
                 const int pos = L - n_new + qi;
                 if (MT && (pos < 0 || (pos >> kLog2Tile) != si.tile)) continue;      // uniform
                 const int pg = (PS == 16 && (pos & 16)) ? si.pg1 : si.pg0;
-                const size_t row = (size_t)pg * ld.page_stride + (size_t)(pos & (PS - 1)) * (D * ES);
+                const size_t row = (size_t)pg * ld.page_stride + (size_t)(pos & (PS - 1)) * RB;
                 if (lane < 2 * kRowPieces) {
                     const bool is_v = lane >= kRowPieces;
                     const int piece = lane & (kRowPieces - 1);
                     const char *src = reinterpret_cast<const char *>(is_v ? p.v_new : p.k_new) +
-                                      (((size_t)si.req * tokens + qi) * p.Hkv + kvh) * (D * ES) + piece * 16;
+                                      (((size_t)si.req * tokens + qi) * p.Hkv + kvh) * RB + piece * 16;
                     char *dst = const_cast<char *>(is_v ? ld.vbase : ld.kbase) + row + piece * 16;
                     *reinterpret_cast<uint4 *>(dst) = *reinterpret_cast<const uint4 *>(src);
                 }
@@ -584,40 +619,46 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(AttnParams p) 
         constexpr bool kPatchAppend = KST && !MT;
         int patch_row = -1;                                      // the new token's place in the tile in flight, or none
         size_t patch_dst = 0;                                    // byte offset of its row behind kbase / vbase
-        uint4 Kn = make_uint4(0, 0, 0, 0), Vn = make_uint4(0, 0, 0, 0);
+        uint4 Kn = make_uint4(0, 0, 0, 0);
+        uint32_t Vn[C::kVDwords] = {};
+        constexpr int kVStep = RB < 512 ? RB / 16 : 16;          // a lane's V piece: 8 or 16 bytes, or two of 16, 256 apart
+        auto load_v_new = [&](const char *src, uint32_t (&v)[C::kVDwords]) __attribute__((always_inline)) {
+            if constexpr (C::kVDwords == 2) {
+                const uint2 x = *reinterpret_cast<const uint2 *>(src);
+                v[0] = x.x; v[1] = x.y;
+            } else {
+#pragma unroll
+                for (int h = 0; h < C::kVDwords / 4; ++h) {
+                    const uint4 x = *reinterpret_cast<const uint4 *>(src + h * 256);
+                    v[4 * h] = x.x; v[4 * h + 1] = x.y; v[4 * h + 2] = x.z; v[4 * h + 3] = x.w;
+                }
+            }
+        };
         auto request_new_row = [&](const SlotInfo &si) {
             const int pos = __builtin_amdgcn_readfirstlane(Lc[si.req]) - 1;
             patch_row = pos - si.tile * kTile;
             const int pg = (PS == 16 && (pos & 16)) ? si.pg1 : si.pg0;
-            patch_dst = (size_t)pg * ld.page_stride + (size_t)(pos & (PS - 1)) * (D * ES);
-            const size_t src = ((size_t)si.req * p.Hkv + kvh) * (D * ES);
+            patch_dst = (size_t)pg * ld.page_stride + (size_t)(pos & (PS - 1)) * RB;
+            const size_t src = ((size_t)si.req * p.Hkv + kvh) * RB;
             Kn = *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(p.k_new) + src + (lane & (kRowPieces - 1)) * 16);
-            if constexpr (KV8) {                                 // a lane's V piece is 8 bytes there: dims 8 col ..
-                const uint2 v8 = *reinterpret_cast<const uint2 *>(reinterpret_cast<const char *>(p.v_new) + src + col * 8);
-                Vn.x = v8.x; Vn.y = v8.y;
-            } else {
-                Vn = *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(p.v_new) + src + col * 16);
-            }
+            const char *vsrc = reinterpret_cast<const char *>(p.v_new) + src + col * kVStep;
+            load_v_new(vsrc, Vn);
         };
 
         // Software pipeline of one wave (single K and V buffers): the K rows of the next tile are requested as soon
         // as the scores of the current tile have consumed K, its V rows as soon as the accumulation has consumed V,
         // and the next request's query as soon as the last scores of the current request are done.  The requests
         // stay in flight across the end-of-segment exchange below.
-        uint4 K[KV8 ? 1 : 8], V[8], Q[4];
-        uint4 Kr[KV8 ? 4 : 1];           // 8-bit cache: the raw bytes of a tile and the scales of its two pages
-        uint2 Vr[KV8 ? 8 : 1];
-        float ks[2] = {1.f, 1.f}, vs[2] = {1.f, 1.f};
+        // 512-byte rows: with both halves' K operands, V and the query in registers at once the kernel spills 30 of them
+        // (120.3 us against 106 for 590 MB with K straight into registers), so the halves take turns
+        constexpr bool kHalves = KST && RB == 512;
+        uint4 K[kHalves ? C::kKRegs : 2 * C::kKRegs], Q[C::kQRegs];
+        uint32_t Vr[8][C::kVDwords];     // V rows as they are stored
+        float ks[2] = {1.f, 1.f}, vs[2] = {1.f, 1.f};            // 8-bit cache: the scales of the tile's two pages
         auto issue_k = [&](int pg0, int pg1) __attribute__((always_inline)) {
-            if constexpr (KST) {
-                if constexpr (KV8) ld8.issue_k_staged(pg0, pg1, kstage, ks); else ld.issue_k_staged(pg0, pg1, kstage);
-            } else {
-                if constexpr (KV8) ld8.issue_k(pg0, pg1, Kr, ks); else ld.issue_k(pg0, pg1, K);
-            }
+            if constexpr (KST) ld.issue_k_staged(pg0, pg1, kstage, ks); else ld.issue_k(pg0, pg1, K, ks);
         };
-        auto issue_v = [&](int pg0, int pg1) __attribute__((always_inline)) {
-            if constexpr (KV8) ld8.issue_v(pg0, pg1, Vr, vs); else ld.issue_v(pg0, pg1, V);
-        };
+        auto issue_v = [&](int pg0, int pg1) __attribute__((always_inline)) { ld.issue_v(pg0, pg1, Vr, vs); };
         int s = 0;                       // slot being computed; its loads are in flight
         SlotInfo cur = slot_info(0);
         if (cur.req >= 0) {
@@ -656,10 +697,10 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(AttnParams p) 
             const int seg_n = MT ? __builtin_amdgcn_readfirstlane(Nc[b]) : 1;
             const int col_back = (MT && col < Gq && col_tok < seg_n) ? seg_n - 1 - col_tok : 0;
             const int t1min = MT ? seg.L - max(seg_n - 1 - t_off, 0) : seg.L;
-            MfmaState st;
+            MfmaState<F> st;
             st.m = -INFINITY; st.l = 0.f;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) st.acc[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            for (int e = 0; e < C::kBlocks; ++e) st.acc[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
             while (cur.req == seg.b) {
                 const SlotInfo nxt = slot_info(s + 1);
                 const bool more = nxt.req >= 0;
@@ -676,57 +717,82 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(AttnParams p) 
                         if (patch_row >= 0) {                    // this tile holds its request's new token (uniform)
                             const int blk = patch_row >> 4, row = patch_row & 15;
                             if (lane < kRowPieces) {             // piece `lane` of the K row: staging area, and its page
-                                *reinterpret_cast<uint4 *>(kstage + blk * (kRowPieces * 256) + row * (D * ES) +
+                                *reinterpret_cast<uint4 *>(kstage + blk * (16 * RB) + row * RB +
                                                            (((lane ^ row) & (kRowPieces - 1)) << 4)) = Kn;
                                 *reinterpret_cast<uint4 *>(const_cast<char *>(ld.kbase) + patch_dst + lane * 16) = Kn;
                             }
                             if (lane < 16) {                     // piece `lane` of the V row to its page
                                 char *vdst = const_cast<char *>(ld.vbase) + patch_dst;
-                                if constexpr (KV8) *reinterpret_cast<uint2 *>(vdst + lane * 8) = make_uint2(Vn.x, Vn.y);
-                                else *reinterpret_cast<uint4 *>(vdst + lane * 16) = Vn;
+                                vdst += lane * kVStep;
+                                if constexpr (C::kVDwords == 2) {
+                                    *reinterpret_cast<uint2 *>(vdst) = make_uint2(Vn[0], Vn[1]);
+                                } else {
+#pragma unroll
+                                    for (int h = 0; h < C::kVDwords / 4; ++h)
+                                        *reinterpret_cast<uint4 *>(vdst + h * 256) = make_uint4(Vn[4 * h], Vn[4 * h + 1], Vn[4 * h + 2], Vn[4 * h + 3]);
+                                }
                             }
 #pragma unroll
                             for (int r = 0; r < 8; ++r) {        // the lane group that holds the token takes the new V
                                 if (slot_token(j, r) == patch_row) {
-                                    if constexpr (KV8) Vr[r] = make_uint2(Vn.x, Vn.y); else V[r] = Vn;
+#pragma unroll
+                                    for (int w = 0; w < C::kVDwords; ++w) Vr[r][w] = Vn[w];
                                 }
                             }
                             patch_row = -1;
                         }
                     }
                     ks_cur[0] = ks[0]; ks_cur[1] = ks[1];
-                    if constexpr (KV8) ld8.read_k_staged(kstage, Kr); else ld.read_k_staged(kstage, K);
+                    if constexpr (kHalves) {
+                        f32x4_t s0 = {0.f, 0.f, 0.f, 0.f};
+                        ld.read_k_staged_half(kstage, 0, K);
+                        mfma_scores_f32_half<F>(K, Q, s0);
+                        __builtin_amdgcn_sched_barrier(0);       // the second half's operands take the first half's registers
+                        ld.read_k_staged_half(kstage, 1, K);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) sv[i] = s0[i] * p.scale_log2;
+                    } else {
+                        ld.read_k_staged(kstage, K);
+                    }
                     __builtin_amdgcn_s_waitcnt(0xc07f);          // operands are in registers (lgkmcnt = 0) ...
                     if (more) {                                  // ... so the next tile may take their place
                         if (nxt.append) { if constexpr (kPatchAppend) request_new_row(nxt); else append_row(nxt); }
                         issue_k(nxt.pg0, nxt.pg1);
                     }
-                    if constexpr (KV8) mfma_scores_fp8(Kr, Q, sv, p.scale_log2, ks_cur);
-                    else mfma_scores(K, Q, sv, p.scale_log2);
+                    if constexpr (kHalves) {
+                        f32x4_t s1 = {0.f, 0.f, 0.f, 0.f};
+                        mfma_scores_f32_half<F>(K, Q, s1);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) sv[4 + i] = s1[i] * p.scale_log2;
+                    } else {
+                        mfma_scores<F>(K, Q, sv, p.scale_log2, ks_cur);
+                    }
                 } else {
-                    if constexpr (KV8) mfma_scores_fp8(Kr, Q, sv, p.scale_log2, ks);
-                    else mfma_scores(K, Q, sv, p.scale_log2);
+                    mfma_scores<F>(K, Q, sv, p.scale_log2, ks);
                     if (more) {
                         if (nxt.append) append_row(nxt);
                         issue_k(nxt.pg0, nxt.pg1);
                         if (nxt.req != seg.b) load_q(nxt.req, Q);
                     }
                 }
-                if constexpr (KV8) {
+                auto request_next = [&]() __attribute__((always_inline)) {
+                    if (!more) return;
+                    if (KST && nxt.req != seg.b) load_q(nxt.req, Q);
+                    issue_v(nxt.pg0, nxt.pg1);
+                };
+                if constexpr (C::kFp8) {
                     const float v0 = vs[0], v1 = vs[1];          // of the current tile: the next V request replaces them
+                    uint32_t V[8][4];
 #pragma unroll
-                    for (int r = 0; r < 8; ++r) V[r] = fp8x8_to_bf16x8(Vr[r].x, Vr[r].y);
-                    if (more) {                                  // the raw V bytes are consumed: request the next ones
-                        if (KST && nxt.req != seg.b) load_q(nxt.req, Q);
-                        issue_v(nxt.pg0, nxt.pg1);
+                    for (int r = 0; r < 8; ++r) {
+                        const uint4 x = fp8x8_to_bf16x8(Vr[r][0], Vr[r][1]);
+                        V[r][0] = x.x; V[r][1] = x.y; V[r][2] = x.z; V[r][3] = x.w;
                     }
-                    mfma_softmax_pv<true, MT>(sv, V, st, cur.tile * kTile, seg.L, seg.L - col_back, t1min, j, v0, v1);
+                    request_next();                              // the raw V bytes are consumed: request the next ones
+                    mfma_softmax_pv<F, MT>(sv, V, st, cur.tile * kTile, seg.L, seg.L - col_back, t1min, j, v0, v1);
                 } else {
-                    mfma_softmax_pv<false, MT>(sv, V, st, cur.tile * kTile, seg.L, seg.L - col_back, t1min, j);
-                    if (more) {
-                        if (KST && nxt.req != seg.b) load_q(nxt.req, Q);
-                        issue_v(nxt.pg0, nxt.pg1);
-                    }
+                    mfma_softmax_pv<F, MT>(sv, Vr, st, cur.tile * kTile, seg.L, seg.L - col_back, t1min, j, 1.f, 1.f);
+                    request_next();
                 }
                 ++s; cur = nxt;
             }
@@ -737,14 +803,14 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(AttnParams p) 
             float *state = ring + (size_t)(wbase + nstate) * state_floats;
             ++nstate;
             if (col < Gq) {
-                float *orow = state + col * (D + 4);
+                float *orow = state + col * (D + 4);             // four dims per store: see the V loads for which block holds them
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    float4 lo4 = make_float4(st.acc[0][i], st.acc[1][i], st.acc[2][i], st.acc[3][i]);
-                    float4 hi4 = make_float4(st.acc[4][i], st.acc[5][i], st.acc[6][i], st.acc[7][i]);
-                    *reinterpret_cast<float4 *>(orow + 32 * j + 8 * i) = lo4;
-                    *reinterpret_cast<float4 *>(orow + 32 * j + 8 * i + 4) = hi4;
-                }
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int h = 0; h < C::kBlocks / 4; ++h) {
+                        const int at = F == kF32D128 ? 64 * h + 16 * j + 4 * i : (4 * j + i) * C::kBlocks + 4 * h;
+                        *reinterpret_cast<float4 *>(orow + at) = make_float4(st.acc[4 * h][i], st.acc[4 * h + 1][i], st.acc[4 * h + 2][i], st.acc[4 * h + 3][i]);
+                    }
                 if (j == 0) {
                     float *sm_m = state + Gq * (D + 4);
                     sm_m[col] = st.m; sm_m[kMaxGroup + col] = st.l;

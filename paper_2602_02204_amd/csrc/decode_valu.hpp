@@ -1,4 +1,4 @@
-// Vector-ALU split-context decode kernel: covers fp32 and bf16 KV, head_dim 64 and 128, page sizes 16 and 32, any
+// Vector-ALU split-context decode kernel (OMNI_TUNE_KERNEL = 1, and the cross-check of the matrix-core kernel): covers fp32 and bf16 KV, head_dim 64 and 128, page sizes 16 and 32, any
 // group size up to GP.  A workgroup walks the segments of its ranges (see plan.hpp) for one KV head; within a segment
 // each wave streams whole token rows with 16-byte loads (a row of D elements is spread over D*es/16 adjacent lanes),
 // keeps one online-softmax state per lane group, and the states are merged by cross-lane shuffles, then through LDS.

@@ -25,6 +25,10 @@ constexpr int kMaxBatch = 4096;                      // the plan keeps 2 * batch
 // Dynamic shared memory any layout of the matrix-core kernel may ask for: normally half a compute unit's 160 KB, and up
 // to a whole one (less the static staging area and the kernel's own variables) for the largest batches with 16 columns.
 constexpr int kMaxDynamicLds = 160 * 1024 - kWaves * kKStageBytes - 1024;
+int max_dynamic_lds(int static_bytes) {                          // the same for a variant with more static memory (512-byte rows)
+    const int left = 160 * 1024 - static_bytes - 1024;
+    return left < kMaxDynamicLds ? left : kMaxDynamicLds;
+}
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -47,7 +51,8 @@ struct omni_handle_s {
     int tune_query_tokens = 1;
     int tune_prefill_sort = 1;
     // derived
-    int kernel = 1;              // 1 = vector ALU, 2 = MFMA
+    int kernel = 1;              // what omni_get_plan reports: 2 = 16-bit matrix-core kernel, 1 = fp32-exact weights
+    bool mfma = false;           // the matrix-core kernel runs (else the vector-ALU kernel)
     int G = 1;
     int pass_tokens = 1;         // query tokens per request one launch of the attention kernel covers
     int max_ctx = 0;
@@ -94,6 +99,11 @@ struct omni_handle_s {
         const bool fp8 = d.kv_dtype == OMNI_FP8_E4M3;
         const bool mfma_ok = (d.kv_dtype == OMNI_BF16 || fp8) && d.head_dim == 128;
         kernel = fp8 ? 2 : ((tune_kernel == 2 && mfma_ok) ? 2 : (tune_kernel == 1 ? 1 : (mfma_ok ? 2 : 1)));
+        // Every other fp32 / bf16 cache runs the same matrix-core kernel with fp32-exact weights unless the vector-ALU kernel
+        // is asked for.  Measured against it over group sizes 1 .. 16, 0.1 MB .. 1.2 GB of cache per step: 1.3 - 7.8 x faster
+        // for bf16 / head_dim 64 (256 speech-token requests 81 -> 22.5 us), 1.3 - 4.5 x for fp32 / 64, 1.4 - 5.2 x for
+        // fp32 / 128; nowhere slower.
+        mfma = kernel == 2 || tune_kernel != 1;
         nw = tune_target_wgs / d.num_kv_heads;
         if (nw < 1) nw = 1;
         // query tokens one launch takes: as many as fit the 16 columns of a KV head's tiles; more go in several passes
@@ -103,7 +113,8 @@ struct omni_handle_s {
         const bool mt = tune_query_tokens > 1;
         // K goes through the staging area wherever the states' area beside it still holds five states (two requests
         // per chunk) with two workgroups per compute unit
-        const MfmaLds plain = mfma_lds_layout(d.batch, Gq, fp8, false, mt), staged = mfma_lds_layout(d.batch, Gq, fp8, true, mt);
+        const MfmaLds plain = mfma_lds_layout(d.batch, Gq, d.head_dim, d.head_dim * elem_bytes(d.kv_dtype), false, mt),
+                      staged = mfma_lds_layout(d.batch, Gq, d.head_dim, d.head_dim * elem_bytes(d.kv_dtype), true, mt);
         k_staged = staged.two_per_cu && staged.ring_states >= kWaves + 1;
         lds = k_staged ? staged : plain;
         lds_attr_set = false;
@@ -263,6 +274,20 @@ void launch_valu(const AttnParams &p, dim3 grid, size_t dyn, hipStream_t s) {
     else decode_valu_kernel<T, D, 16><<<grid, kThreads, dyn, s>>>(p);
 }
 
+// The variant of the matrix-core kernel a handle launches: page size, cache format, K staging, query tokens per request.
+template <CacheFormat F, bool MT>
+const void *mfma_variant_of(bool ps16, bool staged) {
+    return ps16 ? (staged ? (const void *)&decode_mfma_kernel<16, F, true, MT> : (const void *)&decode_mfma_kernel<16, F, false, MT>)
+                : (staged ? (const void *)&decode_mfma_kernel<32, F, true, MT> : (const void *)&decode_mfma_kernel<32, F, false, MT>);
+}
+const void *mfma_variant(const omni_handle_s *h) {
+    const bool ps16 = h->d.page_size == 16, st = h->k_staged, d64 = h->d.head_dim == 64, mt = h->tune_query_tokens > 1;
+    if (h->d.kv_dtype == OMNI_FP8_E4M3) return mt ? mfma_variant_of<kFp8D128, true>(ps16, st) : mfma_variant_of<kFp8D128, false>(ps16, st);
+    if (h->d.kv_dtype == OMNI_F32) return d64 ? mfma_variant_of<kF32D64, false>(ps16, st) : mfma_variant_of<kF32D128, false>(ps16, st);
+    if (d64) return mfma_variant_of<kBf16D64, false>(ps16, st);
+    return mt ? mfma_variant_of<kBf16D128, true>(ps16, st) : mfma_variant_of<kBf16D128, false>(ps16, st);
+}
+
 }  // namespace
 
 extern "C" {
@@ -270,21 +295,6 @@ extern "C" {
 static omni_status_t launch_append(omni_handle_t h, const void *k_new, const void *v_new, void *k_cache, void *v_cache,
                                    const int32_t *block_table, const int32_t *positions, int positions_are_lengths,
                                    void *stream);
-
-// The variant of the matrix-core kernel a handle launches: page size, cache width, K staging, query tokens per request.
-static const void *mfma_variant(const omni_handle_s *h) {
-    const bool ps16 = h->d.page_size == 16, st = h->k_staged, fp8 = h->d.kv_dtype == OMNI_FP8_E4M3;
-    if (h->tune_query_tokens > 1) {
-        if (fp8) return ps16 ? (st ? (const void *)&decode_mfma_kernel<16, true, true, true> : (const void *)&decode_mfma_kernel<16, true, false, true>)
-                             : (st ? (const void *)&decode_mfma_kernel<32, true, true, true> : (const void *)&decode_mfma_kernel<32, true, false, true>);
-        return ps16 ? (st ? (const void *)&decode_mfma_kernel<16, false, true, true> : (const void *)&decode_mfma_kernel<16, false, false, true>)
-                    : (st ? (const void *)&decode_mfma_kernel<32, false, true, true> : (const void *)&decode_mfma_kernel<32, false, false, true>);
-    }
-    if (fp8) return ps16 ? (st ? (const void *)&decode_mfma_kernel<16, true, true> : (const void *)&decode_mfma_kernel<16, true, false>)
-                         : (st ? (const void *)&decode_mfma_kernel<32, true, true> : (const void *)&decode_mfma_kernel<32, true, false>);
-    return ps16 ? (st ? (const void *)&decode_mfma_kernel<16, false, true> : (const void *)&decode_mfma_kernel<16, false, false>)
-                : (st ? (const void *)&decode_mfma_kernel<32, false, true> : (const void *)&decode_mfma_kernel<32, false, false>);
-}
 
 // The attention launch shared by omni_paged_decode_attn (k_new = v_new = null) and omni_decode_step.
 // `ws_base` = null: the workspace the caller registered with the handle; else a buffer of at least h->ws_bytes.
@@ -339,14 +349,14 @@ static omni_status_t launch_attention(omni_handle_t h, const void *q, const void
         const bool prof = (size_t)(2 * h->prof_used + 1) < h->prof_events.size() && (h->prof_calls++ % h->prof_stride) == 0;
         // Profiled launches of the matrix-core kernel carry their event pair in the dispatch itself (the events then hold
         // the kernel's own start and stop times); around the other kernels the pair is recorded on the stream.
-        const bool prof_in_dispatch = prof && h->kernel == 2;
+        const bool prof_in_dispatch = prof && h->mfma;
         if (prof && !prof_in_dispatch && hipEventRecord(h->prof_events[2 * h->prof_used], s) != hipSuccess) return OMNI_ERR_HIP;
-        if (h->kernel == 2) {
+        if (h->mfma) {
             const void *fn = mfma_variant(h);
             if (!h->lds_attr_set) {          // more than the default 64 KB of dynamic shared memory: the setting belongs to
                                              // the kernel, not to the handle, so every handle asks for the same bound (what
                                              // any layout may use) and none lowers what another one needs
-                if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxDynamicLds) != hipSuccess) {
+                if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, max_dynamic_lds(h->lds.static_bytes)) != hipSuccess) {
                     (void)hipGetLastError();
                     return OMNI_ERR_HIP;
                 }
@@ -444,7 +454,7 @@ omni_status_t omni_decode_step(omni_handle_t h, const void *q, const void *k_new
                                void *v_cache, const int32_t *block_table, const int32_t *context_lens, float scale,
                                void *out, void *stream) {
     if (!h || !k_new || !v_new) return OMNI_ERR_NULL;
-    if (h->kernel == 2)          // the MFMA kernel writes the new rows itself, just before it reads their tiles
+    if (h->mfma)                 // the MFMA kernel writes the new rows itself, just before it reads their tiles
         return launch_attention(h, q, k_new, v_new, k_cache, v_cache, block_table, context_lens, scale, out, stream);
     if (!q || !k_cache || !v_cache || !block_table || !context_lens || !out) return OMNI_ERR_NULL;
     if (!h->ws || h->ws_given < h->ws_bytes) return OMNI_ERR_WORKSPACE;
@@ -518,9 +528,9 @@ omni_status_t omni_debug_last_plan(omni_handle_t h, int32_t host_out[4], void *s
 
 omni_status_t omni_debug_lds_layout(omni_handle_t h, int32_t host_out[6]) {
     if (!h || !host_out) return OMNI_ERR_NULL;
-    if (h->kernel != 2) return OMNI_ERR_UNSUPPORTED;
+    if (!h->mfma) return OMNI_ERR_UNSUPPORTED;
     host_out[0] = h->lds.total; host_out[1] = h->lds.static_bytes; host_out[2] = h->lds.ring_states;
-    host_out[3] = h->k_staged ? 1 : 0; host_out[4] = h->lds.two_per_cu ? 1 : 0; host_out[5] = kMaxDynamicLds;
+    host_out[3] = h->k_staged ? 1 : 0; host_out[4] = h->lds.two_per_cu ? 1 : 0; host_out[5] = max_dynamic_lds(h->lds.static_bytes);
     return OMNI_OK;
 }
 
@@ -529,7 +539,7 @@ omni_status_t omni_debug_kernel_resources(omni_handle_t h, int32_t which, int32_
     const void *fn = nullptr;
     int dyn = 0;
     if (which == 0) {
-        if (h->kernel != 2) return OMNI_ERR_UNSUPPORTED;
+        if (!h->mfma) return OMNI_ERR_UNSUPPORTED;
         fn = mfma_variant(h);
         dyn = h->lds.total;
     } else if (which == 1) {
