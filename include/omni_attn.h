@@ -282,11 +282,13 @@ omni_status_t omni_kv_unpack(omni_handle_t h, const void *k_dense, const void *v
  * bf16 q/K/V with head_dim 128 run on the matrix cores (fp32 accumulation).  There V enters the weighted sum as
  * fp16: exact for 2^-14 <= |V| <= 65504; a smaller value carries an absolute error of at most 2^-25; a larger one (or a
  * non-finite one) makes non-finite outputs for the queries of its request whose tiles reach it, never wrong finite
- * ones; and scale must be positive.  Every other fp32 / bf16 configuration (and this one under OMNI_TUNE_KERNEL = 1)
- * runs a plain vector-ALU kernel in fp32 arithmetic, without those two conditions.  An 8-bit cache:
- * OMNI_ERR_UNSUPPORTED here, see omni_paged_prefill_attn_fp8.
+ * ones; and scale must be positive.  bf16 with head_dim 64 runs on the matrix cores too, with V as it is and weights of
+ * 24 bits (a non-finite V row of the chunk then reaches every query whose tiles hold it, also earlier ones).  fp32
+ * configurations (and bf16 ones under OMNI_TUNE_KERNEL = 1, and head_dim 64 with a scale that is not positive) run a plain
+ * vector-ALU kernel in fp32 arithmetic, without those conditions.  An 8-bit cache: OMNI_ERR_UNSUPPORTED here, see
+ * omni_paged_prefill_attn_fp8.
  * One launch and no workspace, unless the call would leave most of the chip idle (few requests, short chunks: a
- * workgroup owns floor(256 / group size) query tokens of one request and KV head) and the registered workspace holds
+ * workgroup owns floor(256 / group size) query tokens of one request and KV head, half as many with head_dim 64) and the registered workspace holds
  * at least omni_prefill_workspace_bytes(max_q_len): then the matrix-core path lets up to 16 workgroups share a
  * query block's context in equal runs of 64-token steps (as many as the context gives OMNI_TUNE_PREFILL_MIN_SPLIT
  * tokens each), and a second launch merges their pieces (log-sum-exp, in order of position: the same exact
@@ -294,7 +296,7 @@ omni_status_t omni_kv_unpack(omni_handle_t h, const void *k_dense, const void *v
  * only, so the result is bit-identical from run to run.  With a registered workspace and more than 256 workgroups a
  * one-workgroup launch first ranks the requests by context length, and the kernel takes them longest first (the order
  * changes when a workgroup runs, not what it computes).
- * Errors: NULL, SHAPE (max_q_len <= 0, scale <= 0 on the matrix-core path, alignment), UNSUPPORTED, HIP.
+ * Errors: NULL, SHAPE (max_q_len <= 0, scale <= 0 with 128-dim heads on the matrix-core path, alignment), UNSUPPORTED, HIP.
  */
 omni_status_t omni_paged_prefill_attn(omni_handle_t h, const void *q, const void *k_cache, const void *v_cache,
                                       const int32_t *block_table, const int32_t *context_lens, const int32_t *q_lens,

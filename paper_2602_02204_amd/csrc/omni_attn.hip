@@ -12,6 +12,7 @@
 #include "aux_kernels.hpp"
 #include "decode_mfma.hpp"
 #include "decode_valu.hpp"
+#include "prefill_exact.hpp"
 #include "prefill_mfma.hpp"
 #include "prefill_valu.hpp"
 
@@ -69,13 +70,15 @@ struct omni_handle_s {
     std::vector<hipEvent_t> prof_events;
     int prof_used = 0, prof_stride = 1, prof_calls = 0;
 
+    // The multi-token call runs a matrix-core kernel (else the vector-ALU kernel, which every format can be sent to but
+    // the 8-bit one).
+    bool prefill_mfma() const { return (d.kv_dtype == OMNI_BF16 && tune_kernel != 1) || d.kv_dtype == OMNI_FP8_E4M3; }
     // Context split of the multi-token-query kernel for chunks of up to max_q_len tokens: where the query blocks fill
     // at most half of the compute units, as many workgroups per (query block, KV head, request) as it takes to fill
     // them, at most 16 and no more than the longest context the handle allows can use.  1 = no split.
     int prefill_splits(int max_q_len) const {
-        const bool mfma = (d.kv_dtype == OMNI_BF16 && d.head_dim == 128 && tune_kernel != 1) || d.kv_dtype == OMNI_FP8_E4M3;
-        if (!mfma || tune_prefill_splits == 1) return 1;
-        const int qb = prefill_tokens_per_block(G);
+        if (!prefill_mfma() || tune_prefill_splits == 1) return 1;
+        const int qb = prefill_tokens_per_block(G, d.head_dim);
         const long long wgs = (long long)((max_q_len + qb - 1) / qb) * d.num_kv_heads * d.batch;
         const int by_ctx = (max_ctx + 2 * kTile - 1) / (2 * kTile) / (tune_prefill_min_split / (2 * kTile));
         int ns = tune_prefill_splits > 1 ? tune_prefill_splits : (wgs > 128 ? 1 : (int)(256 / wgs));
@@ -682,7 +685,10 @@ static omni_status_t launch_prefill(omni_handle_t h, const void *q, const void *
     const bool fp8 = d.kv_dtype == OMNI_FP8_E4M3;
     if (fp8 != (k_scale != nullptr)) return OMNI_ERR_UNSUPPORTED;
     if (fp8 && (!v_scale || misaligned(k_scale, 4) || misaligned(v_scale, 4))) return v_scale ? OMNI_ERR_SHAPE : OMNI_ERR_NULL;
-    const bool mfma = fp8 || (d.kv_dtype == OMNI_BF16 && d.head_dim == 128 && h->tune_kernel != 1);
+    // The matrix-core kernels take the largest raw score for the largest scaled one, so they need a positive scale: with
+    // another one 64-dim heads run the vector-ALU kernel (128-dim heads refuse it).
+    const bool d64 = d.head_dim == 64;
+    const bool mfma = h->prefill_mfma() && (!d64 || scale > 0.f);
     if (max_q_len <= 0 || (mfma && !(scale > 0.f))) return OMNI_ERR_SHAPE;
     if (misaligned(q, 16) || misaligned(k_cache, 16) || misaligned(v_cache, 16) || misaligned(out, 16) ||
         misaligned(block_table, 4) || misaligned(context_lens, 4) || misaligned(q_lens, 4) || misaligned(q_offsets, 8))
@@ -696,7 +702,7 @@ static omni_status_t launch_prefill(omni_handle_t h, const void *q, const void *
     p.scale_log2 = scale * kLog2e;
     p.Hq = d.num_q_heads; p.Hkv = d.num_kv_heads; p.G = h->G; p.MB = d.max_blocks_per_seq;
     p.out_bf16 = d.out_dtype == OMNI_BF16;
-    const int qb = mfma ? prefill_tokens_per_block(h->G) : kWaves;       // query tokens per workgroup
+    const int qb = mfma ? prefill_tokens_per_block(h->G, d.head_dim) : kWaves;       // query tokens per workgroup
     // The context is split only if the registered workspace holds the pieces (omni_prefill_workspace_bytes).
     int ns = mfma ? h->prefill_splits(max_q_len) : 1;
     if (ns > 1 && (!h->ws || h->ws_given < h->prefill_ws_bytes(max_q_len))) ns = 1;
@@ -723,14 +729,19 @@ static omni_status_t launch_prefill(omni_handle_t h, const void *q, const void *
         if (fp8) {
             if (d.page_size == 16) prefill_mfma_kernel<16, true><<<grid, kPrefillThreads, 0, s>>>(p);
             else prefill_mfma_kernel<32, true><<<grid, kPrefillThreads, 0, s>>>(p);
+        } else if (d64) {
+            if (d.page_size == 16) prefill_exact_kernel<16><<<grid, kPrefillExactThreads, 0, s>>>(p);
+            else prefill_exact_kernel<32><<<grid, kPrefillExactThreads, 0, s>>>(p);
         } else {
             if (d.page_size == 16) prefill_mfma_kernel<16><<<grid, kPrefillThreads, 0, s>>>(p);
             else prefill_mfma_kernel<32><<<grid, kPrefillThreads, 0, s>>>(p);
         }
         if (ns > 1) {
             if (hipGetLastError() != hipSuccess) return OMNI_ERR_HIP;
-            const long long items = (long long)max_q_len * d.num_q_heads * 32;
-            prefill_merge_kernel<<<dim3((unsigned)((items + kThreads - 1) / kThreads), (unsigned)d.batch), kThreads, 0, s>>>(p);
+            const long long items = (long long)max_q_len * d.num_q_heads * (d.head_dim / 4);
+            const dim3 mgrid((unsigned)((items + kThreads - 1) / kThreads), (unsigned)d.batch);
+            if (d64) prefill_merge_kernel<64><<<mgrid, kThreads, 0, s>>>(p);
+            else prefill_merge_kernel<128><<<mgrid, kThreads, 0, s>>>(p);
         }
     } else {
         const int l2 = ilog2(d.page_size);

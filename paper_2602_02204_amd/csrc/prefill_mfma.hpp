@@ -112,9 +112,10 @@ __device__ __forceinline__ int prefill_effective_splits(int num_splits, int n_st
     return max(1, min(num_splits, n_steps / min_split_steps));
 }
 
-// Query tokens per workgroup for a group of G heads: its 256 columns are the (token, head) pairs in token-major order,
-// cut into runs of 32 for the waves wherever that falls.
-__host__ __device__ inline int prefill_tokens_per_block(int G) { return kPrefillWaves * kPrefillCols / G; }
+// Query tokens per workgroup for a group of G heads: its 256 columns (128 with 64-dim heads) are the (token, head) pairs
+// in token-major order, cut into runs of 32 for the waves wherever that falls.
+__host__ __device__ constexpr int prefill_columns(int D) { return D == 64 ? 128 : kPrefillWaves * kPrefillCols; }
+__host__ __device__ inline int prefill_tokens_per_block(int G, int D) { return prefill_columns(D) / G; }
 
 // KV8: the pools hold 8-bit E4M3 bytes with one scale per (page, KV head).  The staging threads widen K to bf16
 // (exact) and V times its page's scale to fp16 (one rounding, 2^-12 relative: the size of the weights' own rounding) on
@@ -136,7 +137,7 @@ __global__ __launch_bounds__(kPrefillThreads, 1) void prefill_mfma_kernel(Prefil
     const int L = p.context_lens[b];
     const int n_q = min(p.q_lens[b], L);
     const int n_live = min(n_q, p.max_q_len);                    // a chunk longer than the grid's bound is cut off there
-    const int QB = prefill_tokens_per_block(G);
+    const int QB = prefill_tokens_per_block(G, D);
     const int NS = p.num_splits;
     const int split = NS > 1 ? (int)blockIdx.x % NS : 0;
     const int q0 = (NS > 1 ? (int)blockIdx.x / NS : (int)blockIdx.x) * QB;      // first query token of this workgroup
@@ -461,13 +462,14 @@ __global__ __launch_bounds__(kPrefillOrderMax) void prefill_order_kernel(const i
 
 // Merge of a context split: out row = sum_s 2^(m_s - M) o_s / sum_s 2^(m_s - M) l_s over the pieces with l_s > 0, in
 // split order (M = the largest reference among them; any common reference gives the same quotient).  One thread per
-// four output elements of one (query token, head); grid (ceil(max_q_len * Hq * 32 / 256), B).
+// four output elements of one (query token, head); grid (ceil(max_q_len * Hq * D / 4 / 256), B).
+template <int D>
 __global__ __launch_bounds__(kThreads) void prefill_merge_kernel(PrefillParams p) {
-    constexpr int D = 128;
+    constexpr int kRowThreads = D / 4;
     const int b = blockIdx.y;
     const long long lin = (long long)blockIdx.x * kThreads + threadIdx.x;
-    const int d4 = (int)(lin & 31);
-    const long long rh = lin >> 5;
+    const int d4 = (int)(lin % kRowThreads);
+    const long long rh = lin / kRowThreads;
     const int head = (int)(rh % p.Hq);
     const long long qi = rh / p.Hq;
     const int L = p.context_lens[b];
@@ -475,7 +477,7 @@ __global__ __launch_bounds__(kThreads) void prefill_merge_kernel(PrefillParams p
     const int n_live = min(n_q, p.max_q_len);
     if (qi >= n_live) return;
     // the split count of the row's query block, as the attention kernel derived it
-    const int QB = prefill_tokens_per_block(p.G);
+    const int QB = prefill_tokens_per_block(p.G, D);
     const int wg_last = min(n_live, ((int)qi / QB + 1) * QB) - 1;
     const int n_tiles = (L - n_q + wg_last) / kTile + 1;
     const int ns_eff = prefill_effective_splits(p.num_splits, (n_tiles + 1) >> 1, p.min_split_steps);

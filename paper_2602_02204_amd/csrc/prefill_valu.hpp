@@ -1,6 +1,6 @@
 // Vector-ALU kernel for multi-token queries over the paged cache: every dtype and head size the library knows
-// (fp32 / bf16, head_dim 64 / 128).  It is the fp32-exact path of the multi-token call (tolerance 1e-5 on fp32
-// caches) and the fallback where the matrix-core kernel does not apply; it is not tuned.
+// (fp32 / bf16, head_dim 64 / 128).  It is the multi-token call's path for fp32 caches (tolerance 1e-5), for bf16 caches
+// with 64-dim heads where the scale is not positive, and for any 16-bit cache on request; it is not tuned.
 //
 // A wave owns one query token of one (request, KV head) and walks the token's whole context, four tokens at a time:
 // lane group tg = lane / 16 takes token t + tg, and the 16 lanes of a group each hold D / 16 consecutive dims of the

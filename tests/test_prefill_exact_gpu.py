@@ -1,0 +1,76 @@
+"""The matrix-core kernel for multi-token queries over bf16 caches with 64-dim heads, whose softmax weights keep 24 bits.
+
+Bar: the vector-ALU kernel's 1e-5 (exact products, fp32 sums of values around one).
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2602_02204_amd import binding as omni
+from paper_2602_02204_amd import workloads as W
+from gpu_util import DeviceBatch
+from test_prefill_gpu import ChunkOnDevice, run_chunk
+
+pytestmark = pytest.mark.gpu
+
+# one token, tile / step / page edges, empty, more tokens than one workgroup's columns hold, contexts before the chunk
+LENS = [1, 31, 32, 33, 63, 64, 65, 0, 127, 129, 300, 700, 96, 40]
+Q_LENS = [1, 31, 1, 33, 2, 64, 65, 0, 3, 129, 17, 150, 0, 40]
+
+
+def reference(wl, ch, scale=None):
+    oracle.kv_append_chunk(ch.k_new, ch.v_new, wl.k_cache, wl.v_cache, wl.block_table, wl.context_lens, ch.q_lens, ch.q_offsets)
+    return oracle.paged_prefill_attn(ch.q, wl.k_cache, wl.v_cache, wl.block_table, wl.context_lens, ch.q_lens, ch.q_offsets,
+                                     wl.scale if scale is None else scale, wl.dtype)
+
+
+@pytest.mark.parametrize("ps", [16, 32])
+@pytest.mark.parametrize("G,Hkv", [(1, 3), (3, 1), (7, 2), (8, 2), (16, 1)])
+def test_tile_and_block_edges_with_and_without_a_context_split(G, Hkv, ps):
+    wl = W.build("edge", 41 + G, LENS, Hq=G * Hkv, Hkv=Hkv, D=64, ps=ps, dtype=W.BF16, pool_factor=1.3)
+    ch = W.add_chunk(wl, Q_LENS, 42, gap=1)
+    ref, owned = None, np.concatenate([np.arange(o, o + n) for o, n in zip(ch.q_offsets, ch.q_lens)])
+    for tuning in ({omni.OMNI_TUNE_PREFILL_SPLITS: 1}, {omni.OMNI_TUNE_PREFILL_SPLITS: 5, omni.OMNI_TUNE_PREFILL_MIN_SPLIT: 64}):
+        _, got = run_chunk(wl, ch, tuning=tuning, split_workspace=True)
+        ref = reference(wl, ch) if ref is None else ref
+        assert np.max(np.abs(got[owned] - ref[owned])) <= 1e-5
+        assert np.all(np.isnan(np.delete(got, owned, axis=0)))
+
+
+@pytest.mark.parametrize("gain", [0.0, 1.0, 30.0, 1000.0])
+def test_peaked_and_growing_scores_move_the_reference(gain):
+    """Keys grow along the context, so the reference moves again and again.  A relative error of 2^-23 of the largest score
+    (at most gain * 64 * 4 log2 units; a peaked softmax compares few of them) is an error of a weight."""
+    wl = W.build("grow", 51, [400, 333], Hq=8, Hkv=2, D=64, ps=16, dtype=W.BF16)
+    ramp = W.f32_to_bf16_bits((gain * np.linspace(0, 1, 25)).astype(np.float32))
+    for b in range(2):
+        for i, page in enumerate(wl.block_table[b][:-(-int(wl.context_lens[b]) // 16)]):
+            wl.k_cache[page, :, :, 0] = ramp[i]
+    ch = W.add_chunk(wl, [100, 333], 52)
+    ch.q[..., 0] = W.f32_to_bf16_bits(np.full(1, 1.0, np.float32))[0]
+    _, got = run_chunk(wl, ch)
+    assert np.max(np.abs(got - reference(wl, ch))) <= 1e-5 + 2.0 ** -23 * gain
+
+
+@pytest.mark.parametrize("scale", [0.0, -0.125])
+def test_scales_the_matrix_core_kernel_does_not_take(scale):
+    wl = W.build("scale", 61, [100, 65], Hq=4, Hkv=2, D=64, ps=16, dtype=W.BF16)
+    ch = W.add_chunk(wl, [40, 65], 62, in_cache=True)
+    dev = DeviceBatch(wl)
+    c = ChunkOnDevice(dev, ch)
+    dev.h.omni_paged_prefill_attn(c.q, dev.k_cache, dev.v_cache, dev.block_table, dev.context_lens, c.q_lens, c.q_offsets,
+                                  ch.max_q_len, scale, c.out)
+    torch.cuda.synchronize()
+    assert np.max(np.abs(c.out.cpu().numpy() - reference(wl, ch, scale))) <= 1e-5
+
+
+def test_rows_beyond_a_cut_off_chunk_have_no_effect():
+    """Chunks longer than max_q_len: rows after the last computed token hold NaN and stay unread or weigh exactly nothing."""
+    wl = W.build("cut", 71, [150, 90], Hq=16, Hkv=2, D=64, ps=16, dtype=W.BF16)
+    ch = W.add_chunk(wl, [100, 60], 72, in_cache=False)                          # the chunk's rows are NaN until appended
+    _, got = run_chunk(wl, ch, max_q_len=37)
+    ref = reference(wl, ch)
+    for o, n in zip(ch.q_offsets, ch.q_lens):
+        assert np.max(np.abs(got[o:o + 37] - ref[o:o + 37])) <= 1e-5
+        assert np.all(np.isnan(got[o + 37:o + n]))
