@@ -321,7 +321,7 @@ omni_status_t omni_kv_append_chunk(omni_handle_t h, const void *k_new, const voi
 
 /* Host-known part of the launch plan: which kernel (2 = 16-bit matrix-core kernel, softmax weights kept to 2^-16; 1 = a
  * kernel with fp32-exact weights: vector ALUs, or matrix cores for fp32 caches and head_dim 64), the data-independent
- * grid (workgroups) of the attention kernel, the grid of the merge kernel that follows it, the number of
+ * grid (workgroups) of the attention kernel, the (request, KV head) pairs the merge kernel that follows it runs over, the number of
  * partial-result slots the workspace is sized for, and threads per workgroup.  The range length itself is chosen on the device from
  * context_lens; omni_debug_last_plan reads it back. */
 omni_status_t omni_get_plan(omni_handle_t h, int32_t *kernel, int32_t *partition_grid, int32_t *merge_grid,

@@ -4,51 +4,58 @@
 
 namespace omni {
 
-// Merge kernel: one workgroup per (request, KV head), launched right after the attention kernel.  It takes the
-// request's first slot and number of pieces from the records the attention kernel's first workgroup left in the
-// workspace (one 8-byte read; scanning the lengths again in every workgroup and dividing by the range length cost
+// Merge kernel: one workgroup per (request, KV head, 1024 output elements), launched right after the attention kernel.
+// It takes the request's first slot and number of pieces from the records the attention kernel's first workgroup left in
+// the workspace (one 8-byte read; scanning the lengths again in every workgroup and dividing by the range length cost
 // 0.5 us more at 256 requests and 10 - 28 us at 1024 - 2048); for a request that was cut
 // by range boundaries combines its partial-result slots, in slot order:
 //     out = sum_j 2^(m_j - M) o_j / sum_j 2^(m_j - M) l_j,   M = max_j m_j,   pieces with l_j = 0 skipped.
 // Requests inside one range (finished by the attention kernel) and empty requests return at once.
 // Every thread owns four consecutive output elements (one 16-byte load per piece); the loads of kRound pieces are
 // issued before any is used, so a round costs one trip to memory and no load depends on a loaded value.
+// A round's pieces share one reference, so that their weights hang on nothing but their own piece (rescaled piece by
+// piece, 24 pieces were a chain of 24 exponentials behind the last load); where a request has more than 1024 elements per
+// KV head (several query tokens), each further 1024 are a workgroup of their own.  Measured: 64 requests with two query
+// tokens 60.5 -> 59.6 us per step, one request 13.0 -> 12.8 us, one token per request unchanged; workgroups of one wave or
+// rounds of 32 pieces cost a single request 0.6 - 1.0 us.
 template <int D, int kRound>
-__device__ __forceinline__ void merge_request(const AttnParams &p, int b, int kvh, int slot_first, int n) {
-    for (int idx = 4 * threadIdx.x; idx < p.Gq * D; idx += 4 * kThreads) {    // one pass up to 1024 elements
-        const int g = idx / D;                                                // column: (query token, head)
-        const size_t out0 = out_row(p, b, kvh, g) * D + (idx - g * D);
-        float M = -INFINITY, den = 0.f;
-        float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int j0 = 0; j0 < n; j0 += kRound) {
-            float2 ml[kRound];
-            float4 oj[kRound];
+__device__ __forceinline__ void merge_request(const AttnParams &p, int b, int kvh, int idx, int slot_first, int n) {
+    const int g = idx / D;                                                // column: (query token, head)
+    const size_t out0 = out_row(p, b, kvh, g) * D + (idx - g * D);
+    float M = -INFINITY, den = 0.f;
+    float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int j0 = 0; j0 < n; j0 += kRound) {
+        float2 ml[kRound];
+        float4 oj[kRound];
 #pragma unroll
-            for (int u = 0; u < kRound; ++u) {
-                ml[u] = make_float2(0.f, 0.f); oj[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (j0 + u < n) {
-                    const size_t pi = partial_row(p, slot_first + j0 + u, kvh, g);
-                    ml[u] = p.ws.part_ml[pi];
-                    oj[u] = *reinterpret_cast<const float4 *>(p.ws.part_o + pi * D + (idx - g * D));
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < kRound; ++u) {
-                if (ml[u].y > 0.f) {
-                    const float Mn = fmaxf(M, ml[u].x);
-                    const float a = fast_exp2(M - Mn);               // 0 while M is still -inf
-                    const float w = fast_exp2(ml[u].x - Mn);
-                    num.x = num.x * a + w * oj[u].x; num.y = num.y * a + w * oj[u].y;
-                    num.z = num.z * a + w * oj[u].z; num.w = num.w * a + w * oj[u].w;
-                    den = den * a + w * ml[u].y;
-                    M = Mn;
-                }
+        for (int u = 0; u < kRound; ++u) {
+            ml[u] = make_float2(0.f, 0.f); oj[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (j0 + u < n) {
+                const size_t pi = partial_row(p, slot_first + j0 + u, kvh, g);
+                ml[u] = p.ws.part_ml[pi];
+                oj[u] = *reinterpret_cast<const float4 *>(p.ws.part_o + pi * D + (idx - g * D));
             }
         }
-        const bool live = den > 0.f;
-        store_out4(p, out0, make_float4(live ? num.x / den : 0.f, live ? num.y / den : 0.f, live ? num.z / den : 0.f,
-                                        live ? num.w / den : 0.f));
+        float Mn = M;
+#pragma unroll
+        for (int u = 0; u < kRound; ++u)
+            if (ml[u].y > 0.f) Mn = fmaxf(Mn, ml[u].x);
+        const float a = M > -INFINITY ? fast_exp2(M - Mn) : 0.f;
+        num.x *= a; num.y *= a; num.z *= a; num.w *= a;
+        den *= a;
+        M = Mn;
+#pragma unroll
+        for (int u = 0; u < kRound; ++u) {
+            if (ml[u].y > 0.f) {
+                const float w = fast_exp2(ml[u].x - M);
+                num.x += w * oj[u].x; num.y += w * oj[u].y; num.z += w * oj[u].z; num.w += w * oj[u].w;
+                den += w * ml[u].y;
+            }
+        }
     }
+    const bool live = den > 0.f;
+    store_out4(p, out0, make_float4(live ? num.x / den : 0.f, live ? num.y / den : 0.f, live ? num.z / den : 0.f,
+                                    live ? num.w / den : 0.f));
 }
 
 template <int D>
@@ -56,12 +63,13 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(AttnParams p) {
     const int b = blockIdx.x / p.Hkv, kvh = blockIdx.x - b * p.Hkv;
     const int2 rec = p.ws.merge_rec[b];                      // first slot and number of pieces, from the attention kernel
     const int n = __builtin_amdgcn_readfirstlane(rec.y);
-    if (n < 2) return;                                       // no tile (its zero row is written) or finished already
+    const int idx = 4 * (int)(blockIdx.y * kThreads + threadIdx.x);
+    if (n < 2 || idx >= p.Gq * D) return;                    // no tile (its zero row is written) or finished already
     const int slot_first = __builtin_amdgcn_readfirstlane(rec.x);
     // 4, 8 or 16 pieces per round, so that a request cut into many pieces still costs few dependent trips to memory
-    if (n <= 4) merge_request<D, 4>(p, b, kvh, slot_first, n);
-    else if (n <= 8) merge_request<D, 8>(p, b, kvh, slot_first, n);
-    else merge_request<D, 16>(p, b, kvh, slot_first, n);
+    if (n <= 4) merge_request<D, 4>(p, b, kvh, idx, slot_first, n);
+    else if (n <= 8) merge_request<D, 8>(p, b, kvh, idx, slot_first, n);
+    else merge_request<D, 16>(p, b, kvh, idx, slot_first, n);
 }
 
 struct AppendParams {

@@ -389,7 +389,7 @@ static omni_status_t launch_attention(omni_handle_t h, const void *q, const void
 
         // Whether any request was cut by a range boundary is known only on the device: the merge kernel always runs, and
         // its workgroups return at once for requests that the attention kernel finished.
-        const dim3 mgrid((unsigned)(d.batch * d.num_kv_heads));
+        const dim3 mgrid((unsigned)(d.batch * d.num_kv_heads), (unsigned)((p.Gq * d.head_dim + 4 * kThreads - 1) / (4 * kThreads)));
         if (d.head_dim == 128) merge_kernel<128><<<mgrid, kThreads, 0, s>>>(p);
         else merge_kernel<64><<<mgrid, kThreads, 0, s>>>(p);
         if (hipGetLastError() != hipSuccess) return OMNI_ERR_HIP;
