@@ -9,6 +9,9 @@ namespace omni {
 
 constexpr int kMaxGroup = 16;          // query heads per KV head the kernels cover
 constexpr float kLog2e = 1.4426950408889634f;
+// Softmax reference of a column that has seen no token yet: finite, so that exp2 sees -inf - finite and never
+// -inf - -inf, and no higher than any finite score, so that it never stands in for a visible one.
+constexpr float kNoTokenReference = -3.402823466e38f;
 
 // Workspace layout (bytes from the workspace base, all 256-byte aligned):
 //   [0, 256)                 plan words written by the first workgroup: range length in tokens, number of ranges,

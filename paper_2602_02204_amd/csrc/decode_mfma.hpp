@@ -311,8 +311,8 @@ __device__ __forceinline__ void mfma_softmax_pv(float (&sv)[8], uint32_t (&V)[8]
     tmax = fmaxf(tmax, __shfl_xor(tmax, 16));
     tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
     // finite: in plain decode every tile holds a live token; with several query tokens a column may see none of a
-    // tile's, and then keeps a finite stand-in (exp2 below sees -inf - finite, never -inf - -inf)
-    const float mn = kMulti ? fmaxf(fmaxf(st.m, tmax), -1e30f) : fmaxf(st.m, tmax);
+    // tile's, and then keeps a finite stand-in
+    const float mn = kMulti ? fmaxf(fmaxf(st.m, tmax), kNoTokenReference) : fmaxf(st.m, tmax);
     const float alpha = fast_exp2(st.m - mn);
     float pw[8], psum = 0.f;
 #pragma unroll
