@@ -282,11 +282,11 @@ omni_status_t omni_kv_unpack(omni_handle_t h, const void *k_dense, const void *v
  * bf16 q/K/V with head_dim 128 run on the matrix cores (fp32 accumulation).  There V enters the weighted sum as
  * fp16: exact for 2^-14 <= |V| <= 65504; a smaller value carries an absolute error of at most 2^-25; a larger one (or a
  * non-finite one) makes non-finite outputs for the queries of its request whose tiles reach it, never wrong finite
- * ones; and scale must be positive.  bf16 with head_dim 64 runs on the matrix cores too, with V as it is and weights of
- * 24 bits (a non-finite V row of the chunk then reaches every query whose tiles hold it, also earlier ones).  fp32
+ * ones; scale must be positive, and scores |scale * q . K_t| stay below 2^26.  bf16 with head_dim 64 runs on the matrix
+ * cores too, with V as it is, weights of 24 bits and none of these conditions: queries that a non-finite V row, huge values
+ * or huge scores make unsound there are computed again row by row, at the vector-ALU kernel's speed.  fp32
  * configurations (and bf16 ones under OMNI_TUNE_KERNEL = 1, and head_dim 64 with a scale that is not positive) run a plain
- * vector-ALU kernel in fp32 arithmetic, without those conditions.  An 8-bit cache: OMNI_ERR_UNSUPPORTED here, see
- * omni_paged_prefill_attn_fp8.
+ * vector-ALU kernel in fp32 arithmetic.  An 8-bit cache: OMNI_ERR_UNSUPPORTED here, see omni_paged_prefill_attn_fp8.
  * One launch and no workspace, unless the call would leave most of the chip idle (few requests, short chunks: a
  * workgroup owns floor(256 / group size) query tokens of one request and KV head, half as many with head_dim 64) and the registered workspace holds
  * at least omni_prefill_workspace_bytes(max_q_len): then the matrix-core path lets up to 16 workgroups share a

@@ -119,7 +119,8 @@ __device__ __forceinline__ void store_out(const AttnParams &p, size_t index, flo
     else reinterpret_cast<float *>(p.out)[index] = v;
 }
 // Four consecutive output elements in one store (index a multiple of four).
-__device__ __forceinline__ void store_out4(const AttnParams &p, size_t index, const float4 &r) {
+template <typename Params>
+__device__ __forceinline__ void store_out4(const Params &p, size_t index, const float4 &r) {
     if (p.out_bf16) {
         uint2 pk;
         pk.x = (uint32_t)float_to_bf16_rne(r.x) | ((uint32_t)float_to_bf16_rne(r.y) << 16);

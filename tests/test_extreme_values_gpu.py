@@ -6,17 +6,31 @@ it is not.
 import numpy as np
 import pytest
 
+import oracle
 from paper_2602_02204_amd import binding as omni
 from paper_2602_02204_amd import workloads as W
 from gpu_util import TOL
 from test_multi_token_decode_gpu import attend, expected
+from test_prefill_gpu import run_chunk
 
 pytestmark = pytest.mark.gpu
+
+ONE_PIECE = {omni.OMNI_TUNE_PREFILL_SPLITS: 1}
+FIVE_PIECES = {omni.OMNI_TUNE_PREFILL_SPLITS: 5, omni.OMNI_TUNE_PREFILL_MIN_SPLIT: 64}
+SPLITS = pytest.mark.parametrize("tuning", [ONE_PIECE, FIVE_PIECES], ids=["one-piece", "five-pieces"])
 
 
 def tokens_of(wl, b):
     t = np.arange(int(wl.context_lens[b]))
     return wl.block_table[b, t // wl.ps], t % wl.ps
+
+
+def same_kind(got, ref, tol):
+    """Finite where the reference is, to `tol` of the larger of one and its magnitude; else the same infinity, or NaN."""
+    fin = np.isfinite(ref)
+    assert np.array_equal(np.isfinite(got), fin)
+    assert np.all(np.abs(got[fin] - ref[fin]) <= tol * np.maximum(1.0, np.abs(ref[fin])))
+    assert np.array_equal(got[~fin], ref[~fin], equal_nan=True)
 
 
 def along_dim_0(shape):
@@ -44,3 +58,59 @@ def test_decode_of_several_tokens_whose_scores_all_lie_far_below_zero(part, risi
     _, got = attend(wl, q, 3, {omni.OMNI_TUNE_FORCE_PARTITION: part})
     want = expected(wl, q, 3)
     assert np.max(np.abs(got - want)) <= TOL[W.BF16]
+
+
+@pytest.mark.parametrize("rising", [False, True], ids=["falling", "rising"])
+@SPLITS
+def test_chunk_whose_scores_all_lie_far_below_zero(tuning, rising):
+    """The largest visible score is the reference however low it is, and rounding it moves no weight out of range."""
+    wl = W.build("low", 7, [100, 1, 128], Hq=4, Hkv=2, D=64, ps=16, dtype=W.BF16, scale=1.0)
+    far_below_zero(wl, rising)
+    ch = W.add_chunk(wl, [100, 1, 70], 8)
+    ch.q[:] = along_dim_0(ch.q.shape)
+    _, got = run_chunk(wl, ch, tuning={**tuning, omni.OMNI_TUNE_PREFILL_MIN_SPLIT: 64}, split_workspace=True)
+    ref = oracle.paged_prefill_attn(ch.q, wl.k_cache, wl.v_cache, wl.block_table, wl.context_lens, ch.q_lens, ch.q_offsets,
+                                    wl.scale, wl.dtype)
+    assert np.max(np.abs(got - ref)) <= 1e-5
+
+
+def put(cache, wl, b, t, dim, value):
+    pages, slots = tokens_of(wl, b)
+    enc = (lambda x: x) if wl.dtype == W.F32 else W.f32_to_bf16_bits
+    bits = W.BF16_NAN_BITS if wl.dtype == W.BF16 and np.isnan(value) else enc(np.array([value], np.float32))[0]
+    cache[pages[t], :, slots[t], dim] = bits
+
+
+@pytest.mark.parametrize("G,Hkv", [(1, 3), (5, 2), (16, 1)])
+@SPLITS
+def test_chunk_query_sees_nothing_of_values_behind_it(tuning, G, Hkv):
+    """Infinities and NaN among the chunk's own V rows: the queries in front of them get what the oracle says, in every dim,
+    the queries behind them the infinity or NaN in that dim alone."""
+    wl = W.build("behind", 17 + G, [330, 64, 40], Hq=G * Hkv, Hkv=Hkv, D=64, ps=16, dtype=W.BF16)
+    for b, t, dim, value in ((0, 299, 3, np.nan), (0, 301, 5, np.inf), (0, 321, 63, -np.inf), (1, 0, 0, np.inf),
+                             (1, 63, 0, -np.inf), (2, 38, 9, np.nan)):
+        put(wl.v_cache, wl, b, t, dim, value)
+    ch = W.add_chunk(wl, [130, 64, 3], 18)
+    _, got = run_chunk(wl, ch, tuning=tuning, split_workspace=True)
+    ref = oracle.paged_prefill_attn(ch.q, wl.k_cache, wl.v_cache, wl.block_table, wl.context_lens, ch.q_lens, ch.q_offsets,
+                                    wl.scale, wl.dtype)
+    assert np.isfinite(ref[:99]).all() and not np.isfinite(ref).all()
+    same_kind(got, ref, 1e-5)
+
+
+@SPLITS
+def test_chunk_over_values_near_the_largest_finite_one(tuning):
+    """A weighted mean of values of up to 2^120 is finite, whatever the sum of its unscaled weights does."""
+    wl = W.build("huge", 27, [400, 333], Hq=8, Hkv=2, D=64, ps=16, dtype=W.BF16)
+    big = (1 + np.abs(np.nan_to_num(W.bf16_bits_to_f32(wl.v_cache))).clip(0, 1)) * np.float32(2.0 ** 119)
+    wl.v_cache[:] = W.f32_to_bf16_bits(big)
+    ramp = W.f32_to_bf16_bits((6 * np.linspace(0, 1, 400)).astype(np.float32))
+    for b in range(2):
+        pages, slots = tokens_of(wl, b)
+        wl.k_cache[pages, :, slots, 0] = ramp[:pages.size, None]
+    ch = W.add_chunk(wl, [100, 333], 28)
+    ch.q[..., 0] = W.f32_to_bf16_bits(np.full(1, 8.0, np.float32))[0]
+    _, got = run_chunk(wl, ch, tuning=tuning, split_workspace=True)
+    ref = oracle.paged_prefill_attn(ch.q, wl.k_cache, wl.v_cache, wl.block_table, wl.context_lens, ch.q_lens, ch.q_offsets,
+                                    wl.scale, wl.dtype)
+    assert np.all(np.isfinite(got)) and np.max(np.abs(got - ref)) <= 2e-5 * 2.0 ** 120
