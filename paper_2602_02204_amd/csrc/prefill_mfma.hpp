@@ -460,7 +460,7 @@ __global__ __launch_bounds__(kPrefillOrderMax) void prefill_order_kernel(const i
     order[rank] = t;
 }
 
-// Merge of a context split: out row = sum_s 2^(m_s - M) o_s / sum_s 2^(m_s - M) l_s over the pieces with l_s > 0, in
+// Merge of a context split: out row = sum_s 2^(m_s - M) o_s / sum_s 2^(m_s - M) l_s over the pieces with l_s != 0, in
 // split order (M = the largest reference among them; any common reference gives the same quotient).  One thread per
 // four output elements of one (query token, head); grid (ceil(max_q_len * Hq * D / 4 / 256), B).
 template <int D>
@@ -488,7 +488,7 @@ __global__ __launch_bounds__(kThreads) void prefill_merge_kernel(PrefillParams p
     float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int s = 0; s < ns_eff; ++s) {
         const float2 ml = p.part_ml[pi + s];
-        if (ml.y > 0.f) {
+        if (ml.y != 0.f) {                                       // also a NaN: a piece with a NaN score must show
             const float4 o = *reinterpret_cast<const float4 *>(p.part_o + (pi + s) * D + 4 * d4);
             const float Mn = fmaxf(M, ml.x);
             const float a = fast_exp2(M - Mn);                   // 0 while M is still -inf

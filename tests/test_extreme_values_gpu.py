@@ -114,3 +114,16 @@ def test_chunk_over_values_near_the_largest_finite_one(tuning):
     ref = oracle.paged_prefill_attn(ch.q, wl.k_cache, wl.v_cache, wl.block_table, wl.context_lens, ch.q_lens, ch.q_offsets,
                                     wl.scale, wl.dtype)
     assert np.all(np.isfinite(got)) and np.max(np.abs(got - ref)) <= 2e-5 * 2.0 ** 120
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@SPLITS
+def test_a_nan_key_shows_in_every_query_that_sees_it(D, tuning):
+    """Its score is NaN and so is the softmax; a piece of a split context that holds it must not be left out of the sum."""
+    wl = W.build("nan-key", 47, [400], Hq=4, Hkv=2, D=D, ps=16, dtype=W.BF16)
+    put(wl.k_cache, wl, 0, 380, 11, np.nan)                      # query 50 of the chunk
+    ch = W.add_chunk(wl, [70], 48)
+    _, got = run_chunk(wl, ch, tuning=tuning, split_workspace=True)
+    ref = oracle.paged_prefill_attn(ch.q, wl.k_cache, wl.v_cache, wl.block_table, wl.context_lens, ch.q_lens, ch.q_offsets,
+                                    wl.scale, wl.dtype)
+    assert np.max(np.abs(got[:50] - ref[:50])) <= TOL[W.BF16] and np.all(np.isnan(got[50:]))
