@@ -255,9 +255,19 @@ __device__ __forceinline__ uint32_t upper_halves(float lo, float hi) {
 }
 __device__ __forceinline__ float below_upper_half(float x) { return x - __uint_as_float(__float_as_uint(x) & 0xffff0000u); }
 
+// Each half of `part` (bf16, not negative), or 2^-40 of the same half of `first` if that is more: never zero where `first` is
+// 2^-86 or more.
+__device__ __forceinline__ uint32_t at_least_a_trace(uint32_t part, uint32_t first) {
+    typedef unsigned short u16x2_t __attribute__((ext_vector_type(2)));
+    const u16x2_t f = __builtin_bit_cast(u16x2_t, first), shift = {40 << 7, 40 << 7};
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2_t, part), __builtin_elementwise_sub_sat(f, shift)));
+}
+
 // The eight weights of a lane as bf16 MFMA operands whose sum is the weight: two parts to ~2^-16 relative (rounded), or
-// three that hold all 24 bits (each the upper half of what the parts before it left, so nothing is rounded).
-template <int kParts>
+// three that hold all 24 bits (each the upper half of what the parts before it left, so nothing is rounded).  kTrace: a
+// lower part that has nothing left is 2^-40 of the weight instead of zero, so that an infinite V element times it is
+// infinite like its product with the first part and not NaN.
+template <int kParts, bool kTrace = false>
 __device__ __forceinline__ void split_weights(const float (&pw)[8], uint4 (&P)[kParts]) {
 #pragma clang fp contract(off)
     uint32_t d[kParts][4];
@@ -272,6 +282,7 @@ __device__ __forceinline__ void split_weights(const float (&pw)[8], uint4 (&P)[k
             const float a1 = below_upper_half(a), b1 = below_upper_half(b);
             d[1][w] = upper_halves(a1, b1);
             d[2][w] = upper_halves(below_upper_half(a1), below_upper_half(b1));
+            if constexpr (kTrace) { d[1][w] = at_least_a_trace(d[1][w], d[0][w]); d[2][w] = at_least_a_trace(d[2][w], d[0][w]); }
         }
     }
 #pragma unroll
@@ -333,7 +344,7 @@ __device__ __forceinline__ void mfma_softmax_pv(float (&sv)[8], uint32_t (&V)[8]
     } else {
         constexpr int kParts = C::D == 64 ? 3 : 2;
         uint4 P[kParts];
-        split_weights<kParts>(pw, P);
+        split_weights<kParts, true>(pw, P);
 #pragma unroll
         for (int e = 0; e < C::kBlocks; ++e) st.acc[e] *= alpha;
         // in-lane transpose: operand e holds dim e of the lane's chunk for the 8 tokens of its lane group

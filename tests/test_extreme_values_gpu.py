@@ -5,11 +5,12 @@ it is not.
 """
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from paper_2602_02204_amd import binding as omni
 from paper_2602_02204_amd import workloads as W
-from gpu_util import TOL
+from gpu_util import TOL, DeviceBatch
 from test_multi_token_decode_gpu import attend, expected
 from test_prefill_gpu import run_chunk
 
@@ -127,3 +128,30 @@ def test_a_nan_key_shows_in_every_query_that_sees_it(D, tuning):
     ref = oracle.paged_prefill_attn(ch.q, wl.k_cache, wl.v_cache, wl.block_table, wl.context_lens, ch.q_lens, ch.q_offsets,
                                     wl.scale, wl.dtype)
     assert np.max(np.abs(got[:50] - ref[:50])) <= TOL[W.BF16] and np.all(np.isnan(got[50:]))
+
+
+@pytest.mark.parametrize("fused", [False, True], ids=["attention", "fused-step"])
+@pytest.mark.parametrize("part", [0, 64], ids=["planned", "two-tile-ranges"])
+@pytest.mark.parametrize("dtype,D", [(W.F32, 64), (W.F32, 128), (W.BF16, 64)], ids=["f32-64", "f32-128", "bf16-64"])
+def test_decode_over_infinite_values(dtype, D, part, fused):
+    """An infinite V element makes its own output dim infinite (NaN where both signs meet) and leaves the others alone,
+    whatever bits the weights have: a weight of one, the only token's, among them."""
+    wl = W.build("inf", 37 + D, [1, 2, 40, 300, 129], Hq=10, Hkv=2, D=D, ps=16, dtype=dtype, append=fused)
+    for b, t, dim, value in ((0, 0, 3, np.inf), (1, 0, 5, -np.inf), (2, 38, 0, np.inf), (2, 3, 0, -np.inf), (2, 20, 63, np.nan),
+                             (3, 100, 7, np.inf), (4, 128, 9, -np.inf)):
+        new = fused and t == int(wl.context_lens[b]) - 1
+        if new:
+            wl.v_new[b, :, dim] = value if dtype == W.F32 else W.f32_to_bf16_bits(np.array([value], np.float32))[0]
+        else:
+            put(wl.v_cache, wl, b, t, dim, value)
+    dev = DeviceBatch(wl, tuning={omni.OMNI_TUNE_FORCE_PARTITION: part})
+    if fused:
+        dev.h.omni_decode_step(dev.q, dev.k_new, dev.v_new, dev.k_cache, dev.v_cache, dev.block_table, dev.context_lens,
+                               float(wl.scale), dev.out)
+        torch.cuda.synchronize()
+        got = dev.out.cpu().numpy().astype(np.float64)
+        oracle.kv_append(wl.k_new, wl.v_new, wl.k_cache, wl.v_cache, wl.block_table, wl.positions, wl.dtype)
+    else:
+        got = dev.attend()
+    same_kind(got, oracle.paged_decode_attn(wl.q, wl.k_cache, wl.v_cache, wl.block_table, wl.context_lens, wl.scale, wl.dtype),
+              1e-5)
