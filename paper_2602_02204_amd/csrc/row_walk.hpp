@@ -104,6 +104,7 @@ __device__ __forceinline__ void walk_rows(const RowSource &src, const char *q, i
     // merge the four lane groups (a group that saw no token has m = -inf, l = 0)
 #pragma unroll
     for (int h = 0; h < HC; ++h) {
+        if (h >= nh) continue;
 #pragma unroll
         for (int d = 16; d <= 32; d <<= 1) {
             const float mo = other(w.m[h], d), lo = other(w.l[h], d);
