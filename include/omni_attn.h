@@ -119,7 +119,9 @@ omni_status_t omni_workspace_bytes(omni_handle_t h, size_t *bytes);
 
 /* Bytes of workspace with which omni_paged_prefill_attn splits the context for chunks of up to max_q_len tokens
  * (0 where it would not split).  The one registered workspace serves both calls: register the larger of the two
- * sizes.  Errors: NULL, SHAPE (max_q_len <= 0). */
+ * sizes.  With head_dim 64 this many bytes hold omni_workspace_bytes for the decode calls and, behind them, a part for the
+ * multi-token call's pieces and ranking (0 where it would use neither); it writes nothing with fewer registered, and never
+ * into the decode calls' part, so the two kinds of call may overlap there.  Errors: NULL, SHAPE (max_q_len <= 0). */
 omni_status_t omni_prefill_workspace_bytes(omni_handle_t h, int32_t max_q_len, size_t *bytes);
 
 /* With OMNI_TUNE_QUERY_TOKENS = T > 1: a DEVICE array [batch] int32 that says how many query tokens each request
@@ -132,7 +134,8 @@ omni_status_t omni_set_query_lens(omni_handle_t h, const int32_t *dev_q_lens);
 
 /* Hand the library a caller-owned device buffer of at least omni_workspace_bytes, 256-byte aligned.
  * The library keeps the pointer only; contents need no initialisation.  The buffer must not be shared by calls that
- * run concurrently.  Errors: NULL, WORKSPACE. */
+ * run concurrently, be it calls of one handle on two streams (but see omni_prefill_workspace_bytes).
+ * Errors: NULL, WORKSPACE. */
 omni_status_t omni_set_workspace(omni_handle_t h, void *dev_ptr, size_t bytes);
 
 /*
@@ -293,7 +296,8 @@ omni_status_t omni_kv_unpack(omni_handle_t h, const void *k_dense, const void *v
  * query block's context in equal runs of 64-token steps (as many as the context gives OMNI_TUNE_PREFILL_MIN_SPLIT
  * tokens each), and a second launch merges their pieces (log-sum-exp, in order of position: the same exact
  * re-association as in decode).  How a block is shared depends on the handle, its tuning, max_q_len and the lengths
- * only, so the result is bit-identical from run to run.  With a registered workspace and more than 256 workgroups a
+ * only, so the result is bit-identical from run to run.  With a registered workspace (head_dim 64: of at least
+ * omni_prefill_workspace_bytes(max_q_len)) and more than 256 workgroups a
  * one-workgroup launch first ranks the requests by context length, and the kernel takes them longest first (the order
  * changes when a workgroup runs, not what it computes).
  * Errors: NULL, SHAPE (max_q_len <= 0, scale <= 0 with 128-dim heads on the matrix-core path, alignment), UNSUPPORTED, HIP.

@@ -76,10 +76,13 @@ struct omni_handle_s {
     // Context split of the multi-token-query kernel for chunks of up to max_q_len tokens: where the query blocks fill
     // at most half of the compute units, as many workgroups per (query block, KV head, request) as it takes to fill
     // them, at most 16 and no more than the longest context the handle allows can use.  1 = no split.
+    long long prefill_workgroups(int max_q_len) const {          // of the matrix-core kernel, unsplit
+        const int qb = prefill_tokens_per_block(G, d.head_dim);
+        return (long long)((max_q_len + qb - 1) / qb) * d.num_kv_heads * d.batch;
+    }
     int prefill_splits(int max_q_len) const {
         if (!prefill_mfma() || tune_prefill_splits == 1) return 1;
-        const int qb = prefill_tokens_per_block(G, d.head_dim);
-        const long long wgs = (long long)((max_q_len + qb - 1) / qb) * d.num_kv_heads * d.batch;
+        const long long wgs = prefill_workgroups(max_q_len);
         const int by_ctx = (max_ctx + 2 * kTile - 1) / (2 * kTile) / (tune_prefill_min_split / (2 * kTile));
         int ns = tune_prefill_splits > 1 ? tune_prefill_splits : (wgs > 128 ? 1 : (int)(256 / wgs));
         if (ns > 16) ns = 16;
@@ -89,10 +92,21 @@ struct omni_handle_s {
     static size_t prefill_ml_bytes(const omni_attn_desc_t &d, int max_q_len, int ns) {
         return align256((size_t)d.batch * max_q_len * d.num_q_heads * ns * sizeof(float2));
     }
+    // The requests are ranked by context length where the call has more than one round of workgroups.
+    bool prefill_ranks(int max_q_len) const {
+        return prefill_mfma() && tune_prefill_sort != 0 && d.batch > 1 && d.batch <= kPrefillOrderMax && prefill_workgroups(max_q_len) > 256;
+    }
+    size_t prefill_order_bytes(int max_q_len) const { return prefill_ranks(max_q_len) ? align256((size_t)d.batch * sizeof(int32_t)) : 0; }
+    // Where the multi-token call's part of the workspace begins.  With 64-dim heads behind the decode calls' part: a program
+    // may have a decode call and a chunk of the same handle on two streams at once, which had no data in common there before
+    // the chunks came to use the workspace.  With 128-dim heads the two have always shared it.
+    size_t prefill_ws_begin() const { return d.head_dim == 64 ? ws_bytes : 0; }
     size_t prefill_ws_bytes(int max_q_len) const {
         const int ns = prefill_splits(max_q_len);
-        if (ns <= 1) return 0;
-        return prefill_ml_bytes(d, max_q_len, ns) + align256((size_t)d.batch * max_q_len * d.num_q_heads * ns * d.head_dim * sizeof(float));
+        const size_t order = d.head_dim == 64 ? prefill_order_bytes(max_q_len) : 0;
+        if (ns <= 1) return order ? prefill_ws_begin() + order : 0;
+        return prefill_ws_begin() + order + prefill_ml_bytes(d, max_q_len, ns) +
+               align256((size_t)d.batch * max_q_len * d.num_q_heads * ns * d.head_dim * sizeof(float));
     }
 
     void derive() {
@@ -703,26 +717,27 @@ static omni_status_t launch_prefill(omni_handle_t h, const void *q, const void *
     p.Hq = d.num_q_heads; p.Hkv = d.num_kv_heads; p.G = h->G; p.MB = d.max_blocks_per_seq;
     p.out_bf16 = d.out_dtype == OMNI_BF16;
     const int qb = mfma ? prefill_tokens_per_block(h->G, d.head_dim) : kWaves;       // query tokens per workgroup
-    // The context is split only if the registered workspace holds the pieces (omni_prefill_workspace_bytes).
+    // The context is split only if the registered workspace holds the pieces (omni_prefill_workspace_bytes), and the requests
+    // are taken longest first only with a registered workspace: a one-workgroup kernel ranks them into its first words, the
+    // pieces of a split follow.  With 64-dim heads both stay behind the decode calls' part of the workspace, if it is that
+    // large.
+    size_t order_bytes = mfma && h->ws ? h->prefill_order_bytes(max_q_len) : 0;
+    if (d64 && h->ws_given < h->prefill_ws_begin() + order_bytes) order_bytes = 0;
+    const bool sorted = order_bytes > 0;
     int ns = mfma ? h->prefill_splits(max_q_len) : 1;
-    if (ns > 1 && (!h->ws || h->ws_given < h->prefill_ws_bytes(max_q_len))) ns = 1;
-    // With a registered workspace and more than one round of workgroups, the requests are taken longest first: a
-    // one-workgroup kernel ranks them into the first words of the workspace (the pieces of a split follow).
-    const long long wgs_all = (long long)((max_q_len + qb - 1) / qb) * d.num_kv_heads * d.batch;
-    const bool sorted = mfma && h->ws && d.batch > 1 && d.batch <= kPrefillOrderMax && wgs_all > 256 && h->tune_prefill_sort != 0;
-    const size_t order_bytes = sorted ? align256((size_t)d.batch * sizeof(int32_t)) : 0;
-    if (ns > 1 && h->ws_given < order_bytes + h->prefill_ws_bytes(max_q_len)) ns = 1;
-    p.order = sorted ? reinterpret_cast<const int32_t *>(h->ws) : nullptr;
+    if (ns > 1 && (!h->ws || h->ws_given < h->prefill_ws_bytes(max_q_len) + (d64 ? 0 : order_bytes))) ns = 1;
+    char *ws = reinterpret_cast<char *>(h->ws) + (h->ws ? h->prefill_ws_begin() : 0);
+    p.order = sorted ? reinterpret_cast<const int32_t *>(ws) : nullptr;
     p.B = d.batch;
     p.num_splits = ns; p.max_q_len = max_q_len;
     p.min_split_steps = h->tune_prefill_min_split / (2 * kTile);
-    p.part_ml = reinterpret_cast<float2 *>(reinterpret_cast<char *>(h->ws) + order_bytes);
-    p.part_o = ns > 1 ? reinterpret_cast<float *>(reinterpret_cast<char *>(h->ws) + order_bytes + omni_handle_s::prefill_ml_bytes(d, max_q_len, ns)) : nullptr;
+    p.part_ml = ns > 1 ? reinterpret_cast<float2 *>(ws + order_bytes) : nullptr;
+    p.part_o = ns > 1 ? reinterpret_cast<float *>(ws + order_bytes + omni_handle_s::prefill_ml_bytes(d, max_q_len, ns)) : nullptr;
     const dim3 grid((unsigned)((max_q_len + qb - 1) / qb) * (unsigned)ns, (unsigned)d.num_kv_heads, (unsigned)d.batch);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     (void)hipGetLastError();
     if (sorted) {
-        prefill_order_kernel<<<1, kPrefillOrderMax, 0, s>>>(context_lens, d.batch, reinterpret_cast<int32_t *>(h->ws));
+        prefill_order_kernel<<<1, kPrefillOrderMax, 0, s>>>(context_lens, d.batch, reinterpret_cast<int32_t *>(ws));
         if (hipGetLastError() != hipSuccess) return OMNI_ERR_HIP;
     }
     if (mfma) {

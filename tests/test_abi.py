@@ -135,6 +135,17 @@ def test_shared_memory_layout_fits_for_every_batch_and_group(kv):
         assert omni.Handle(**good(batch=B, num_q_heads=Hq, num_kv_heads=Hkv)).omni_debug_lds_layout()["two_workgroups_per_cu"]
 
 
+def test_chunk_workspace_of_64_dim_heads_lies_behind_the_decode_calls_part():
+    for over, q_len in ((dict(batch=1, max_blocks_per_seq=2048), 512),            # a split context
+                        (dict(batch=64, max_blocks_per_seq=256), 512)):           # a ranking
+        h = omni.Handle(**good(head_dim=64, **over))
+        assert h.omni_prefill_workspace_bytes(q_len) >= h.omni_workspace_bytes() + 256
+    h.omni_set_tuning(omni.OMNI_TUNE_PREFILL_SORT, 0)
+    assert h.omni_prefill_workspace_bytes(512) == 0
+    assert omni.Handle(**good(head_dim=64, batch=1, max_blocks_per_seq=8)).omni_prefill_workspace_bytes(64) == 0
+    assert omni.Handle(**good(head_dim=64, kv_dtype=omni.OMNI_F32)).omni_prefill_workspace_bytes(512) == 0
+
+
 def test_fp8_cache_descriptions():
     h = omni.Handle(**good(kv_dtype=omni.OMNI_FP8_E4M3, q_dtype=omni.OMNI_BF16))
     plan = h.omni_get_plan()

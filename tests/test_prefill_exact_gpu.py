@@ -74,3 +74,26 @@ def test_rows_beyond_a_cut_off_chunk_have_no_effect():
     for o, n in zip(ch.q_offsets, ch.q_lens):
         assert np.max(np.abs(got[o:o + 37] - ref[o:o + 37])) <= 1e-5
         assert np.all(np.isnan(got[o + 37:o + n]))
+
+
+@pytest.mark.parametrize("lens,q_lens,max_q_len", [([3000], [300], 300), ([90] * 40, [70] * 40, 70)], ids=["split", "ranked"])
+@pytest.mark.parametrize("given", ["decode-calls-bytes", "chunk-calls-bytes"])
+def test_the_decode_calls_part_of_the_workspace_stays_as_it_is(lens, q_lens, max_q_len, given):
+    """A decode call of the same handle may be under way on another stream: nothing of its part of the workspace changes,
+    and nothing beyond the registered bytes does."""
+    wl = W.build("apart", 81, lens, Hq=16, Hkv=4, D=64, ps=16, dtype=W.BF16)
+    ch = W.add_chunk(wl, q_lens, 82)
+    ref = reference(wl, ch)
+    dev = DeviceBatch(wl, tuning={omni.OMNI_TUNE_PREFILL_MIN_SPLIT: 64})
+    c = ChunkOnDevice(dev, ch)
+    decode, chunk = dev.h.omni_workspace_bytes(), dev.h.omni_prefill_workspace_bytes(max_q_len)
+    assert chunk > 0
+    n = decode if given == "decode-calls-bytes" else max(decode, chunk)
+    buf = torch.full((n + (1 << 20),), 0x5a, dtype=torch.uint8, device="cuda")
+    dev.h.omni_set_workspace(buf, n)
+    dev.h.omni_paged_prefill_attn(c.q, dev.k_cache, dev.v_cache, dev.block_table, dev.context_lens, c.q_lens, c.q_offsets,
+                                  max_q_len, float(wl.scale), c.out)
+    torch.cuda.synchronize()
+    assert bool(torch.all(buf[:decode] == 0x5a)) and bool(torch.all(buf[n:] == 0x5a))
+    assert bool(torch.all(buf[decode:n] == 0x5a)) == (n == decode)               # the part behind it is what the call uses
+    assert np.max(np.abs(c.out.cpu().numpy() - ref)) <= 1e-5
