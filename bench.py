@@ -150,11 +150,12 @@ class DecodeSetup:
     def plan(self):
         plan = self.h.omni_debug_last_plan()
         plan.update(self.h.omni_get_plan())
+        plan["runs"] = self.h.omni_get_kernel()
         return plan
 
     def resources(self):
         res = {"merge_kernel": self.h.omni_debug_kernel_resources(1)}
-        if self.h.omni_get_plan()["kernel"] == self.omni.KERNEL_MFMA:
+        if self.h.omni_get_kernel()["kernel"] == self.omni.KERNEL_MFMA:
             res["decode_mfma_kernel"] = self.h.omni_debug_kernel_resources(0)
             res["decode_mfma_kernel"]["shared_memory_layout"] = self.h.omni_debug_lds_layout()
         return res
@@ -199,7 +200,7 @@ def measure_other(name, args, torch, np, omni, W, oracle, batch=None):
            "total_context_tokens": wl.total_tokens, "kv_bytes_per_step": d.kv_bytes, "pool_replicas": d.R,
            "steps": OTHER_STEPS, "ms_per_step": ms, "tokens_per_s": wl.B / (ms * 1e-3),
            "kv_gbs_per_step": d.kv_bytes / (ms * 1e-3) / 1e9, "step_frac": d.kv_bytes / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
-           "kernel": "decode_mfma_kernel" if plan["kernel"] == 2 else "decode_valu_kernel",
+           "kernel": plan["runs"]["name"],
            "kernel_avg_us": k_avg_us, "kernel_median_us": k_med_us, "kernel_launches_timed": len(km),
            "kernel_GB/s": d.kv_bytes / k_avg_us / 1e3, "frac": d.kv_bytes / k_avg_us / 1e3 / HBM_PEAK_GBS,
            "traffic": traffic_for(wl, plan), "stream_read_ceiling": d.stream_read_ceiling(k_avg_us, n=24),
@@ -295,7 +296,7 @@ def main():
     # ---- several query tokens per request (speculative decoding / multi-token prediction): the same batch with T
     # tokens per request through the same kernel, T * (Hq / Hkv) <= 16 columns; attention + merge over rotating replicas
     multi = None
-    if not args.timed_only and h.omni_get_plan()["kernel"] == omni.KERNEL_MFMA and 2 * (wl.Hq // wl.Hkv) <= 16:
+    if not args.timed_only and h.omni_get_kernel()["weight_bits"] == 16 and 2 * (wl.Hq // wl.Hkv) <= 16:
         T = 16 // (wl.Hq // wl.Hkv)
         hT = omni.Handle(batch=wl.B, num_q_heads=wl.Hq, num_kv_heads=wl.Hkv, head_dim=wl.D, page_size=wl.ps,
                          num_pages=wl.P, max_blocks_per_seq=wl.MB, kv_dtype=kvd, out_dtype=omni.OMNI_F32)
@@ -562,7 +563,7 @@ def main():
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS,
                      "traffic": traffic_for(wl, plan),
-                     "kernel": "decode_mfma_kernel" if plan["kernel"] == 2 else "decode_valu_kernel",
+                     "kernel": plan["runs"]["name"],
                      "kernel_avg_us": k_avg_ms * 1e3, "kernel_median_us": k_med_ms * 1e3,
                      "kernel_launches_timed": len(kernel_ms),
                      "algorithmic_bytes_per_launch": kv_bytes,

@@ -86,8 +86,9 @@ typedef struct omni_handle_s *omni_handle_t;
 
 /* Tuning keys for omni_set_tuning.  Defaults are chosen for 256 compute units. */
 typedef enum {
-    OMNI_TUNE_KERNEL = 0,           /* 0 = auto, 1 = vector-ALU kernel, 2 = matrix-core (MFMA) kernel (value for bf16, head_dim 128
-                                       only: everywhere else auto takes the matrix cores by itself, with fp32-exact weights) */
+    OMNI_TUNE_KERNEL = 0,           /* 0 = auto: the matrix cores for every format; 1 = vector-ALU kernel (not over an 8-bit
+                                       cache); 2 = the matrix-core kernel whose softmax weights keep 16 bits (bf16 with
+                                       head_dim 128, 8-bit caches: what auto takes there; UNSUPPORTED for the others) */
     OMNI_TUNE_TARGET_WORKGROUPS = 1,/* workgroups the attention kernel is launched with (> 0; rounded down to a multiple of Hkv) */
     OMNI_TUNE_MIN_PARTITION = 2,    /* smallest range of context, in tokens, one workgroup may be given (multiple of 32) */
     OMNI_TUNE_FORCE_PARTITION = 3,  /* > 0: every workgroup range is exactly this many tokens (multiple of 32); 0 = plan decides */
@@ -96,7 +97,8 @@ typedef enum {
     OMNI_TUNE_PREFILL_MIN_SPLIT = 5,/* fewest tokens of context one of them takes (multiple of 64; default 256): a query
                                        block with a shorter context is shared by fewer, decided on the device */
     OMNI_TUNE_QUERY_TOKENS = 6,     /* T >= 1 (default 1): omni_paged_decode_attn and omni_paged_decode_attn_fp8 take T query
-                                       tokens per request, see there.  Matrix-core kernel only, else UNSUPPORTED */
+                                       tokens per request, see there.  T > 1: bf16 with head_dim 128 and 8-bit caches, not
+                                       under OMNI_TUNE_KERNEL = 1, else UNSUPPORTED */
     OMNI_TUNE_PREFILL_SORT = 7      /* omni_paged_prefill_attn, matrix-core path with a registered workspace and more than 256
                                        workgroups: 1 (default) = requests are taken longest context first (one more tiny
                                        launch ranks them), 0 = in batch order */
@@ -323,13 +325,18 @@ omni_status_t omni_kv_append_chunk(omni_handle_t h, const void *k_new, const voi
                                    const int32_t *block_table, const int32_t *context_lens, const int32_t *q_lens,
                                    const int64_t *q_offsets, int32_t max_q_len, void *stream);
 
-/* Host-known part of the launch plan: which kernel (2 = 16-bit matrix-core kernel, softmax weights kept to 2^-16; 1 = a
- * kernel with fp32-exact weights: vector ALUs, or matrix cores for fp32 caches and head_dim 64), the data-independent
- * grid (workgroups) of the attention kernel, the (request, KV head) pairs the merge kernel that follows it runs over, the number of
- * partial-result slots the workspace is sized for, and threads per workgroup.  The range length itself is chosen on the device from
- * context_lens; omni_debug_last_plan reads it back. */
+/* Host-known part of the launch plan: the precision of the softmax weights (kernel: 2 = kept to 2^-16, 1 = fp32-exact; which
+ * units compute is omni_get_kernel's to say), the data-independent grid (workgroups) of the attention kernel, the
+ * (request, KV head) pairs the merge kernel that follows it runs over (its workgroups: that many for each 1024 output
+ * elements of a pair), the number of partial-result slots the workspace is sized for, and threads per workgroup.  The range
+ * length itself is chosen on the device from context_lens; omni_debug_last_plan reads it back. */
 omni_status_t omni_get_plan(omni_handle_t h, int32_t *kernel, int32_t *partition_grid, int32_t *merge_grid,
                             int32_t *max_request_parts, int32_t *threads_per_workgroup);
+
+/* What the decode calls of this handle run: *kernel = 1 the vector-ALU kernel, 2 the matrix-core kernel; *weight_bits =
+ * significant bits the softmax weights keep on their way into the product with V, 16 or 24.  Either pointer may be null.
+ * Errors: NULL (handle). */
+omni_status_t omni_get_kernel(omni_handle_t h, int32_t *kernel, int32_t *weight_bits);
 
 const char *omni_status_string(omni_status_t s);
 

@@ -17,12 +17,12 @@ OMNI_F32, OMNI_BF16, OMNI_FP8_E4M3 = 0, 1, 2
 OMNI_TUNE_KERNEL, OMNI_TUNE_TARGET_WORKGROUPS, OMNI_TUNE_MIN_PARTITION, OMNI_TUNE_FORCE_PARTITION = 0, 1, 2, 3
 OMNI_TUNE_PREFILL_SPLITS, OMNI_TUNE_PREFILL_MIN_SPLIT, OMNI_TUNE_QUERY_TOKENS = 4, 5, 6
 OMNI_TUNE_PREFILL_SORT = 7
-KERNEL_AUTO, KERNEL_VALU, KERNEL_MFMA = 0, 1, 2
+KERNEL_AUTO, KERNEL_VALU, KERNEL_MFMA = 0, 1, 2      # OMNI_TUNE_KERNEL; what runs: omni_get_kernel
 
 EXPORTS = (
     "omni_create", "omni_destroy", "omni_set_tuning", "omni_workspace_bytes", "omni_prefill_workspace_bytes",
     "omni_set_workspace", "omni_set_query_lens",
-    "omni_paged_decode_attn", "omni_paged_decode_attn_static", "omni_paged_decode_attn_fp8", "omni_kv_append", "omni_decode_step", "omni_decode_step_fp8", "omni_kv_append_quant_fp8", "omni_kv_pack", "omni_kv_unpack", "omni_paged_prefill_attn", "omni_paged_prefill_attn_fp8", "omni_kv_append_chunk", "omni_get_plan",
+    "omni_paged_decode_attn", "omni_paged_decode_attn_static", "omni_paged_decode_attn_fp8", "omni_kv_append", "omni_decode_step", "omni_decode_step_fp8", "omni_kv_append_quant_fp8", "omni_kv_pack", "omni_kv_unpack", "omni_paged_prefill_attn", "omni_paged_prefill_attn_fp8", "omni_kv_append_chunk", "omni_get_plan", "omni_get_kernel",
     "omni_status_string",
     "omni_debug_last_plan", "omni_debug_lds_layout", "omni_debug_kernel_resources", "omni_debug_gather", "omni_debug_stream_read", "omni_debug_profile_begin",
     "omni_debug_profile_end", "omni_graph_begin", "omni_graph_end", "omni_graph_launch", "omni_graph_destroy",
@@ -73,6 +73,7 @@ def lib():
         L.omni_paged_prefill_attn_fp8.argtypes = [vp] * 10 + [C.c_int32, C.c_float, vp, vp]
         L.omni_kv_append_chunk.argtypes = [vp] * 9 + [C.c_int32, vp]
         L.omni_get_plan.argtypes = [vp] + [i32p] * 5
+        L.omni_get_kernel.argtypes = [vp] + [i32p] * 2
         L.omni_status_string.argtypes = [C.c_int]; L.omni_status_string.restype = C.c_char_p
         L.omni_debug_last_plan.argtypes = [vp, i32p, vp]
         L.omni_debug_lds_layout.argtypes = [vp, i32p]
@@ -234,6 +235,12 @@ class Handle:
         _ck(lib().omni_get_plan(self._h, *[C.byref(x) for x in v]), "omni_get_plan")
         keys = ("kernel", "partition_grid", "merge_grid", "max_request_parts", "threads_per_workgroup")
         return dict(zip(keys, (x.value for x in v)))
+
+    def omni_get_kernel(self) -> dict:
+        v = [C.c_int32() for _ in range(2)]
+        _ck(lib().omni_get_kernel(self._h, *[C.byref(x) for x in v]), "omni_get_kernel")
+        return {"name": "decode_mfma_kernel" if v[0].value == KERNEL_MFMA else "decode_valu_kernel", "kernel": v[0].value,
+                "weight_bits": v[1].value}
 
     def omni_kv_pack(self, k_cache, v_cache, block_table, context_lens, token_offsets, k_dense, v_dense, stream=None) -> None:
         _ck(lib().omni_kv_pack(self._h, _ptr(k_cache), _ptr(v_cache), _ptr(block_table), _ptr(context_lens),

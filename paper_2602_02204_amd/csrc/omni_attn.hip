@@ -52,7 +52,7 @@ struct omni_handle_s {
     int tune_query_tokens = 1;
     int tune_prefill_sort = 1;
     // derived
-    int kernel = 1;              // what omni_get_plan reports: 2 = 16-bit matrix-core kernel, 1 = fp32-exact weights
+    int kernel = 1;              // what omni_get_plan reports: 2 = softmax weights of 16 bits (matrix cores), 1 = of 24
     bool mfma = false;           // the matrix-core kernel runs (else the vector-ALU kernel)
     int G = 1;
     int pass_tokens = 1;         // query tokens per request one launch of the attention kernel covers
@@ -275,6 +275,13 @@ omni_status_t omni_get_plan(omni_handle_t h, int32_t *kernel, int32_t *partition
     if (merge_grid) *merge_grid = h->d.batch * h->d.num_kv_heads;
     if (max_request_parts) *max_request_parts = h->r_cap;
     if (threads_per_workgroup) *threads_per_workgroup = kThreads;
+    return OMNI_OK;
+}
+
+omni_status_t omni_get_kernel(omni_handle_t h, int32_t *kernel, int32_t *weight_bits) {
+    if (!h) return OMNI_ERR_NULL;
+    if (kernel) *kernel = h->mfma ? 2 : 1;
+    if (weight_bits) *weight_bits = h->kernel == 2 ? 16 : 24;
     return OMNI_OK;
 }
 

@@ -135,6 +135,31 @@ def test_shared_memory_layout_fits_for_every_batch_and_group(kv):
         assert omni.Handle(**good(batch=B, num_q_heads=Hq, num_kv_heads=Hkv)).omni_debug_lds_layout()["two_workgroups_per_cu"]
 
 
+def test_the_kernel_that_runs_and_the_bits_its_weights_keep():
+    def kernel(tune=None, **over):
+        h = omni.Handle(**good(**over))
+        if tune is not None:
+            h.omni_set_tuning(omni.OMNI_TUNE_KERNEL, tune)
+        got = h.omni_get_kernel()
+        assert (got["name"] == "decode_mfma_kernel") == (got["kernel"] == omni.KERNEL_MFMA)
+        try:                                                     # the shared-memory layout is the matrix-core kernel's
+            h.omni_debug_lds_layout()
+            assert got["kernel"] == omni.KERNEL_MFMA
+        except omni.OmniError:
+            assert got["kernel"] == omni.KERNEL_VALU
+        assert h.omni_get_plan()["kernel"] == (2 if got["weight_bits"] == 16 else 1)
+        return got["kernel"], got["weight_bits"]
+
+    fp8 = dict(kv_dtype=omni.OMNI_FP8_E4M3, q_dtype=omni.OMNI_BF16)
+    for D in (64, 128):
+        exact = D == 64
+        assert kernel(head_dim=D) == (omni.KERNEL_MFMA, 24 if exact else 16)
+        assert kernel(head_dim=D, kv_dtype=omni.OMNI_F32) == (omni.KERNEL_MFMA, 24)
+        for dt in (omni.OMNI_BF16, omni.OMNI_F32):
+            assert kernel(omni.KERNEL_VALU, head_dim=D, kv_dtype=dt) == (omni.KERNEL_VALU, 24)
+    assert kernel(**fp8) == kernel(omni.KERNEL_MFMA) == kernel(omni.KERNEL_MFMA, **fp8) == (omni.KERNEL_MFMA, 16)
+
+
 def test_chunk_workspace_of_64_dim_heads_lies_behind_the_decode_calls_part():
     for over, q_len in ((dict(batch=1, max_blocks_per_seq=2048), 512),            # a split context
                         (dict(batch=64, max_blocks_per_seq=256), 512)):           # a ranking
