@@ -373,8 +373,8 @@ constexpr int kKStageBytes = 8192;                     // one 32-token K tile of
 // columns), the layout keeps four and `two_per_cu` is false: the launch is still valid, with one workgroup per
 // compute unit.
 constexpr int kLdsPerWorkgroup = 80 * 1024 - 512;      // half a compute unit's shared memory less the kernel's own variables
-inline MfmaLds mfma_lds_layout(int B, int G, int D, int row_bytes, bool staged, bool query_counts = false) {
-    MfmaLds L;
+constexpr MfmaLds mfma_lds_layout(int B, int G, int D, int row_bytes, bool staged, bool query_counts = false) {
+    MfmaLds L{};
     L.ring_off = (((query_counts ? 3 : 2) * B + 1) * 4 + 15) & ~15;      // E[B + 1], Lc[B] and, if asked for, Nc[B]
     L.state_floats = G * (D + 4) + 2 * kMaxGroup;
     L.static_bytes = staged ? kWaves * kTile * row_bytes : 0;          // the waves' K tiles

@@ -308,7 +308,11 @@ const void *mfma_variant(const omni_handle_s *h) {
     const bool ps16 = h->d.page_size == 16, st = h->k_staged, d64 = h->d.head_dim == 64, mt = h->tune_query_tokens > 1;
     if (h->d.kv_dtype == OMNI_FP8_E4M3) return mt ? mfma_variant_of<kFp8D128, true>(ps16, st) : mfma_variant_of<kFp8D128, false>(ps16, st);
     if (h->d.kv_dtype == OMNI_F32) return d64 ? mfma_variant_of<kF32D64, false>(ps16, st) : mfma_variant_of<kF32D128, false>(ps16, st);
-    if (d64) return mfma_variant_of<kBf16D64, false>(ps16, st);
+    if (d64) {                   // always staged: the largest batch with the most columns leaves room for it
+        static_assert(mfma_lds_layout(kMaxBatch, kMaxGroup, 64, 128, true).two_per_cu &&
+                      mfma_lds_layout(kMaxBatch, kMaxGroup, 64, 128, true).ring_states >= kWaves + 1, "");
+        return ps16 ? (const void *)&decode_mfma_kernel<16, kBf16D64, true, false> : (const void *)&decode_mfma_kernel<32, kBf16D64, true, false>;
+    }
     return mt ? mfma_variant_of<kBf16D128, true>(ps16, st) : mfma_variant_of<kBf16D128, false>(ps16, st);
 }
 

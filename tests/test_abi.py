@@ -109,15 +109,17 @@ def test_tuning_validation_and_plan():
         f32.omni_set_tuning(omni.OMNI_TUNE_KERNEL, omni.KERNEL_MFMA)
 
 
-@pytest.mark.parametrize("kv", [omni.OMNI_BF16, omni.OMNI_FP8_E4M3], ids=["bf16", "fp8"])
-def test_shared_memory_layout_fits_for_every_batch_and_group(kv):
+@pytest.mark.parametrize("kv,D", [(omni.OMNI_BF16, 128), (omni.OMNI_FP8_E4M3, 128), (omni.OMNI_BF16, 64), (omni.OMNI_F32, 64),
+                                  (omni.OMNI_F32, 128)], ids=["bf16", "fp8", "bf16-64", "f32-64", "f32-128"])
+def test_shared_memory_layout_fits_for_every_batch_and_group(kv, D):
     """Over the whole (batch, columns) range the library accepts: the dynamic and static shared memory of the
     matrix-core kernel fit two workgroups per compute unit (half of 160 KB each) wherever the layout says so, never
     exceed what the launch may ask for, and K is staged only where its staging area leaves room for five states."""
     for B in (1, 64, 256, 257, 1024, 2048, 3000, 4096):
         for G in (1, 4, 7, 8, 16):
-            for T in (1, 2, 16 // G if G < 16 else 1):
-                h = omni.Handle(**good(batch=B, num_q_heads=2 * G, kv_dtype=kv,
+            several = D == 128 and kv != omni.OMNI_F32                   # the formats that take several query tokens
+            for T in (1, 2, 16 // G if G < 16 else 1) if several else (1,):
+                h = omni.Handle(**good(batch=B, num_q_heads=2 * G, head_dim=D, kv_dtype=kv,
                                        q_dtype=omni.OMNI_BF16 if kv == omni.OMNI_FP8_E4M3 else None))
                 if T > 1:
                     h.omni_set_tuning(omni.OMNI_TUNE_QUERY_TOKENS, T)
@@ -130,6 +132,10 @@ def test_shared_memory_layout_fits_for_every_batch_and_group(kv):
                 assert (lay["static_bytes"] > 0) == lay["k_staged"]
                 if lay["k_staged"]:
                     assert lay["two_workgroups_per_cu"] and lay["ring_states"] >= 5, (B, G, T, lay)
+                if D == 64:                                              # where each variant runs
+                    assert lay["k_staged"] != (kv == omni.OMNI_F32 and G == 16 and B > 3000), (B, G, lay)
+                elif kv == omni.OMNI_F32:
+                    assert lay["k_staged"] == (B <= {1: 1024, 4: 257}.get(G, 0)), (B, G, lay)
     # the benchmark shapes keep two workgroups per compute unit
     for B, Hq, Hkv in ((64, 28, 4), (256, 16, 2), (8, 28, 4), (128, 32, 8)):
         assert omni.Handle(**good(batch=B, num_q_heads=Hq, num_kv_heads=Hkv)).omni_debug_lds_layout()["two_workgroups_per_cu"]
