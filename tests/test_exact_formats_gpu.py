@@ -41,16 +41,34 @@ def test_tile_edges(dtype, D, ps, G, Hkv):
         assert np.array_equal(got[1], np.repeat(v1, G, axis=0))
 
 
-@pytest.mark.parametrize("dtype,D", FORMATS, ids=IDS)
+# every variant that appends: K staged (the new rows are patched into the tile in flight) or not (they are written first)
+APPENDS = [(W.F32, 64, 3, True), (W.F32, 128, 3, True), (W.BF16, 64, 3, True), (W.BF16, 64, 16, True), (W.F32, 128, 7, False),
+           (W.F32, 128, 16, False)]
+
+
+@pytest.mark.parametrize("dtype,D,G,staged", APPENDS, ids=[f"{'f32' if t == W.F32 else 'bf16'}-{D}-G{G}" for t, D, G, _ in APPENDS])
+@pytest.mark.parametrize("ps", [16, 32])
 @pytest.mark.parametrize("batch", [40, 300], ids=["wave-plan", "workgroup-plan"])
-def test_fused_step_equals_append_then_attention(dtype, D, batch):
+def test_fused_step_equals_append_then_attention(dtype, D, G, staged, ps, batch):
     """Many short requests per range (more than a chunk holds) and both plans; pools and outputs bit for bit."""
     rng = np.random.default_rng(5 + batch + D)
-    lens = rng.choice([1, 2, 16, 17, 31, 32, 33, 48, 64, 65, 200], size=batch)
-    wl = W.build("step", 9 + D, lens, Hq=6, Hkv=2, D=D, ps=16, dtype=dtype, append=True)
+    lens = rng.choice([0, 1, 2, 16, 17, 31, 32, 33, 48, 64, 65, 200], size=batch)
+    check_fused_step(W.build("step", 9 + D, lens, Hq=2 * G, Hkv=2, D=D, ps=ps, dtype=dtype, append=True), staged)
+
+
+@pytest.mark.parametrize("ps", [16, 32])
+def test_fused_step_of_the_largest_batch_without_staging(ps):
+    """fp32 caches with 64-dim heads leave no room for staging only with 12 columns or more and thousands of requests."""
+    rng = np.random.default_rng(3)
+    lens = rng.choice([0, 1, 16, 17, 31, 32, 33, 40], size=4096)
+    check_fused_step(W.build("step", 11, lens, Hq=16, Hkv=1, D=64, ps=ps, dtype=W.F32, append=True), False)
+
+
+def check_fused_step(wl, staged):
     res = []
     for fused in (True, False):
         dev = DeviceBatch(wl, tuning={omni.OMNI_TUNE_FORCE_PARTITION: 1024})
+        assert dev.h.omni_debug_lds_layout()["k_staged"] == staged
         if fused:
             dev.h.omni_decode_step(dev.q, dev.k_new, dev.v_new, dev.k_cache, dev.v_cache, dev.block_table, dev.context_lens,
                                    float(wl.scale), dev.out)
@@ -62,8 +80,8 @@ def test_fused_step_equals_append_then_attention(dtype, D, batch):
     assert all(np.array_equal(a, b) for a, b in zip(*res))
     oracle.kv_append(wl.k_new, wl.v_new, wl.k_cache, wl.v_cache, wl.block_table, wl.positions, wl.dtype)
     assert np.array_equal(res[0][1], wl.k_cache.view(np.uint8)) and np.array_equal(res[0][2], wl.v_cache.view(np.uint8))
-    got = res[0][0].view(np.float32).reshape(ref_of(wl).shape)
-    assert np.max(np.abs(got - ref_of(wl))) <= 1e-5
+    ref = ref_of(wl)
+    assert np.max(np.abs(res[0][0].view(np.float32).reshape(ref.shape) - ref)) <= 1e-5
 
 
 def test_subnormal_values_pass_through():
