@@ -43,7 +43,7 @@ def run_chunk(wl, ch, max_q_len=None, out_dtype=W.F32, tuning=None, split_worksp
     return dev, c.out.float().cpu().numpy().astype(np.float64)
 
 
-def check_chunk(wl, ch, label="", **kw):
+def check_chunk(wl, ch, label="", tol=None, **kw):
     dev, got = run_chunk(wl, ch, **kw)
     oracle.kv_append_chunk(ch.k_new, ch.v_new, wl.k_cache, wl.v_cache, wl.block_table, wl.context_lens, ch.q_lens,
                            ch.q_offsets)
@@ -56,7 +56,7 @@ def check_chunk(wl, ch, label="", **kw):
         owned[ch.q_offsets[b]:ch.q_offsets[b] + ch.q_lens[b]] = True
     assert np.all(np.isnan(got[~owned])), f"{label}: rows nobody owns were written"
     err = np.max(np.abs(got[owned] - ref[owned])) if owned.any() else 0.0
-    assert np.all(np.isfinite(got[owned])) and err <= TOL[wl.dtype], f"{label}: max|err| {err:.3e}"
+    assert np.all(np.isfinite(got[owned])) and err <= (tol or TOL[wl.dtype]), f"{label}: max|err| {err:.3e}"
     return got, ref
 
 
@@ -76,12 +76,12 @@ def test_chunks_of_many_shapes(G, Hkv, ps):
 @pytest.mark.parametrize("dtype,D,G,Hkv,ps", [(W.F32, 64, 2, 2, 16), (W.F32, 64, 7, 1, 32), (W.F32, 128, 4, 2, 16),
                                               (W.BF16, 64, 5, 2, 16), (W.BF16, 64, 16, 1, 32)])
 def test_chunks_on_every_other_dtype_and_head_size(dtype, D, G, Hkv, ps):
-    """fp32 caches and head_dim 64 go through the vector-ALU kernel (fp32 caches to 1e-5)."""
+    """fp32 caches (the vector-ALU kernel) and 64-dim bf16 heads (the matrix-core kernel with weights of 24 bits), to 1e-5."""
     lens = [300, 64, 1, 0, 33, 257, 96, 40]
     q_lens = [300, 1, 1, 0, 17, 100, 37, 40]
     wl = W.build("chunk", 800 + G + D, lens, Hq=G * Hkv, Hkv=Hkv, D=D, ps=ps, dtype=dtype, pool_factor=1.5)
     ch = W.add_chunk(wl, q_lens, 801 + G, in_cache=False, gap=3)
-    check_chunk(wl, ch, label=f"{dtype} D={D} G={G} ps={ps}")
+    check_chunk(wl, ch, label=f"{dtype} D={D} G={G} ps={ps}", tol=1e-5)
 
 
 def test_vector_alu_kernel_agrees_with_the_matrix_core_kernel_on_bf16():
