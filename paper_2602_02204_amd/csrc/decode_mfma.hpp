@@ -150,6 +150,10 @@ struct TileLoader {
         }
         load_k_scales(pg0, pg1, ks);
     }
+    __device__ __forceinline__ void issue_k_half(const char *rows, uint4 *K) const {     // 16-bit and fp32 caches
+#pragma unroll
+        for (int n = 0; n < NK; ++n) K[n] = nt_load16(rows + koff + n * 64);
+    }
     __device__ __forceinline__ void issue_k_staged(int pg0, int pg1, char *stage, float (&ks)[2]) const {
         const char *k0 = kbase + (size_t)pg0 * page_stride, *k1 = kbase + second_half(pg0, pg1);
 #pragma unroll
@@ -205,6 +209,45 @@ struct MfmaState {
     f32x4_t acc[CacheTraits<F>::kBlocks];    // acc[e][i] = O^T[dim of output row 4j + i of block e][column lane%16]
 };
 
+__device__ __forceinline__ f32x4_t rescale_add(const f32x4_t &acc, float alpha, const f32x4_t &t) {
+    f32x4_t r;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r[i] = fmaf(acc[i], alpha, t[i]);
+    return r;
+}
+
+// The raw scores of one 16-token half of an fp32 tile.  A matrix instruction adds its products one after the other, so a
+// chain over all dims rounds 64 or 128 partial sums one upon the other.  Each instruction starts from zero instead and the
+// four-product sums are added as a tree, like the lanes of the vector-ALU kernel.  With the chains of mfma_softmax_pv this
+// brings the error against 64 bits from 1.6 - 3.3 times that kernel's to 0.8 - 1.06 times (64 .. 2 requests of 17 .. 17000
+// tokens, scores of deviation 1 and 4), for 11 % of the time over 128-dim rows (28/4 heads, 592 MB: 109 -> 123 us; the
+// vector-ALU kernel takes 354) and 1 - 4 % over 64-dim rows.
+template <CacheFormat F>
+__device__ __forceinline__ f32x4_t mfma_scores_f32(const uint4 *K, const uint4 (&Q)[CacheTraits<F>::kQRegs]) {
+    constexpr int N = CacheTraits<F>::kQRegs;
+    const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+    f32x4_t part[3];                                             // partial sums of 1, 2 and 4 chunks that wait for their sibling
+    f32x4_t sum = zero;
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+        f32x4_t t[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t[e] = mfma_f32(dword_of(K[n], e), dword_of(Q[n], e), zero);
+        sum = (t[0] + t[1]) + (t[2] + t[3]);
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+            if (!(n >> b & 1)) { part[b] = sum; break; }
+            sum = part[b] + sum;
+        }
+        // the additions stay here: moved down to where the scores are used, their 128 operands would wait in registers
+        if (n & 1) asm volatile("" : "+v"(sum));
+        if (!(n & 1)) part[0] = sum;
+        else if (!(n & 2)) part[1] = sum;
+        else if (!(n & 4)) part[2] = sum;
+    }
+    return sum;
+}
+
 // First half of a 32-token tile: the scores S^T = K Q^T of the tile, in the log2 domain.  Bytes of an 8-bit cache are
 // widened to bf16 right before each MFMA step, and the K scale of each 16-token half (ks) joins the softmax scale.
 template <CacheFormat F>
@@ -216,20 +259,19 @@ __device__ __forceinline__ void mfma_scores(const uint4 (&K)[2 * CacheTraits<F>:
     using C = CacheTraits<F>;
     constexpr int NK = C::kKRegs;
     f32x4_t s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (C::kF32) { s0 = mfma_scores_f32<F>(K, Q); s1 = mfma_scores_f32<F>(K + NK, Q); }
 #pragma unroll
-    for (int n = 0; n < C::kQRegs; ++n) {
+    for (int n = 0; n < (C::kF32 ? 0 : C::kQRegs); ++n) {
         if constexpr (C::kFp8) {
             const uint4 &a = K[n >> 1], &b = K[NK + (n >> 1)];
             const uint4 A0 = (n & 1) ? fp8x8_to_bf16x8(a.z, a.w) : fp8x8_to_bf16x8(a.x, a.y);
             const uint4 A1 = (n & 1) ? fp8x8_to_bf16x8(b.z, b.w) : fp8x8_to_bf16x8(b.x, b.y);
             s0 = mfma_bf16(A0, Q[n], s0);
             s1 = mfma_bf16(A1, Q[n], s1);
-        } else if constexpr (C::kF32) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                s0 = mfma_f32(dword_of(K[n], e), dword_of(Q[n], e), s0);
-                s1 = mfma_f32(dword_of(K[NK + n], e), dword_of(Q[n], e), s1);
-            }
+        } else if constexpr (C::D == 64) {       // each from zero, as in mfma_scores_f32: error 1.15 -> 1.03 times
+            const f32x4_t none = {0.f, 0.f, 0.f, 0.f};
+            s0 += mfma_bf16(K[n], Q[n], none);
+            s1 += mfma_bf16(K[NK + n], Q[n], none);
         } else {
             s0 = mfma_bf16(K[n], Q[n], s0);
             s1 = mfma_bf16(K[NK + n], Q[n], s1);
@@ -238,15 +280,6 @@ __device__ __forceinline__ void mfma_scores(const uint4 (&K)[2 * CacheTraits<F>:
     const float c0 = C::kFp8 ? ks[0] * scale_log2 : scale_log2, c1 = C::kFp8 ? ks[1] * scale_log2 : scale_log2;
 #pragma unroll
     for (int i = 0; i < 4; ++i) { sv[i] = s0[i] * c0; sv[4 + i] = s1[i] * c1; }
-}
-
-// The raw scores of one 16-token half of an fp32 tile.
-template <CacheFormat F>
-__device__ __forceinline__ void mfma_scores_f32_half(const uint4 *K, const uint4 (&Q)[CacheTraits<F>::kQRegs], f32x4_t &s) {
-#pragma unroll
-    for (int n = 0; n < CacheTraits<F>::kQRegs; ++n)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) s = mfma_f32(dword_of(K[n], e), dword_of(Q[n], e), s);
 }
 
 // Two floats' upper halves as a pair of bf16 (truncated).
@@ -334,19 +367,31 @@ __device__ __forceinline__ void mfma_softmax_pv(float (&sv)[8], uint32_t (&V)[8]
 #pragma unroll
         for (int r = 0; r < 4; ++r) { pw[r] *= vs0; pw[4 + r] *= vs1; }
     }
+    const f32x4_t none = {0.f, 0.f, 0.f, 0.f};
     if constexpr (C::kF32) {
+        // a tile's sum in two chains (four over 64 dims), each as long as a lane group's in the vector-ALU kernel, and one
+        // rounding where it joins the sum of the tiles before
+        constexpr int kChains = C::D == 128 ? 2 : 4, kLength = 8 / kChains;
 #pragma unroll
-        for (int e = 0; e < C::kBlocks; ++e) st.acc[e] *= alpha;
+        for (int e = 0; e < C::kBlocks; ++e) {
+            f32x4_t t[kChains];
 #pragma unroll
-        for (int r = 0; r < 8; ++r)
+            for (int c = 0; c < kChains; ++c) {
+                t[c] = none;
 #pragma unroll
-            for (int e = 0; e < C::kBlocks; ++e) st.acc[e] = mfma_f32(V[r][e], __float_as_uint(pw[r]), st.acc[e]);
+                for (int r = 0; r < kLength; ++r) t[c] = mfma_f32(V[c * kLength + r][e], __float_as_uint(pw[c * kLength + r]), t[c]);
+            }
+            st.acc[e] = rescale_add(st.acc[e], alpha, kChains == 2 ? t[0] + t[1] : (t[0] + t[1]) + (t[kChains - 2] + t[kChains - 1]));
+            if constexpr (C::D == 128) { if (e & 1) asm volatile("" : "+v"(st.acc[e]), "+v"(st.acc[e - 1])); }   // two blocks at a time
+        }
     } else {
         constexpr int kParts = C::D == 64 ? 3 : 2;
         uint4 P[kParts];
         split_weights<kParts, true>(pw, P);
+        if constexpr (kParts == 2) {
 #pragma unroll
-        for (int e = 0; e < C::kBlocks; ++e) st.acc[e] *= alpha;
+            for (int e = 0; e < C::kBlocks; ++e) st.acc[e] *= alpha;
+        }
         // in-lane transpose: operand e holds dim e of the lane's chunk for the 8 tokens of its lane group
         // (dword w of V[r] holds dims 2w and 2w+1 of token slot r)
 #pragma unroll
@@ -358,8 +403,15 @@ __device__ __forceinline__ void mfma_softmax_pv(float (&sv)[8], uint32_t (&V)[8]
             A.y = __builtin_amdgcn_perm(V[3][w], V[2][w], sel);
             A.z = __builtin_amdgcn_perm(V[5][w], V[4][w], sel);
             A.w = __builtin_amdgcn_perm(V[7][w], V[6][w], sel);
+            if constexpr (kParts == 2) {
 #pragma unroll
-            for (int i = 0; i < kParts; ++i) st.acc[e] = mfma_bf16(A, P[i], st.acc[e]);
+                for (int i = 0; i < kParts; ++i) st.acc[e] = mfma_bf16(A, P[i], st.acc[e]);
+            } else {                                             // the tile's sum first, from its smallest part up
+                f32x4_t t = none;
+#pragma unroll
+                for (int i = kParts - 1; i >= 0; --i) t = mfma_bf16(A, P[i], t);
+                st.acc[e] = rescale_add(st.acc[e], alpha, t);
+            }
         }
     }
 }
@@ -755,9 +807,8 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(AttnParams p) 
                     }
                     ks_cur[0] = ks[0]; ks_cur[1] = ks[1];
                     if constexpr (kHalves) {
-                        f32x4_t s0 = {0.f, 0.f, 0.f, 0.f};
                         ld.read_k_staged_half(kstage, 0, K);
-                        mfma_scores_f32_half<F>(K, Q, s0);
+                        const f32x4_t s0 = mfma_scores_f32<F>(K, Q);
                         __builtin_amdgcn_sched_barrier(0);       // the second half's operands take the first half's registers
                         ld.read_k_staged_half(kstage, 1, K);
 #pragma unroll
@@ -771,13 +822,26 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(AttnParams p) 
                         issue_k(nxt.pg0, nxt.pg1);
                     }
                     if constexpr (kHalves) {
-                        f32x4_t s1 = {0.f, 0.f, 0.f, 0.f};
-                        mfma_scores_f32_half<F>(K, Q, s1);
+                        const f32x4_t s1 = mfma_scores_f32<F>(K, Q);
 #pragma unroll
                         for (int i = 0; i < 4; ++i) sv[4 + i] = s1[i] * p.scale_log2;
                     } else {
                         mfma_scores<F>(K, Q, sv, p.scale_log2, ks_cur);
                     }
+                } else if constexpr (C::kF32) {
+                    // the halves' operands are asked for as soon as each is free: the scores take as long as a trip to memory
+                    const f32x4_t s0 = mfma_scores_f32<F>(K, Q);
+                    if (more) {
+                        if (nxt.append) append_row(nxt);
+                        ld.issue_k_half(ld.kbase + (size_t)nxt.pg0 * ld.page_stride, K);
+                    }
+                    const f32x4_t s1 = mfma_scores_f32<F>(K + C::kKRegs, Q);
+                    if (more) {
+                        ld.issue_k_half(ld.kbase + ld.second_half(nxt.pg0, nxt.pg1), K + C::kKRegs);
+                        if (nxt.req != seg.b) load_q(nxt.req, Q);
+                    }
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) { sv[i] = s0[i] * p.scale_log2; sv[4 + i] = s1[i] * p.scale_log2; }
                 } else {
                     mfma_scores<F>(K, Q, sv, p.scale_log2, ks);
                     if (more) {

@@ -92,3 +92,17 @@ def test_subnormal_values_pass_through():
         row[:] = np.ldexp(np.arange(1, 65, dtype=np.float32), -149 + b)
     got = DeviceBatch(wl).attend()
     assert np.array_equal(got[:, 0], np.stack([wl.v_cache[wl.block_table[b, 0], 0, 0] for b in range(2)]).astype(np.float64))
+
+
+@pytest.mark.parametrize("sharp", [1.0, 4.0])
+@pytest.mark.parametrize("dtype,D", FORMATS, ids=IDS)
+def test_sums_are_as_accurate_as_the_vector_alu_kernels(dtype, D, sharp):
+    """Both kernels take exact products and fp32 sums; the order of the sums decides how far the result is from 64 bits.
+    896 (request, head) pairs: the ratio of two such errors scatters by about sqrt(2 / 896) = 5 %, hence 10 %."""
+    rng = np.random.default_rng(7)
+    wl = W.build("sums", 8, rng.integers(256, 2048, size=32), Hq=28, Hkv=4, D=D, ps=16, dtype=dtype)
+    wl.q = wl.q * np.float32(sharp) if dtype == W.F32 else W.f32_to_bf16_bits(W.bf16_bits_to_f32(wl.q) * np.float32(sharp))
+    ref = ref_of(wl)
+    err = [np.linalg.norm(DeviceBatch(wl, tuning={omni.OMNI_TUNE_KERNEL: k}).attend() - ref)
+           for k in (omni.KERNEL_AUTO, omni.KERNEL_VALU)]
+    assert err[0] <= 1.1 * err[1], err[0] / err[1]
