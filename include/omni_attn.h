@@ -219,8 +219,9 @@ omni_status_t omni_kv_append(omni_handle_t h,
  * positions[b] = context_lens[b] - 1 (requests of length 0 are skipped) followed by omni_paged_decode_attn, but with
  * the append fused into the attention kernel (except under OMNI_TUNE_KERNEL = 1): the wave that
  * reads a request's last tile takes the new K/V row from k_new / v_new in place of that row of the page and writes it
- * into the page.  Same results, bit for bit, as the two separate calls; k_cache / v_cache hold the new rows when the
- * call has completed in stream order.
+ * into the page.  Same results, bit for bit, as the two separate calls, where no other request of the batch reads a row
+ * that this call appends (a page that is still being filled belongs to one request); k_cache / v_cache hold the new rows
+ * when the call has completed in stream order.
  * Errors: NULL, WORKSPACE, HIP.
  */
 omni_status_t omni_decode_step(omni_handle_t h,

@@ -226,24 +226,19 @@ template <CacheFormat F>
 __device__ __forceinline__ f32x4_t mfma_scores_f32(const uint4 *K, const uint4 (&Q)[CacheTraits<F>::kQRegs]) {
     constexpr int N = CacheTraits<F>::kQRegs;
     const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
-    f32x4_t part[3];                                             // partial sums of 1, 2 and 4 chunks that wait for their sibling
-    f32x4_t sum = zero;
+    f32x4_t part[4], sum = zero;                                 // sums of 1, 2, 4 chunks that wait for their sibling
 #pragma unroll
     for (int n = 0; n < N; ++n) {
         f32x4_t t[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) t[e] = mfma_f32(dword_of(K[n], e), dword_of(Q[n], e), zero);
         sum = (t[0] + t[1]) + (t[2] + t[3]);
+        int b = 0;
 #pragma unroll
-        for (int b = 0; b < 3; ++b) {
-            if (!(n >> b & 1)) { part[b] = sum; break; }
-            sum = part[b] + sum;
-        }
+        for (; n >> b & 1; ++b) sum = part[b] + sum;
         // the additions stay here: moved down to where the scores are used, their 128 operands would wait in registers
         if (n & 1) asm volatile("" : "+v"(sum));
-        if (!(n & 1)) part[0] = sum;
-        else if (!(n & 2)) part[1] = sum;
-        else if (!(n & 4)) part[2] = sum;
+        part[b] = sum;
     }
     return sum;
 }
