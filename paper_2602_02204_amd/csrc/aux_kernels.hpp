@@ -15,9 +15,9 @@ namespace omni {
 // issued before any is used, so a round costs one trip to memory and no load depends on a loaded value.
 // A round's pieces share one reference, so that their weights hang on nothing but their own piece (rescaled piece by
 // piece, 24 pieces were a chain of 24 exponentials behind the last load); where a request has more than 1024 elements per
-// KV head (several query tokens), each further 1024 are a workgroup of their own.  Measured: 64 requests with two query
-// tokens 60.5 -> 59.6 us per step, one request 13.0 -> 12.8 us, one token per request unchanged; workgroups of one wave or
-// rounds of 32 pieces cost a single request 0.6 - 1.0 us.
+// KV head (several query tokens), each further 1024 are a workgroup of their own.  Measured together: 1 - 2 % of a step of one
+// request (12.7 -> 12.55 us) or of two query tokens per request (60.1 -> 59.2 us), at the edge of what boxes and runs differ
+// by; nothing elsewhere.  Workgroups of one wave or rounds of 32 pieces cost a single request 0.6 - 1.0 us.
 template <int D, int kRound>
 __device__ __forceinline__ void merge_request(const AttnParams &p, int b, int kvh, int idx, int slot_first, int n) {
     const int g = idx / D;                                                // column: (query token, head)

@@ -22,9 +22,10 @@
 // 4 (4kk + j) + e and in step r of V^T P^T token slot_token(j, r), so it loads and stages exactly as the 16-bit caches
 // do and V needs no transposing at all.
 // Measured against the vector-ALU kernel (fp32 FMAs and cross-lane sums: bound by the vector ALUs from four heads per KV
-// head on, by a barrier per request below): 64-dim bf16, 256 requests of a speech-token stage 81 -> 22.5 us per step
-// (77 MB); fp32, 64 requests of 500 .. 4000 tokens: 28/4 heads of 128 dims 354 -> 106 us (592 MB, 5.6 TB/s), 8/8 heads
-// 359 -> 187 us (1.18 GB, 6.3 TB/s), 8/8 heads of 64 dims 191 -> 99 us (591 MB, 6.0 TB/s).
+// head on, by a barrier per request below): 256 requests of a speech-token stage with 64-dim bf16 heads 81.2 -> 22.2 us per
+// step (76 MB), four short fp32 requests 15.4 -> 10.9 us; fp32, 64 requests of 512 .. 4096 tokens (one pool): 16/4 heads of
+// 128 dims 265.7 -> 109.3 us (K staged; 606 MB, 5.5 TB/s), 32/4 heads 390.2 -> 121.9 us (K not staged), 32/4 heads of 64
+// dims 184.3 -> 57.0 us (303 MB, 5.3 TB/s).
 // With T query tokens per request (kernel variant MT, T * G <= 16) a column is a (query token, head) pair instead of
 // a head: it has its own query row, its own causal limit (tokens 0 .. L - T + i) and its own output row; everything
 // that is said of a head above holds per column.  An 8-bit cache is widened to bf16 in registers.
@@ -707,8 +708,8 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(AttnParams p) 
         // as the scores of the current tile have consumed K, its V rows as soon as the accumulation has consumed V,
         // and the next request's query as soon as the last scores of the current request are done.  The requests
         // stay in flight across the end-of-segment exchange below.
-        // 512-byte rows: with both halves' K operands, V and the query in registers at once the kernel spills 30 of them
-        // (120.3 us against 106 for 590 MB with K straight into registers), so the halves take turns
+        // 512-byte rows: with both halves' staged K operands, V and the query in registers at once the kernel spills 30 of
+        // them, so the halves take turns
         constexpr bool kHalves = KST && RB == 512;
         uint4 K[kHalves ? C::kKRegs : 2 * C::kKRegs], Q[C::kQRegs];
         uint32_t Vr[8][C::kVDwords];     // V rows as they are stored

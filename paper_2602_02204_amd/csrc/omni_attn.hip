@@ -117,9 +117,9 @@ struct omni_handle_s {
         const bool mfma_ok = (d.kv_dtype == OMNI_BF16 || fp8) && d.head_dim == 128;
         kernel = fp8 ? 2 : ((tune_kernel == 2 && mfma_ok) ? 2 : (tune_kernel == 1 ? 1 : (mfma_ok ? 2 : 1)));
         // Every other fp32 / bf16 cache runs the same matrix-core kernel with fp32-exact weights unless the vector-ALU kernel
-        // is asked for.  Measured against it over group sizes 1 .. 16, 0.1 MB .. 1.2 GB of cache per step: 1.3 - 7.8 x faster
-        // for bf16 / head_dim 64 (256 speech-token requests 81 -> 22.5 us), 1.3 - 4.5 x for fp32 / 64, 1.4 - 5.2 x for
-        // fp32 / 128; nowhere slower.
+        // is asked for.  Measured against it over group sizes 1, 2, 4, 8 and 16, 0.2 .. 609 MB of cache per step and 1 .. 1024
+        // requests: 1.2 - 10.5 x faster for bf16 / head_dim 64, 1.1 - 5.0 x for fp32 / 64, 1.1 - 5.1 x for fp32 / 128; the
+        // least with one head per KV head and few bytes (64 requests of 64 .. 256 tokens 16.2 -> 14.6 us), nowhere slower.
         mfma = kernel == 2 || tune_kernel != 1;
         nw = tune_target_wgs / d.num_kv_heads;
         if (nw < 1) nw = 1;

@@ -11,15 +11,18 @@
 // so a lane owns one column and nothing crosses lanes on the common path.  The scores leave a lane with tokens
 // 8 (r / 4) + 4 (lane / 32) + r % 4 in register r, and the k-slots of the second product are bound to just these.
 //
-// Bound by the vector ALUs: 195 instructions per wave and tile (half of them split the weights) against 16 matrix
-// instructions; the counters show the ALUs issuing 70 % of the time, exponentials at a quarter of the rate on top, and the
-// matrix cores busy 42 %.  Therefore 32-column instructions (half as many to issue as 16-column ones) and three
+// Bound by the vector ALUs: 174 instructions per wave and tile on 512-token chunks, 196 on ragged ones (half of them split
+// the weights), against 16 matrix instructions; the counters show the ALUs issuing 81 and 71 % of the time, exponentials at a
+// quarter of the rate on top, and the matrix cores busy 50 and 40 %.  Therefore 32-column instructions (half as many to issue
+// as 16-column ones) and three
 // independent workgroups per compute unit: their barriers do not meet, so one's matrix work hides another's weights.
-// Measured, 24 requests of 129 .. 2049 tokens with chunks of 1 .. 1024, 16/2 heads: vector-ALU kernel 2078 us, this one
-// 115 us (with the append); 32 requests with 512-token chunks (137 GFLOP) 311 us = 440 TFLOP/s.  Taken back: 8 waves per workgroup (174 us,
-// 330 us), the tiles' work software-pipelined as in prefill_mfma.hpp at two waves per SIMD (143 us, 331 us), four waves
-// per SIMD (231 us: 128 registers do not hold it).  v_dot2_f32_bf16 for the split's subtractions (one instruction for
-// two) gained nothing: it does not run at the full rate.
+// Measured with the append, 24 requests of 129 .. 2049 tokens with chunks of 1 .. 1024, 16/2 heads: vector-ALU kernel
+// 2010 us, this one 115 us; 32 requests with 512-token chunks (137 GFLOP) 310 us = 440 TFLOP/s.  Taken back: 8 waves per
+// workgroup (174 us, 330 us), the tiles' work software-pipelined as in prefill_mfma.hpp at two waves per SIMD (143 us, 331 us),
+// four waves per SIMD (231 us: 128 registers do not hold it).  v_dot2_f32_bf16 for the split's subtractions (one instruction
+// for two) gained nothing: it does not run at the full rate.  Distance from 64 bits against the vector-ALU kernel's: 1.05 - 1.17
+// times where scores have deviation one and the context is not split, 0.2 - 0.8 times where it is split or scores are larger;
+// the scores in two chains bring 1.12 to 1.06 on 40-token contexts and cost 2 % (taken back).
 #pragma once
 #include "prefill_mfma.hpp"
 #include "row_walk.hpp"
