@@ -86,9 +86,10 @@ typedef struct omni_handle_s *omni_handle_t;
 
 /* Tuning keys for omni_set_tuning.  Defaults are chosen for 256 compute units. */
 typedef enum {
-    OMNI_TUNE_KERNEL = 0,           /* 0 = auto: the matrix cores for every format; 1 = vector-ALU kernel (not over an 8-bit
-                                       cache); 2 = the matrix-core kernel whose softmax weights keep 16 bits (bf16 with
-                                       head_dim 128, 8-bit caches: what auto takes there; UNSUPPORTED for the others) */
+    OMNI_TUNE_KERNEL = 0,           /* decode calls: 0 = auto, the matrix cores for every format; 1 = vector-ALU kernel (not over
+                                       an 8-bit cache); 2 = the matrix-core kernel whose softmax weights keep 16 bits (bf16
+                                       with head_dim 128, 8-bit caches: what auto takes there; UNSUPPORTED for the others).
+                                       1 also sends the multi-token calls to the vector ALUs */
     OMNI_TUNE_TARGET_WORKGROUPS = 1,/* workgroups the attention kernel is launched with (> 0; rounded down to a multiple of Hkv) */
     OMNI_TUNE_MIN_PARTITION = 2,    /* smallest range of context, in tokens, one workgroup may be given (multiple of 32) */
     OMNI_TUNE_FORCE_PARTITION = 3,  /* > 0: every workgroup range is exactly this many tokens (multiple of 32); 0 = plan decides */
