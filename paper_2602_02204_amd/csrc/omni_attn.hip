@@ -76,9 +76,12 @@ struct omni_handle_s {
     // Context split of the multi-token-query kernel for chunks of up to max_q_len tokens: where the query blocks fill
     // at most half of the compute units, as many workgroups per (query block, KV head, request) as it takes to fill
     // them, at most 16 and no more than the longest context the handle allows can use.  1 = no split.
+    unsigned prefill_blocks(int max_q_len) const {               // per (request, KV head)
+        const int columns = prefill_columns(d.head_dim);
+        return (unsigned)(((long long)max_q_len * G + columns - 1) / columns);
+    }
     long long prefill_workgroups(int max_q_len) const {          // of the matrix-core kernel, unsplit
-        const int qb = prefill_tokens_per_block(G, d.head_dim);
-        return (long long)((max_q_len + qb - 1) / qb) * d.num_kv_heads * d.batch;
+        return (long long)prefill_blocks(max_q_len) * d.num_kv_heads * d.batch;
     }
     int prefill_splits(int max_q_len) const {
         if (!prefill_mfma() || tune_prefill_splits == 1) return 1;
@@ -727,7 +730,6 @@ static omni_status_t launch_prefill(omni_handle_t h, const void *q, const void *
     p.scale_log2 = scale * kLog2e;
     p.Hq = d.num_q_heads; p.Hkv = d.num_kv_heads; p.G = h->G; p.MB = d.max_blocks_per_seq;
     p.out_bf16 = d.out_dtype == OMNI_BF16;
-    const int qb = mfma ? prefill_tokens_per_block(h->G, d.head_dim) : kWaves;       // query tokens per workgroup
     // The context is split only if the registered workspace holds the pieces (omni_prefill_workspace_bytes), and the requests
     // are taken longest first only with a registered workspace: a one-workgroup kernel ranks them into its first words, the
     // pieces of a split follow.  With 64-dim heads both stay behind the decode calls' part of the workspace, if it is that
@@ -744,7 +746,8 @@ static omni_status_t launch_prefill(omni_handle_t h, const void *q, const void *
     p.min_split_steps = h->tune_prefill_min_split / (2 * kTile);
     p.part_ml = ns > 1 ? reinterpret_cast<float2 *>(ws + order_bytes) : nullptr;
     p.part_o = ns > 1 ? reinterpret_cast<float *>(ws + order_bytes + omni_handle_s::prefill_ml_bytes(d, max_q_len, ns)) : nullptr;
-    const dim3 grid((unsigned)((max_q_len + qb - 1) / qb) * (unsigned)ns, (unsigned)d.num_kv_heads, (unsigned)d.batch);
+    const unsigned blocks = mfma ? h->prefill_blocks(max_q_len) : (unsigned)(((long long)max_q_len + kWaves - 1) / kWaves);
+    const dim3 grid(blocks * (unsigned)ns, (unsigned)d.num_kv_heads, (unsigned)d.batch);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     (void)hipGetLastError();
     if (sorted) {

@@ -32,12 +32,6 @@ namespace omni {
 constexpr int kPrefillExactThreads = 2 * prefill_columns(64);      // 32 columns per wave
 constexpr float kPrefillExactLimit = 256.f;                        // sum of a lane's 16 weights of a tile beyond which the reference moves
 
-typedef float f32x16_t __attribute__((ext_vector_type(16)));
-
-__device__ __forceinline__ f32x16_t mfma32_bf16(const uint4 &a, const uint4 &b, f32x16_t c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
-}
-
 template <int PS>
 __global__ __launch_bounds__(kPrefillExactThreads, 3) void prefill_exact_kernel(PrefillParams p) {
     constexpr int D = 64, RB = 2 * D;                            // bytes of a cache row
@@ -55,13 +49,13 @@ __global__ __launch_bounds__(kPrefillExactThreads, 3) void prefill_exact_kernel(
     const int L = p.context_lens[b];
     const int n_q = min(p.q_lens[b], L);
     const int n_live = min(n_q, p.max_q_len);                    // a chunk longer than the grid's bound is cut off there
-    const int QB = prefill_tokens_per_block(G, D);
+    constexpr int kColumns = prefill_columns(D);
     const int NS = p.num_splits;
     const int split = NS > 1 ? (int)blockIdx.x % NS : 0;
-    const int q0 = (NS > 1 ? (int)blockIdx.x / NS : (int)blockIdx.x) * QB;      // first query token of this workgroup
-    if (n_live <= 0 || q0 >= n_live) return;
+    const int c0 = (NS > 1 ? (int)blockIdx.x / NS : (int)blockIdx.x) * kColumns;     // first column of this workgroup
+    if (n_live <= 0 || c0 >= n_live * G) return;
     const int pos0 = L - n_q;                                    // position of the chunk's first token
-    const int wg_last = min(n_live, q0 + QB) - 1;                // last query token of the workgroup
+    const int wg_last = prefill_last_token(c0, kColumns, G, n_live);
     const int kv_end = pos0 + wg_last + 1;                       // the workgroup's queries see tokens 0 .. kv_end - 1
     const int n_tiles = (kv_end + kTile - 1) / kTile;
     const int n_steps = (n_tiles + 1) >> 1;
@@ -75,11 +69,11 @@ __global__ __launch_bounds__(kPrefillExactThreads, 3) void prefill_exact_kernel(
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int col = lane & 31, h = lane >> 5;
-    const int c = wave * 32 + col;                               // column of the workgroup
-    const int tl = c / G, g = c - tl * G;
-    const bool live = tl < QB && q0 + tl < n_live;
-    const int pos = live ? pos0 + q0 + tl : -1;                  // -1: padding column (never stored)
-    const size_t row = ((size_t)(p.q_offsets[b] + q0 + tl) * p.Hq + head0 + g) * D;
+    const int c = c0 + wave * 32 + col;
+    const int qi = c / G, g = c - qi * G;
+    const bool live = qi < n_live;
+    const int pos = live ? pos0 + qi : -1;                       // -1: padding column (never stored)
+    const size_t row = ((size_t)(p.q_offsets[b] + qi) * p.Hq + head0 + g) * D;
     uint4 Q[4];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
@@ -236,9 +230,10 @@ __global__ __launch_bounds__(kPrefillExactThreads, 3) void prefill_exact_kernel(
     int id;
     asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(id));
     const int ecol = id & 31, eh = id >> 5;
-    const int etl = (wave * 32 + ecol) / G, eg = wave * 32 + ecol - etl * G;
-    const int epos = (etl < QB && q0 + etl < n_live) ? pos0 + q0 + etl : -1;
-    const long long q_row0 = p.q_offsets[b] + q0;
+    const int wc0 = c0 + wave * 32;                              // the wave's first column
+    const int eqi = (wc0 + ecol) / G, eg = wc0 + ecol - eqi * G;
+    const int epos = eqi < n_live ? pos0 + eqi : -1;
+    const long long q_row0 = p.q_offsets[b];
     const float lsum = l + __shfl_xor(l, 32);                    // the two halves hold disjoint tokens
     // A column is sound if its sums are finite and its largest weight is about one.  Else it is walked again row by row:
     //  - an infinite or NaN V element is multiplied with the weights of all 32 columns, that is with zero for a query in
@@ -254,8 +249,8 @@ __global__ __launch_bounds__(kPrefillExactThreads, 3) void prefill_exact_kernel(
     unsigned again = (unsigned)halves | (unsigned)(halves >> 32);            // by column
     if (epos >= 0 && !(again >> ecol & 1)) {
         const float inv = 1.f / lsum;                            // without a split the column saw its own position: lsum > 0
-        const size_t row = ((size_t)(q_row0 + etl) * p.Hq + head0 + eg) * D;
-        const size_t pi = (((size_t)b * p.max_q_len + q0 + etl) * p.Hq + head0 + eg) * NS + split;
+        const size_t row = ((size_t)(q_row0 + eqi) * p.Hq + head0 + eg) * D;
+        const size_t pi = (((size_t)b * p.max_q_len + eqi) * p.Hq + head0 + eg) * NS + split;
 #pragma unroll
         for (int e = 0; e < 2; ++e)
 #pragma unroll
@@ -270,17 +265,17 @@ __global__ __launch_bounds__(kPrefillExactThreads, 3) void prefill_exact_kernel(
     }
     const RowSource src = row_source<uint16_t, D>(p.k_cache, p.v_cache, bt, p.Hkv, kvh, kLog2Ps);
     while (again) {                                              // uniform
-        const int c0 = __builtin_ctz(again), tok = (wave * 32 + c0) / G, h0 = wave * 32 + c0 - tok * G;
-        const int nh = min(min(kWalkHeads, G - h0), 32 - c0);    // heads of one query token: consecutive columns
+        const int c1 = __builtin_ctz(again), tok = (wc0 + c1) / G, h0 = wc0 + c1 - tok * G;
+        const int nh = min(min(kWalkHeads, G - h0), 32 - c1);    // heads of one query token: consecutive columns
         const size_t row0 = (size_t)(q_row0 + tok) * p.Hq + head0 + h0;
         RowWalk<D> w;
         walk_rows<uint16_t, D, true>(src, reinterpret_cast<const char *>(p.q) + row0 * RB, nh, s_begin * kStep,
-                                     min(s_end * kStep, pos0 + q0 + tok + 1), p.scale_log2, id, w);
+                                     min(s_end * kStep, pos0 + tok + 1), p.scale_log2, id, w);
 #pragma unroll
         for (int i = 0; i < kWalkHeads; ++i)
-            if (i < nh && (again >> (c0 + i) & 1) && id < 16) {            // every lane group has the sums: one stores them
+            if (i < nh && (again >> (c1 + i) & 1) && id < 16) {            // every lane group has the sums: one stores them
                 if (ns_eff > 1) {
-                    const size_t pi = (((size_t)b * p.max_q_len + q0 + tok) * p.Hq + head0 + h0 + i) * NS + split;
+                    const size_t pi = (((size_t)b * p.max_q_len + tok) * p.Hq + head0 + h0 + i) * NS + split;
                     *reinterpret_cast<float4 *>(p.part_o + pi * D + 4 * id) = make_float4(w.o[i][0], w.o[i][1], w.o[i][2], w.o[i][3]);
                     if (id == 0) p.part_ml[pi] = make_float2(w.m[i], w.l[i]);
                 } else {
@@ -288,7 +283,7 @@ __global__ __launch_bounds__(kPrefillExactThreads, 3) void prefill_exact_kernel(
                     store_out4(p, (row0 + i) * D + 4 * id, make_float4(w.o[i][0] * inv, w.o[i][1] * inv, w.o[i][2] * inv, w.o[i][3] * inv));
                 }
             }
-        again &= ~(((1u << nh) - 1) << c0);
+        again &= ~(((1u << nh) - 1) << c1);
     }
 }
 

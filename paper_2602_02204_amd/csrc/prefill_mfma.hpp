@@ -2,22 +2,28 @@
 // head_dim 128, group size <= 16.  Query i of request b's chunk sits at position p = L_b - n_b + i and attends to
 // tokens 0 .. p (causal inside the chunk).
 //
-// A workgroup (8 waves, two per SIMD) owns one (request, KV head, block of query tokens).  Its 256 "columns" are the
-// (query token, query head of the group) pairs of that block in token-major order; a wave owns 32 consecutive ones =
-// two 16-column MFMA blocks.  The same transposed products as in the decode kernel are used, per 32-token tile and
-// per column block:
-//   S^T = K Q^T     (A = K rows from shared memory, B = the block's queries, held in registers for the whole kernel)
+// The (query token, query head of the group) pairs of a request's chunk and one KV head are its "columns", in token-major
+// order; a workgroup (8 waves, two per SIMD) owns 256 consecutive ones, wherever that cuts a token's heads (512 tokens of
+// 7 heads are 14 workgroups; whole tokens only would make them 15), a wave 32 of them = the columns of one 32x32x16 matrix
+// instruction.  Per 32-token tile:
+//   S^T = K Q^T     (A = K rows from shared memory, B = the wave's queries, held in registers for the whole kernel)
 //   O^T += V^T P^T  (A = V transposed, B = the softmax weights; both as fp16: V is converted once per workgroup on
 //                    its way into shared memory, exactly for 2^-14 <= |V| <= 65504, and fp16 weights carry 11
 //                    significant bits, so one product does what bf16 weights need a hi + lo pair for)
-// so every lane owns one column: running reference, sum and rescale never cross lanes on the common path.
+// so every lane owns one column (the two halves of a wave hold its even and odd groups of four tokens): running reference,
+// sum and rescale never cross lanes on the common path.
 // What differs from decode is reuse: K/V tiles are fetched once per workgroup into shared memory (double buffered,
-// one barrier per 64 tokens) and feed 16 column blocks, and V^T comes out of shared memory through transposing reads.
+// one barrier per 64 tokens) and feed 256 columns, and V^T comes out of shared memory through transposing reads.
 // That makes the path a dense contraction, not a stream.  The three pieces of a tile's work are software-pipelined
-// across tiles, so that a wave has matrix-core and vector-ALU instructions to issue side by side; on this chip both
-// kinds go through one issue port per SIMD, and the two instruction streams together account for about half of a tile's
-// time (0.65 of 1.2 us per SIMD; 32 requests with 512-token chunks, 28/4 heads: 556 us, vector ALUs issuing 49 %, matrix cores
-// busy 40 % of the cycles); the rest is waiting, two waves per SIMD that meet at a barrier every 64 tokens.
+// across tiles, so that a wave has matrix-core and vector-ALU instructions to issue side by side.
+// What bounds it: the clock the chip holds under this load (1.7 - 1.85 GHz of 2.4), at which the matrix cores are busy
+// 56 % of the time on long contexts (1080 TFLOP/s; a library product of 8192^3 reaches 1190) and 47 % on 32 requests with
+// 512-token chunks, whose workgroups spend 10 of 75 us on their start and end.  Against 16-column instructions over 36
+// whole tokens with every step testing each of its tiles: 16 % fewer cycles at a clock 8 % lower,
+// 590.0 -> 574.8 us for those 32 requests with their append.
+// The instructions are 32 columns wide: half as many to issue for the same product.  The rows of V are padded to 320 bytes because a transposing read of 32 lanes takes 64 bytes of each of four rows
+// (288: 583 -> 564 us); the steps at the ends of the context have their own code because conditions around 16-register
+// operands made the compiler copy and spill the accumulators (in one loop with tests: 2400 us).
 #pragma once
 #include <type_traits>
 
@@ -27,12 +33,10 @@ namespace omni {
 
 constexpr int kPrefillThreads = 512;                  // 8 waves = 2 per SIMD share one K/V tile in shared memory
 constexpr int kPrefillWaves = kPrefillThreads / 64;
-constexpr int kPrefillBlocks = 2;                     // 16-column MFMA blocks per wave
-constexpr int kPrefillCols = 16 * kPrefillBlocks;     // (token, head) pairs per wave
 constexpr int kPrefillRowBytes = 256 + 16;            // a 256-byte K row plus padding: conflict-free 16-byte LDS reads
-constexpr int kPrefillVRowBytes = 256 + 32;           // V rows: conflict-free 8-byte transposing reads (4 rows x 32 B)
+constexpr int kPrefillVRowBytes = 256 + 64;           // V rows: conflict-free 8-byte transposing reads (4 rows x 64 B)
 constexpr float kPrefillBias = 6.f;                   // a moved reference sits this many log2 units below the maximum
-constexpr float kPrefillSumLimit = 32768.f;           // sum of a lane's 8 weights of a tile beyond which the reference moves
+constexpr float kPrefillSumLimit = 32768.f;           // sum of a lane's 16 weights of a tile beyond which the reference moves
 
 // Transposing 64-bit read from shared memory (see its use below for the lane arrangement).
 __device__ __forceinline__ uint2 lds_read_tr16_b64(const char *p) {
@@ -45,8 +49,15 @@ __device__ __forceinline__ uint2 lds_read_tr16_b64(const char *p) {
 typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ f32x4_t mfma_f16(const uint4 &a, const uint4 &b, f32x4_t c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), c, 0, 0, 0);
+typedef float f32x16_t __attribute__((ext_vector_type(16)));
+
+// A: 32 rows x 16 k, B: 16 k x 32 columns; a lane holds row / column lane % 32 and the 8 k of half lane / 32.  The result
+// leaves it with rows 8 (r / 4) + 4 (lane / 32) + r % 4 of column lane % 32 in register r.
+__device__ __forceinline__ f32x16_t mfma32_bf16(const uint4 &a, const uint4 &b, f32x16_t c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x16_t mfma32_f16(const uint4 &a, const uint4 &b, f32x16_t c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), c, 0, 0, 0);
 }
 
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
@@ -114,10 +125,14 @@ __device__ __forceinline__ int prefill_effective_splits(int num_splits, int n_st
     return max(1, min(num_splits, n_steps / min_split_steps));
 }
 
-// Query tokens per workgroup for a group of G heads: its 256 columns (128 with 64-dim heads) are the (token, head) pairs
-// in token-major order, cut into runs of 32 for the waves wherever that falls.
-__host__ __device__ constexpr int prefill_columns(int D) { return D == 64 ? 128 : kPrefillWaves * kPrefillCols; }
-__host__ __device__ inline int prefill_tokens_per_block(int G, int D) { return prefill_columns(D) / G; }
+// Columns of a workgroup: the (query token, head) pairs of a chunk and one KV head, in token-major order, are cut into runs
+// of this many, and those into runs of 32 for the waves.
+__host__ __device__ constexpr int prefill_columns(int D) { return D == 64 ? 128 : 32 * kPrefillWaves; }
+// The chunk's last query token that the workgroup with first column c0 has a column of (n_live tokens are live).
+__host__ __device__ inline int prefill_last_token(int c0, int columns, int G, int n_live) {
+    const int t = (c0 + columns - 1) / G;
+    return t < n_live ? t : n_live - 1;
+}
 
 // KV8: the pools hold 8-bit E4M3 bytes with one scale per (page, KV head).  The staging threads widen K to bf16
 // (exact) and V times its page's scale to fp16 (one rounding, 2^-12 relative: the size of the weights' own rounding) on
@@ -128,9 +143,14 @@ __global__ __launch_bounds__(kPrefillThreads, 1) void prefill_mfma_kernel(Prefil
     constexpr int D = 128;
     constexpr int ES = KV8 ? 1 : 2;                              // bytes per cache element
     constexpr int kLog2Ps = (PS == 16) ? 4 : 5;
-    constexpr int kTileBytes = kTile * kPrefillVRowBytes;        // room for one K or V tile in shared memory
-    __shared__ __align__(16) char smem[2][2][2][kTileBytes];     // [buffer][tile of the step][K, V]
-    __shared__ float kscale_lds[2][2][2];                        // 8-bit cache: [buffer][tile][16-token half] K scales
+    constexpr int kStep = 2 * kTile;                             // tokens staged at a time
+    constexpr int kColumns = prefill_columns(D);
+    constexpr int kKRow = kPrefillRowBytes, kVRow = kPrefillVRowBytes;
+    constexpr int kTokStride = kPrefillThreads / 16;             // a thread stages one of a row's 16 pieces of every
+    constexpr int NP = kStep / kTokStride;                       // kTokStride-th token of a step
+    __shared__ __align__(16) char k_lds[2][kStep * kKRow];
+    __shared__ __align__(16) char v_lds[2][kStep * kVRow];
+    __shared__ float kscale_lds[2][4];                           // 8-bit cache: [buffer][16 tokens] K scales
 
     // Workgroups are dispatched in blockIdx order, z slowest: with the requests taken longest first the long-running
     // workgroups start first and the short ones fill the end of the launch.
@@ -139,312 +159,296 @@ __global__ __launch_bounds__(kPrefillThreads, 1) void prefill_mfma_kernel(Prefil
     const int L = p.context_lens[b];
     const int n_q = min(p.q_lens[b], L);
     const int n_live = min(n_q, p.max_q_len);                    // a chunk longer than the grid's bound is cut off there
-    const int QB = prefill_tokens_per_block(G, D);
     const int NS = p.num_splits;
     const int split = NS > 1 ? (int)blockIdx.x % NS : 0;
-    const int q0 = (NS > 1 ? (int)blockIdx.x / NS : (int)blockIdx.x) * QB;      // first query token of this workgroup
-    if (n_live <= 0 || q0 >= n_live) return;
+    const int c0 = (NS > 1 ? (int)blockIdx.x / NS : (int)blockIdx.x) * kColumns;     // first column of this workgroup
+    if (n_live <= 0 || c0 >= n_live * G) return;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int col = lane & 15, j = lane >> 4;
+    const int col = lane & 31, h = lane >> 5;
     const long long q_row0 = p.q_offsets[b];
     const int pos0 = L - n_q;                                    // position of the chunk's first token
-    const int wg_last = min(n_live, q0 + QB) - 1;                // last query token of the workgroup
+    const int wg_last = prefill_last_token(c0, kColumns, G, n_live);
     const int n_tiles = (pos0 + wg_last) / kTile + 1;            // tiles that hold tokens 0 .. position of wg_last
 
-    // ---- this lane's columns (one per column block): query token, head, position; and the queries as MFMA B operands
-    int pos[kPrefillBlocks];                                     // -1: padding column (never stored)
-    uint4 Q[kPrefillBlocks][4];
-    int wave_max_pos = -1;
+    // ---- this lane's column: query token, head, position; and the queries as MFMA B operands
+    const int qi = (c0 + wave * 32 + col) / G, g = c0 + wave * 32 + col - qi * G;
+    const bool live = qi < n_live;
+    const int pos = live ? pos0 + qi : -1;                       // -1: padding column (never stored)
+    uint4 Q[8];
+    {
+        const char *qrow = reinterpret_cast<const char *>(p.q) + ((size_t)(q_row0 + qi) * p.Hq + head0 + g) * (D * 2);
 #pragma unroll
-    for (int cb = 0; cb < kPrefillBlocks; ++cb) {
-        const int c = wave * kPrefillCols + cb * 16 + col;       // column of the workgroup
-        const int tl = c / G, g = c - tl * G;
-        const int qi = q0 + tl;                                  // query token inside the chunk
-        const bool live = tl < QB && qi < n_live;
-        pos[cb] = live ? pos0 + qi : -1;
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) Q[cb][kk] = make_uint4(0, 0, 0, 0);
-        if (live) {
-            const char *qrow = reinterpret_cast<const char *>(p.q) + ((size_t)(q_row0 + qi) * p.Hq + head0 + g) * (D * 2);
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) Q[cb][kk] = *reinterpret_cast<const uint4 *>(qrow + (4 * kk + j) * 16);
+        for (int kk = 0; kk < 8; ++kk) {
+            Q[kk] = make_uint4(0, 0, 0, 0);
+            if (live) Q[kk] = *reinterpret_cast<const uint4 *>(qrow + (2 * kk + h) * 16);
         }
-        wave_max_pos = max(wave_max_pos, pos[cb]);
     }
+    int wave_max_pos = pos, wave_min_pos = live ? pos : 0x7fffffff;
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) wave_max_pos = max(wave_max_pos, __shfl_xor(wave_max_pos, off));
-    // the smallest live position of the wave: tiles that end at or before it need no mask
-    int wave_min_pos = 0x7fffffff;
-#pragma unroll
-    for (int cb = 0; cb < kPrefillBlocks; ++cb) wave_min_pos = min(wave_min_pos, pos[cb] >= 0 ? pos[cb] : 0x7fffffff);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) wave_min_pos = min(wave_min_pos, __shfl_xor(wave_min_pos, off));
+    for (int off = 16; off > 0; off >>= 1) {
+        wave_max_pos = max(wave_max_pos, __shfl_xor(wave_max_pos, off));
+        wave_min_pos = min(wave_min_pos, __shfl_xor(wave_min_pos, off));
+    }
+    wave_max_pos = __builtin_amdgcn_readfirstlane(wave_max_pos);
+    wave_min_pos = __builtin_amdgcn_readfirstlane(wave_min_pos);
 
-    // ---- staging: a step is 64 tokens = two 32-token tiles; thread t moves piece t of the 512 16-byte pieces of
-    // each tile's K rows and V rows (piece = 16 * token + chunk).  The products below run as a pipeline in which V of a
-    // tile is needed two tiles after its K, so V is fetched and staged one step behind K.
-    const size_t page_stride = (size_t)p.Hkv * PS * D * ES;
+    // ---- staging: thread t moves piece t % 16 of tokens t / 16, ... of a step's K rows and V rows.  The products below run
+    // as a pipeline in which V of a tile is needed two tiles after its K, so V is fetched and staged one step behind K.
+    const unsigned page_stride = (unsigned)(p.Hkv * PS * D * ES);   // gridDim.y bounds Hkv: fits 32 bits
     const char *kbase = reinterpret_cast<const char *>(p.k_cache) + (size_t)kvh * PS * D * ES;
     const char *vbase = reinterpret_cast<const char *>(p.v_cache) + (size_t)kvh * PS * D * ES;
     const int32_t *bt = p.block_table + (size_t)b * p.MB;
-    const int st_tok = threadIdx.x >> 4, st_chunk = threadIdx.x & 15;       // token 0..31 of a tile
-    const int lds_off = st_tok * kPrefillRowBytes + st_chunk * 16;
-    const int lds_off_v = st_tok * kPrefillVRowBytes + st_chunk * 16;
+    const int st_tok = threadIdx.x >> 4, st_chunk = threadIdx.x & 15;
+    const int lds_off = st_tok * kKRow + st_chunk * 16;
+    const int lds_off_v = st_tok * kVRow + st_chunk * 16;
     const int n_steps = (n_tiles + 1) >> 1;
     // this workgroup's share of the steps: [s_begin, s_end), all of them without a split.  The launch provides NS
-    // workgroups per query block; how many of them share the work depends on the block's context.
+    // workgroups per 256 columns; how many of them share the work depends on their context.
     const int ns_eff = prefill_effective_splits(NS, n_steps, p.min_split_steps);
     if (split >= ns_eff) return;
     const int s_begin = (int)((long long)n_steps * split / ns_eff);
     const int s_end = (int)((long long)n_steps * (split + 1) / ns_eff);
-    uint4 sk[2], sv_[2];                                         // 8-bit cache: 8 bytes each, in .x and .y
-    float sks[2] = {1.f, 1.f}, svs[2] = {1.f, 1.f};             // 8-bit cache: the scales of the rows' pages
+    const int last_page = (L - 1) >> kLog2Ps;
+    uint4 sk[NP], sv_[NP];                                       // 8-bit cache: 8 bytes each, in .x and .y
+    float sks[NP], svs[NP];                                      // 8-bit cache: the scales of the rows' pages
     // Page numbers are looked up one step before the rows they address are fetched, so that no fetch waits for its
     // own table entry: pg_k holds the pages of the step whose K rows are fetched next, pg_v (the same entries one
     // step later) those of the step whose V rows are fetched next.
-    int pg_k[2], pg_v[2] = {0, 0};
+    int pg_k[NP], pg_v[NP];
     auto lookup = [&](int step) __attribute__((always_inline)) {
 #pragma unroll
-        for (int sub = 0; sub < 2; ++sub)                                   // an entry of the table for every lane
-            pg_k[sub] = bt[min((2 * step + sub) * kTile + st_tok, L - 1) >> kLog2Ps];
+        for (int i = 0; i < NP; ++i)
+            pg_k[i] = bt[(unsigned)min(step * (kStep / PS) + ((st_tok + i * kTokStride) >> kLog2Ps), last_page)];
     };
-    auto fetch_rows = [&](auto fast, const char *base, const float *scale, int step, const int (&pg)[2], uint4 (&r)[2],
-                          float (&sc)[2]) __attribute__((always_inline)) {
+    auto fetch_rows = [&](auto fast, const char *base, const float *scale, int step, const int (&pg)[NP], uint4 (&r)[NP],
+                          float (&sc)[NP]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int sub = 0; sub < 2; ++sub) {
-            const int t = (2 * step + sub) * kTile + st_tok;
-            const char *src = base + (size_t)pg[sub] * page_stride + (size_t)(t & (PS - 1)) * (D * ES) + st_chunk * (8 * ES);
+        for (int i = 0; i < NP; ++i) {
+            const int t = step * kStep + st_tok + i * kTokStride;
+            const char *src = base + (unsigned long long)(unsigned)pg[i] * page_stride +
+                              ((st_tok + i * kTokStride) & (PS - 1)) * (D * ES) + st_chunk * (8 * ES);
             const bool in = decltype(fast)::value || (step < s_end && t < L);
-            r[sub] = make_uint4(0, 0, 0, 0);                                // rows beyond the context are zero
+            r[i] = make_uint4(0, 0, 0, 0);                                // rows beyond the context are zero
             if constexpr (KV8) {
                 if (in) {
                     const uint2 v = *reinterpret_cast<const uint2 *>(src);
-                    r[sub].x = v.x; r[sub].y = v.y;
+                    r[i].x = v.x; r[i].y = v.y;
                 }
-                sc[sub] = scale[(size_t)pg[sub] * p.Hkv];                   // the page is a valid one also beyond the context
+                sc[i] = scale[(size_t)pg[i] * p.Hkv];                   // the page is a valid one also beyond the context
             } else {
-                if (in) r[sub] = *reinterpret_cast<const uint4 *>(src);
+                if (in) r[i] = *reinterpret_cast<const uint4 *>(src);
             }
         }
     };
     auto stage_k = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
-        for (int sub = 0; sub < 2; ++sub) {
+        for (int i = 0; i < NP; ++i) {
+            char *dst = &k_lds[buf][lds_off + i * (kTokStride * kKRow)];
             if constexpr (KV8) {
-                *reinterpret_cast<uint4 *>(&smem[buf][sub][0][lds_off]) = fp8x8_to_bf16x8(sk[sub].x, sk[sub].y);
-                if (st_chunk == 0 && (st_tok & 15) == 0) kscale_lds[buf][sub][st_tok >> 4] = sks[sub];
+                *reinterpret_cast<uint4 *>(dst) = fp8x8_to_bf16x8(sk[i].x, sk[i].y);
+                if (st_chunk == 0 && (st_tok & 15) == 0) kscale_lds[buf][(st_tok + i * kTokStride) >> 4] = sks[i];
             } else {
-                *reinterpret_cast<uint4 *>(&smem[buf][sub][0][lds_off]) = sk[sub];
+                *reinterpret_cast<uint4 *>(dst) = sk[i];
             }
         }
     };
     auto stage_v = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
-        for (int sub = 0; sub < 2; ++sub) {
+        for (int i = 0; i < NP; ++i) {
+            char *dst = &v_lds[buf][lds_off_v + i * (kTokStride * kVRow)];
             if constexpr (KV8)
-                *reinterpret_cast<uint4 *>(&smem[buf][sub][1][lds_off_v]) = fp8x8_scaled_to_f16x8(sv_[sub].x, sv_[sub].y, svs[sub]);
+                *reinterpret_cast<uint4 *>(dst) = fp8x8_scaled_to_f16x8(sv_[i].x, sv_[i].y, svs[i]);
             else
-                *reinterpret_cast<uint4 *>(&smem[buf][sub][1][lds_off_v]) = bf16x8_to_f16x8(sv_[sub]);
+                *reinterpret_cast<uint4 *>(dst) = bf16x8_to_f16x8(sv_[i]);
         }
     };
 
-    // ---- per-column online-softmax state
-    float m[kPrefillBlocks], l[kPrefillBlocks];
-    f32x4_t acc[kPrefillBlocks][8];
-#pragma unroll
-    for (int cb = 0; cb < kPrefillBlocks; ++cb) {
-        m[cb] = -INFINITY; l[cb] = 0.f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[cb][e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    }
-    // A tile of this workgroup's steps that holds tokens some column of this wave sees.
-    auto tile_active = [&](int t) { return t >= 2 * s_begin && t < 2 * s_end && t * kTile <= wave_max_pos; };
+    // ---- the column's online-softmax state
+    float m = -INFINITY, l = 0.f;
+    f32x16_t acc[4] = {{}, {}, {}, {}};                          // acc[e][r] = O^T[dim 32 e + 8 (r / 4) + 4 h + r % 4][column]
 
     // ---- the three pieces of a tile's work
-    // Raw scores q.k of the column blocks: S[cb][h] holds tokens 16 h + 4 j .. + 3 of the tile for column `col`.  The
-    // softmax scale is applied inside the exponent (one fused multiply-add per score): scale > 0, so the order of
-    // scores is that of the raw dot products.
-    auto scores = [&](const char *ks, f32x4_t (&S)[kPrefillBlocks][2], const float *ksc, float (&a)[2]) __attribute__((always_inline)) {
+    // Raw scores q.k: S[r] holds token 8 (r / 4) + 4 h + r % 4 of the tile for column `col`.  The softmax scale is applied
+    // inside the exponent (one fused multiply-add per score): scale > 0, so the order of scores is that of the raw dot
+    // products.
+    const int k_off = col * kKRow + h * 16;
+    const int v_off = (4 * h + ((lane & 15) >> 2)) * kVRow + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
+    auto scores = [&](const char *ks, f32x16_t &S, const float *ksc, float (&a)[2]) __attribute__((always_inline)) {
         if constexpr (KV8) {                                     // read with the rows: both are replaced together
             a[0] = ksc[0] * p.scale_log2; a[1] = ksc[1] * p.scale_log2;
         }
         uint4 K[8];
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            K[kk] = *reinterpret_cast<const uint4 *>(ks + col * kPrefillRowBytes + (4 * kk + j) * 16);
-            K[4 + kk] = *reinterpret_cast<const uint4 *>(ks + (16 + col) * kPrefillRowBytes + (4 * kk + j) * 16);
-        }
+        for (int kk = 0; kk < 8; ++kk) K[kk] = *reinterpret_cast<const uint4 *>(ks + k_off + kk * 32);
+        S = f32x16_t{};
 #pragma unroll
-        for (int cb = 0; cb < kPrefillBlocks; ++cb) {
-            S[cb][0] = f32x4_t{0.f, 0.f, 0.f, 0.f}; S[cb][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        }
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-#pragma unroll
-            for (int cb = 0; cb < kPrefillBlocks; ++cb) {
-                S[cb][0] = mfma_bf16(K[kk], Q[cb][kk], S[cb][0]);
-                S[cb][1] = mfma_bf16(K[4 + kk], Q[cb][kk], S[cb][1]);
-            }
-        }
+        for (int kk = 0; kk < 8; ++kk) S = mfma32_bf16(K[kk], Q[kk], S);
     };
-    // Weights of tile t from its raw scores: P[cb] as one fp16 MFMA operand.  A column's reference m (log2 domain) is
+    // Weights of tile t from its raw scores: P as two fp16 MFMA operands.  A column's reference m (log2 domain) is
     // moved only when a weight would leave the fp16 range, which shows in the sum of the tile's weights: any common
     // reference gives the same softmax.  A move puts m at the running maximum less the bias, so the largest weight of a
     // column then lies between 2^bias and the limit, and a weight loses precision as an fp16 subnormal only when it is
     // 2^-20 of the largest or less.  After a column's first tiles moves are rare, so the maximum over the tile, its
-    // exchange between the four lane groups of a column and the rescale of what was summed under the old reference
+    // exchange between the two halves of a column and the rescale of what was summed under the old reference
     // leave the common path.  The sums are taken over the rounded weights, the ones the matrix cores multiply.
-    auto weights = [&](auto fast, int t, f32x4_t (&S)[kPrefillBlocks][2], uint4 (&P)[kPrefillBlocks], const float (&a)[2]) __attribute__((always_inline)) {
+    // `mask`: tokens after the column's position may be among the tile's (kMaybe: the wave looks first).
+    constexpr int kNone = 0, kMaybe = 1, kAlways = 2;
+    constexpr std::integral_constant<int, kNone> before{};
+    constexpr std::integral_constant<int, kMaybe> maybe{};
+    constexpr std::integral_constant<int, kAlways> masked{};
+    auto weights = [&](auto mask, int t, f32x16_t &S, uint4 (&P)[2], const float (&a)[2]) __attribute__((always_inline)) {
         const int tb = t * kTile;
-        if constexpr (!decltype(fast)::value) {
-            if (tb + kTile - 1 > wave_min_pos) {                 // tokens after the column's position
+        if (decltype(mask)::value == kAlways || (decltype(mask)::value == kMaybe && tb + kTile - 1 > wave_min_pos)) {
 #pragma unroll
-                for (int cb = 0; cb < kPrefillBlocks; ++cb)
-#pragma unroll
-                    for (int r = 0; r < 8; ++r)
-                        if (tb + slot_token(j, r) > pos[cb]) S[cb][r >> 2][r & 3] = -INFINITY;
-            }
+            for (int r = 0; r < 16; ++r)
+                if (tb + 8 * (r >> 2) + 4 * h + (r & 3) > pos) S[r] = -INFINITY;
         }
-        float psum[kPrefillBlocks];
-        auto form = [&](int cb) __attribute__((always_inline)) {
-            float pw[8];
+        float psum;
+        auto form = [&]() __attribute__((always_inline)) {
+            float pw[16];
 #pragma unroll
-            for (int r = 0; r < 8; ++r) pw[r] = fast_exp2(fmaf(S[cb][r >> 2][r & 3], KV8 ? a[r >> 2] : p.scale_log2, -m[cb]));
-            P[cb] = make_uint4(pack_f16x2(pw[0], pw[1]), pack_f16x2(pw[2], pw[3]), pack_f16x2(pw[4], pw[5]),
-                               pack_f16x2(pw[6], pw[7]));
-            psum[cb] = sum_f16x2(P[cb].w, sum_f16x2(P[cb].z, sum_f16x2(P[cb].y, sum_f16x2(P[cb].x, 0.f))));
+            for (int r = 0; r < 16; ++r) pw[r] = fast_exp2(fmaf(S[r], KV8 ? a[r >> 3] : p.scale_log2, -m));
+            float s2[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                P[i] = make_uint4(pack_f16x2(pw[8 * i], pw[8 * i + 1]), pack_f16x2(pw[8 * i + 2], pw[8 * i + 3]),
+                                  pack_f16x2(pw[8 * i + 4], pw[8 * i + 5]), pack_f16x2(pw[8 * i + 6], pw[8 * i + 7]));
+                s2[i] = sum_f16x2(P[i].w, sum_f16x2(P[i].z, sum_f16x2(P[i].y, sum_f16x2(P[i].x, i ? s2[0] : 0.f))));
+            }
+            psum = s2[1];
         };
-        bool over = false;
+        form();
+        if (__any(!(psum < kPrefillSumLimit))) {                 // also for an infinite or undefined sum
+            float t0 = fmaxf(S[0], S[1]), t1 = fmaxf(S[8], S[9]);
 #pragma unroll
-        for (int cb = 0; cb < kPrefillBlocks; ++cb) {
-            form(cb);
-            over |= !(psum[cb] < kPrefillSumLimit);              // also true for an infinite or undefined sum
+            for (int r = 2; r < 8; ++r) { t0 = fmaxf(t0, S[r]); t1 = fmaxf(t1, S[8 + r]); }
+            // the largest scaled score of the tile, in log2 units (scales are positive)
+            float tmax = KV8 ? fmaxf(t0 * a[0], t1 * a[1]) : fmaxf(t0, t1) * p.scale_log2;
+            tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
+            // a column whose tokens are all masked so far keeps a finite stand-in: exp2 then sees -inf - finite
+            const float mn = fmaxf(fmaxf(m, tmax - kPrefillBias), -1e30f);
+            const float alpha = fast_exp2(m - mn);       // 0 while m is still -inf
+            l *= alpha;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] *= alpha;
+            m = mn;
+            form();
         }
-        if (__any(over)) {
-#pragma unroll
-            for (int cb = 0; cb < kPrefillBlocks; ++cb) {
-                const float t0 = fmaxf(fmaxf(S[cb][0][0], S[cb][0][1]), fmaxf(S[cb][0][2], S[cb][0][3]));
-                const float t1 = fmaxf(fmaxf(S[cb][1][0], S[cb][1][1]), fmaxf(S[cb][1][2], S[cb][1][3]));
-                // the largest scaled score of the tile, in log2 units (scales are positive)
-                float tmax = KV8 ? fmaxf(t0 * a[0], t1 * a[1]) : fmaxf(t0, t1) * p.scale_log2;
-                tmax = fmaxf(tmax, __shfl_xor(tmax, 16));
-                tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
-                // a column whose tokens are all masked so far keeps a finite stand-in: exp2 then sees -inf - finite
-                const float mn = fmaxf(fmaxf(m[cb], tmax - kPrefillBias), -1e30f);
-                const float alpha = fast_exp2(m[cb] - mn);       // 0 while m is still -inf
-                l[cb] *= alpha;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) acc[cb][e] *= alpha;
-                m[cb] = mn;
-                form(cb);
-            }
-        }
-#pragma unroll
-        for (int cb = 0; cb < kPrefillBlocks; ++cb) l[cb] += psum[cb];
+        l += psum;
     };
-    // O^T += V^T P^T.  The V^T operands, shared by the column blocks, come transposed out of shared memory: in a
-    // transposing 8-byte read the 16 lanes of a group each name four consecutive 16-bit values (lane 4k + q: dims
-    // 4q .. 4q+3 of token k of the group's four tokens) and lane i receives value i of each token, i.e. one output dim
-    // for four tokens.  Two reads (tokens 4j .. 4j+3 and 16+4j .. 16+4j+3, exactly the tokens whose weights this lane
-    // group holds) make the operand of one 16-dim block of output rows.
-    auto pv = [&](const char *vs, const uint4 (&P)[kPrefillBlocks]) __attribute__((always_inline)) {
-        const char *v_lo = vs + (4 * j + (col >> 2)) * kPrefillVRowBytes + (col & 3) * 8;
-        const char *v_hi = v_lo + 16 * kPrefillVRowBytes;
+    // O^T += V^T P^T.  The V^T operands come transposed out of shared memory: in a transposing 8-byte read the 16 lanes of a
+    // group each name four consecutive 16-bit values (lane 4k + q: dims 4q .. 4q+3 of token k of the group's four tokens) and
+    // lane i receives value i of each token, i.e. one output dim for four tokens.  Two reads (tokens 4h .. 4h+3 and
+    // 8+4h .. 8+4h+3 of 16, exactly the tokens whose weights this half holds) make the operand of 16 tokens and 32 dims.
+    auto pv = [&](const char *vs, const uint4 (&P)[2]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int eb = 0; eb < 8; ++eb) {
-            const uint2 a0 = lds_read_tr16_b64(v_lo + eb * 32);
-            const uint2 a1 = lds_read_tr16_b64(v_hi + eb * 32);
-            const uint4 A = make_uint4(a0.x, a0.y, a1.x, a1.y);
+        for (int e = 0; e < 4; ++e)
 #pragma unroll
-            for (int cb = 0; cb < kPrefillBlocks; ++cb) acc[cb][eb] = mfma_f16(A, P[cb], acc[cb][eb]);
-        }
+            for (int i = 0; i < 2; ++i) {
+                const uint2 a0 = lds_read_tr16_b64(vs + v_off + (16 * i) * kVRow + e * 64);
+                const uint2 a1 = lds_read_tr16_b64(vs + v_off + (16 * i + 8) * kVRow + e * 64);
+                acc[e] = mfma32_f16(make_uint4(a0.x, a0.y, a1.x, a1.y), P[i], acc[e]);
+            }
     };
     // ---- the pipeline.  Phase t multiplies the weights of tile t-1 into the accumulators and forms the scores of
     // tile t+1 on the matrix cores while the vector ALUs turn the scores of tile t into weights; the three are
     // independent, so one wave keeps both units busy.  A step is the two phases of an (even, odd) pair of tiles and
     // ends with one barrier: during step s the workgroup reads K of step s (tiles 2s, 2s+1) and V of step s-1 from
-    // shared memory and stages K of step s+1 and V of step s.  Steps in which every tile touched lies wholly before
-    // all of the wave's positions run without the per-tile conditions (`fast`).
-    f32x4_t Se[kPrefillBlocks][2], So[kPrefillBlocks][2];        // scores of the even / odd tile in flight
-    uint4 Pe[kPrefillBlocks], Po[kPrefillBlocks];                // weights of the even / odd tile in flight
+    // shared memory and stages K of step s+1 and V of step s.
+    f32x16_t Se, So;                                             // scores of the even / odd tile in flight
+    uint4 Pe[2], Po[2];                                          // weights of the even / odd tile in flight
     float ae[2] = {0.f, 0.f}, ao[2] = {0.f, 0.f};                // 8-bit cache: their scores' multipliers per 16-token half
     const float *k_scale = KV8 ? p.k_scale + kvh : nullptr, *v_scale = KV8 ? p.v_scale + kvh : nullptr;
+    auto fetch = [&](auto inside, int s) __attribute__((always_inline)) {        // in flight while step s is computed
+        fetch_rows(inside, vbase, v_scale, s, pg_v, sv_, svs);
+        fetch_rows(inside, kbase, k_scale, s + 1, pg_k, sk, sks);
 #pragma unroll
-    for (int cb = 0; cb < kPrefillBlocks; ++cb) Pe[cb] = Po[cb] = make_uint4(0, 0, 0, 0);
-    auto step_body = [&](auto fast, int s) __attribute__((always_inline)) {
-        constexpr bool kFast = decltype(fast)::value;
-        const int buf = s & 1;
-        fetch_rows(fast, vbase, v_scale, s, pg_v, sv_, svs);     // in flight while this step is computed
-        fetch_rows(fast, kbase, k_scale, s + 1, pg_k, sk, sks);
-        pg_v[0] = pg_k[0]; pg_v[1] = pg_k[1];
+        for (int i = 0; i < NP; ++i) pg_v[i] = pg_k[i];
         lookup(s + 2);
-        // phase 2s-1: P.V of tile 2s-2, weights of tile 2s-1, scores of tile 2s
-        if (kFast || tile_active(2 * s - 2)) pv(smem[buf ^ 1][0][1], Pe);
-        if (kFast || tile_active(2 * s)) scores(smem[buf][0][0], Se, kscale_lds[buf][0], ae);
-        if (kFast || tile_active(2 * s - 1)) weights(fast, 2 * s - 1, So, Po, ao);
-        // phase 2s: P.V of tile 2s-1, weights of tile 2s, scores of tile 2s+1
-        if (kFast || tile_active(2 * s - 1)) pv(smem[buf ^ 1][1][1], Po);
-        if (kFast || tile_active(2 * s + 1)) scores(smem[buf][1][0], So, kscale_lds[buf][1], ao);
-        if (kFast || s < s_end) {                                // ahead of the weights: one block with the MFMAs above
-            stage_k(buf ^ 1);
-            stage_v(buf);
-        }
-        if (kFast || tile_active(2 * s)) weights(fast, 2 * s, Se, Pe, ae);
-        if (kFast || s < s_end) lds_barrier();
     };
-    // last step whose tiles 2s-2 .. 2s+1 are all wholly visible to every live column of the wave and all this
-    // workgroup's, and whose fetches (V of step s, K of step s+1) lie wholly inside the context
-    const int fast_last = wave_max_pos < 0 ? -1 : min(min(((wave_min_pos - (kTile - 1)) / kTile - 1) / 2, L / (2 * kTile) - 2),
-                                                      s_end - 1);
-
-    {
-        lookup(s_begin);
-        fetch_rows(std::false_type{}, kbase, k_scale, s_begin, pg_k, sk, sks);
-        pg_v[0] = pg_k[0]; pg_v[1] = pg_k[1];
-        lookup(s_begin + 1);
-        stage_k(s_begin & 1);
+    auto stage = [&](int s) __attribute__((always_inline)) { stage_k((s & 1) ^ 1); stage_v(s & 1); };
+    // A step all of whose tiles 2s-2 .. 2s+1 hold tokens that the wave sees.  `mask` none: they lie wholly before all of its
+    // positions, and what is fetched lies wholly inside the context.
+    auto full_step = [&](auto mask, int s) __attribute__((always_inline)) {
+        const int buf = s & 1;
+        fetch(std::integral_constant<bool, decltype(mask)::value == kNone>{}, s);
+        // phase 2s-1: P.V of tile 2s-2, weights of tile 2s-1, scores of tile 2s
+        pv(v_lds[buf ^ 1], Pe);
+        scores(k_lds[buf], Se, kscale_lds[buf], ae);
+        weights(mask, 2 * s - 1, So, Po, ao);
+        // phase 2s: P.V of tile 2s-1, weights of tile 2s, scores of tile 2s+1
+        pv(v_lds[buf ^ 1] + kTile * kVRow, Po);
+        scores(k_lds[buf] + kTile * kKRow, So, kscale_lds[buf] + 2, ao);
+        stage(s);                                                // ahead of the weights: one block with the MFMAs above
+        weights(mask, 2 * s, Se, Pe, ae);
         lds_barrier();
-        for (int s = s_begin; s <= s_end; ++s) {
-            if (s > s_begin && s <= fast_last) step_body(std::true_type{}, s);
-            else step_body(std::false_type{}, s);
+    };
+    const int fast_last = min(min(((wave_min_pos - (kTile - 1)) / kTile - 1) / 2, L / kStep - 2), s_end - 1);
+    const int last_tile = min(wave_max_pos >> kLog2Tile, 2 * s_end - 1);     // the last one the wave sees any of (-1: no live column)
+    lookup(s_begin);
+    fetch_rows(std::false_type{}, kbase, k_scale, s_begin, pg_k, sk, sks);
+#pragma unroll
+    for (int i = 0; i < NP; ++i) pg_v[i] = pg_k[i];
+    lookup(s_begin + 1);
+    stage_k(s_begin & 1);
+    lds_barrier();
+    // Every wave passes s_end - s_begin more barriers, one at the end of each step before s_end, wherever its own tiles end.
+    int s = s_begin;
+    if (last_tile >= 2 * s) {
+        fetch(std::false_type{}, s);                             // the first step: nothing to multiply yet
+        scores(k_lds[s & 1], Se, kscale_lds[s & 1], ae);
+        if (last_tile > 2 * s) scores(k_lds[s & 1] + kTile * kKRow, So, kscale_lds[s & 1] + 2, ao);
+        stage(s);
+        weights(maybe, 2 * s, Se, Pe, ae);
+        lds_barrier();
+        for (++s; s <= fast_last; ++s) full_step(before, s);
+        for (; last_tile > 2 * s; ++s) full_step(masked, s);
+        // here the last tile is 2s-1 or 2s, or 2s-2 if the first step held it; what is left: an even tile's weights to
+        // multiply, and the odd one's before them
+        bool even = true;
+        if (last_tile >= 2 * s - 1) {
+            even = last_tile == 2 * s;
+            if (s < s_end) fetch(std::false_type{}, s);
+            pv(v_lds[(s & 1) ^ 1], Pe);
+            if (even) scores(k_lds[s & 1], Se, kscale_lds[s & 1], ae);
+            weights(masked, 2 * s - 1, So, Po, ao);
+            pv(v_lds[(s & 1) ^ 1] + kTile * kVRow, Po);
+            if (s < s_end) stage(s);
+            if (even) weights(masked, 2 * s, Se, Pe, ae);
+            if (s < s_end) lds_barrier();
+            ++s;
+        }
+        if (even) {
+            if (s < s_end) fetch(std::false_type{}, s);
+            pv(v_lds[(s & 1) ^ 1], Pe);
+            if (s < s_end) { stage(s); lds_barrier(); }
+            ++s;
         }
     }
+    for (; s < s_end; ++s) { fetch(std::false_type{}, s); stage(s); lds_barrier(); }     // for the other waves
 
-    // ---- normalise and store: a lane holds, for each of its columns, dims 16 eb + 4j .. + 3 of every 16-dim block eb
+    // ---- normalise and store
+    const float lsum = l + __shfl_xor(l, 32);                    // the two halves hold disjoint tokens
+    if (!live) return;
+    if (ns_eff > 1) {                                            // a piece for the merge: unnormalised, with (m, l)
+        const size_t pi = ((((size_t)b * p.max_q_len + qi) * p.Hq + head0 + g) * NS + split);
+        float *po = p.part_o + pi * D;
 #pragma unroll
-    for (int cb = 0; cb < kPrefillBlocks; ++cb) {
-        float lsum = l[cb];
-        lsum += __shfl_xor(lsum, 16);                            // the four lane groups hold disjoint tokens
-        lsum += __shfl_xor(lsum, 32);
-        if (pos[cb] < 0) continue;
-        const int c = wave * kPrefillCols + cb * 16 + col;
-        const int tl = c / G, g = c - tl * G;
-        if (ns_eff > 1) {                                        // a piece for the merge: unnormalised, with (m, l)
-            const size_t pi = ((((size_t)b * p.max_q_len + q0 + tl) * p.Hq + head0 + g) * NS + split);
-            float *po = p.part_o + pi * D;
+        for (int e = 0; e < 4; ++e)
 #pragma unroll
-            for (int eb = 0; eb < 8; ++eb)
-                *reinterpret_cast<float4 *>(po + 16 * eb + 4 * j) = make_float4(acc[cb][eb][0], acc[cb][eb][1], acc[cb][eb][2], acc[cb][eb][3]);
-            if (j == 0) p.part_ml[pi] = make_float2(m[cb], lsum);
-            continue;
-        }
-        const size_t row = ((size_t)(q_row0 + q0 + tl) * p.Hq + head0 + g) * D;
-        const float inv = 1.f / lsum;                            // every live column saw its own position: lsum > 0
-#pragma unroll
-        for (int eb = 0; eb < 8; ++eb) {                         // acc[cb][eb][i] = O^T[dim 16 eb + 4 j + i][column]
-            const float o0 = acc[cb][eb][0] * inv, o1 = acc[cb][eb][1] * inv, o2 = acc[cb][eb][2] * inv, o3 = acc[cb][eb][3] * inv;
-            const size_t at = row + 16 * eb + 4 * j;
-            if (p.out_bf16) {
-                uint2 pk;
-                pk.x = (uint32_t)float_to_bf16_rne(o0) | ((uint32_t)float_to_bf16_rne(o1) << 16);
-                pk.y = (uint32_t)float_to_bf16_rne(o2) | ((uint32_t)float_to_bf16_rne(o3) << 16);
-                *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(p.out) + at) = pk;
-            } else {
-                *reinterpret_cast<float4 *>(reinterpret_cast<float *>(p.out) + at) = make_float4(o0, o1, o2, o3);
-            }
-        }
+            for (int i = 0; i < 4; ++i)
+                *reinterpret_cast<float4 *>(po + 32 * e + 8 * i + 4 * h) = make_float4(acc[e][4 * i], acc[e][4 * i + 1], acc[e][4 * i + 2], acc[e][4 * i + 3]);
+        if (h == 0) p.part_ml[pi] = make_float2(m, lsum);
+        return;
     }
+    const size_t row = ((size_t)(q_row0 + qi) * p.Hq + head0 + g) * D;
+    const float inv = 1.f / lsum;                                // every live column saw its own position: lsum > 0
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            store_out4(p, row + 32 * e + 8 * i + 4 * h, make_float4(acc[e][4 * i] * inv, acc[e][4 * i + 1] * inv, acc[e][4 * i + 2] * inv, acc[e][4 * i + 3] * inv));
 }
 
 // order[r] = the request with the r-th longest context (ties by index): one workgroup, thread t ranks request t.
@@ -478,9 +482,10 @@ __global__ __launch_bounds__(kThreads) void prefill_merge_kernel(PrefillParams p
     const int n_q = min(p.q_lens[b], L);
     const int n_live = min(n_q, p.max_q_len);
     if (qi >= n_live) return;
-    // the split count of the row's query block, as the attention kernel derived it
-    const int QB = prefill_tokens_per_block(p.G, D);
-    const int wg_last = min(n_live, ((int)qi / QB + 1) * QB) - 1;
+    // the split count of the row's workgroup, as the attention kernel derived it
+    constexpr int kColumns = prefill_columns(D);
+    const int c = (int)qi * p.G + head % p.G;
+    const int wg_last = prefill_last_token(c - c % kColumns, kColumns, p.G, n_live);
     const int n_tiles = (L - n_q + wg_last) / kTile + 1;
     const int ns_eff = prefill_effective_splits(p.num_splits, (n_tiles + 1) >> 1, p.min_split_steps);
     if (ns_eff == 1) return;                                     // written by the attention kernel itself

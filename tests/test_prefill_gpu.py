@@ -73,6 +73,21 @@ def test_chunks_of_many_shapes(G, Hkv, ps):
     assert np.max(np.abs(got[ch.q_offsets[0]] - np.repeat(v0, G, axis=0))) <= 1e-5
 
 
+# Contexts that end in every place of a 64-token step (the even or odd tile, its first or last token), the first step among
+# them, and chunks of one token up to several workgroups of 256 (token, head) columns, cut inside a token's heads.
+EDGE_LENS = [1, 31, 32, 33, 63, 64, 65, 96, 97, 128, 129, 160, 161, 193, 0, 320, 351, 417, 500]
+EDGE_Q_LENS = [1, 31, 1, 33, 2, 64, 36, 37, 97, 3, 38, 73, 74, 110, 0, 1, 147, 52, 171]
+
+
+@pytest.mark.parametrize("G,Hkv,ps", [(3, 2, 32), (5, 1, 16), (7, 2, 16), (16, 1, 32)])
+def test_columns_cut_inside_a_token_and_contexts_that_end_anywhere(G, Hkv, ps):
+    wl = W.build("edge", 720 + G, EDGE_LENS, Hq=G * Hkv, Hkv=Hkv, D=128, ps=ps, dtype=W.BF16, pool_factor=1.3)
+    ch = W.add_chunk(wl, EDGE_Q_LENS, 721, in_cache=True, gap=1)
+    check_chunk(wl, ch, label="unsplit", tuning={omni.OMNI_TUNE_PREFILL_SPLITS: 1})
+    check_chunk(wl, ch, label="split", split_workspace=True,
+                tuning={omni.OMNI_TUNE_PREFILL_SPLITS: 5, omni.OMNI_TUNE_PREFILL_MIN_SPLIT: 64})
+
+
 @pytest.mark.parametrize("dtype,D,G,Hkv,ps", [(W.F32, 64, 2, 2, 16), (W.F32, 64, 7, 1, 32), (W.F32, 128, 4, 2, 16),
                                               (W.BF16, 64, 5, 2, 16), (W.BF16, 64, 16, 1, 32)])
 def test_chunks_on_every_other_dtype_and_head_size(dtype, D, G, Hkv, ps):
