@@ -44,15 +44,15 @@ __global__ __launch_bounds__(kPrefillExactThreads, 3) void prefill_exact_kernel(
     __shared__ __align__(16) char k_lds[2][kStep * kKRow];
     __shared__ __align__(16) char v_lds[2][kStep * kVRow];
 
-    const int b = p.order ? p.order[blockIdx.z] : (int)blockIdx.z, kvh = blockIdx.y;
+    const PrefillPlace at = prefill_place(p);
+    const int b = at.b, kvh = at.kvh, L = at.L;
     const int G = p.G, head0 = kvh * G;
-    const int L = p.context_lens[b];
     const int n_q = min(p.q_lens[b], L);
     const int n_live = min(n_q, p.max_q_len);                    // a chunk longer than the grid's bound is cut off there
     constexpr int kColumns = prefill_columns(D);
     const int NS = p.num_splits;
-    const int split = NS > 1 ? (int)blockIdx.x % NS : 0;
-    const int c0 = (NS > 1 ? (int)blockIdx.x / NS : (int)blockIdx.x) * kColumns;     // first column of this workgroup
+    const int split = NS > 1 ? at.block % NS : 0;
+    const int c0 = (NS > 1 ? at.block / NS : at.block) * kColumns;     // first column of this workgroup
     if (n_live <= 0 || c0 >= n_live * G) return;
     const int pos0 = L - n_q;                                    // position of the chunk's first token
     const int wg_last = prefill_last_token(c0, kColumns, G, n_live);

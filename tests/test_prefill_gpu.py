@@ -88,6 +88,15 @@ def test_columns_cut_inside_a_token_and_contexts_that_end_anywhere(G, Hkv, ps):
                 tuning={omni.OMNI_TUNE_PREFILL_SPLITS: 5, omni.OMNI_TUNE_PREFILL_MIN_SPLIT: 64})
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("Hkv,G,q_len", [(1, 16, 128), (2, 16, 64), (4, 16, 50), (8, 4, 30), (8, 4, 200), (16, 2, 100), (24, 1, 300), (6, 4, 200)])
+def test_every_column_runs_once_however_workgroups_are_dealt_to_the_dies(Hkv, G, q_len, D):
+    """Numbers of KV heads and of workgroups per head that are and are not arranged by compute die, chunks of several lengths."""
+    wl = W.build("dies", 730 + Hkv, [q_len, q_len + 40, 3 * q_len // 4, 17], Hq=G * Hkv, Hkv=Hkv, D=D, ps=16, dtype=W.BF16)
+    ch = W.add_chunk(wl, [q_len, q_len // 2, 3 * q_len // 4, 1], 731, in_cache=True, gap=1)
+    check_chunk(wl, ch, tuning={omni.OMNI_TUNE_PREFILL_SPLITS: 1})
+
+
 @pytest.mark.parametrize("dtype,D,G,Hkv,ps", [(W.F32, 64, 2, 2, 16), (W.F32, 64, 7, 1, 32), (W.F32, 128, 4, 2, 16),
                                               (W.BF16, 64, 5, 2, 16), (W.BF16, 64, 16, 1, 32)])
 def test_chunks_on_every_other_dtype_and_head_size(dtype, D, G, Hkv, ps):
