@@ -157,7 +157,10 @@ __device__ __forceinline__ PrefillPlace prefill_place(const PrefillParams &p) {
     if (p.num_splits == 1 && gx * heads % kDies == 0) {
         const int u = blockIdx.x + gx * blockIdx.y, die = u % kDies, i = u / kDies;
         if (heads % kDies == 0) { at.kvh = die + kDies * (i / gx); at.block = i % gx; }
-        else if (kDies % heads == 0) { at.kvh = die % heads; at.block = die / heads + kDies / heads * i; }
+        else if (kDies % heads == 0) {                           // (short chunks lack the last blocks: not always on one die)
+            const int share = kDies / heads;
+            at.kvh = die % heads; at.block = (die / heads + blockIdx.z) % share + share * i;
+        }
     }
     return at;
 }
