@@ -100,8 +100,8 @@ typedef enum {
     OMNI_TUNE_QUERY_TOKENS = 6,     /* T >= 1 (default 1): omni_paged_decode_attn and omni_paged_decode_attn_fp8 take T query
                                        tokens per request, see there.  T > 1: bf16 with head_dim 128 and 8-bit caches, not
                                        under OMNI_TUNE_KERNEL = 1, else UNSUPPORTED */
-    OMNI_TUNE_PREFILL_SORT = 7      /* omni_paged_prefill_attn, matrix-core path with a registered workspace and more than 256
-                                       workgroups: 1 (default) = requests are taken longest context first (one more tiny
+    OMNI_TUNE_PREFILL_SORT = 7      /* omni_paged_prefill_attn, matrix-core path with a registered workspace and more
+                                       workgroups than run at once: 1 (default) = requests are taken longest context first (one more tiny
                                        launch ranks them), 0 = in batch order */
 } omni_tune_key_t;
 
@@ -295,14 +295,14 @@ omni_status_t omni_kv_unpack(omni_handle_t h, const void *k_dense, const void *v
  * configurations (and bf16 ones under OMNI_TUNE_KERNEL = 1, and head_dim 64 with a scale that is not positive) run a plain
  * vector-ALU kernel in fp32 arithmetic.  An 8-bit cache: OMNI_ERR_UNSUPPORTED here, see omni_paged_prefill_attn_fp8.
  * One launch and no workspace, unless the call would leave most of the chip idle (few requests, short chunks: a
- * workgroup owns floor(256 / group size) query tokens of one request and KV head, half as many with head_dim 64) and the registered workspace holds
- * at least omni_prefill_workspace_bytes(max_q_len): then the matrix-core path lets up to 16 workgroups share a
+ * workgroup owns 256 (query token, head) pairs of one request and KV head; 128 with head_dim 64, and where there are few
+ * of them) and the registered workspace holds at least omni_prefill_workspace_bytes(max_q_len): then the matrix-core path lets up to 16 workgroups share a
  * query block's context in equal runs of 64-token steps (as many as the context gives OMNI_TUNE_PREFILL_MIN_SPLIT
  * tokens each), and a second launch merges their pieces (log-sum-exp, in order of position: the same exact
  * re-association as in decode).  How a block is shared depends on the handle, its tuning, max_q_len and the lengths
  * only, so the result is bit-identical from run to run.  With a registered workspace (head_dim 64: of at least
- * omni_prefill_workspace_bytes(max_q_len)) and more than 256 workgroups a
- * one-workgroup launch first ranks the requests by context length, and the kernel takes them longest first (the order
+ * omni_prefill_workspace_bytes(max_q_len)) and more workgroups than compute units (than twice as many, of 128 pairs with
+ * 128-dim heads) a one-workgroup launch first ranks the requests by context length, and the kernel takes them longest first (the order
  * changes when a workgroup runs, not what it computes).
  * Errors: NULL, SHAPE (max_q_len <= 0, scale <= 0 with 128-dim heads on the matrix-core path, alignment), UNSUPPORTED, HIP.
  */

@@ -73,31 +73,52 @@ struct omni_handle_s {
     // The multi-token call runs a matrix-core kernel (else the vector-ALU kernel, which every format can be sent to but
     // the 8-bit one).
     bool prefill_mfma() const { return (d.kv_dtype == OMNI_BF16 && tune_kernel != 1) || d.kv_dtype == OMNI_FP8_E4M3; }
-    // Context split of the multi-token-query kernel for chunks of up to max_q_len tokens: where the query blocks fill
-    // at most half of the compute units, as many workgroups per (query block, KV head, request) as it takes to fill
-    // them, at most 16 and no more than the longest context the handle allows can use.  1 = no split.
-    unsigned prefill_blocks(int max_q_len) const {               // per (request, KV head)
-        const int columns = prefill_columns(d.head_dim);
+    // How the matrix-core kernels of the multi-token call are launched for chunks of up to max_q_len tokens: waves per
+    // workgroup (32 (query token, head) columns each) and into how many parts the context is split.  Decided from sizes the
+    // handle knows; how many parts a workgroup's context really has is decided on the device.
+    struct PrefillShape { int waves, splits; };
+    unsigned prefill_blocks(int max_q_len, int waves) const {    // workgroups per (request, KV head), unsplit
+        const int columns = prefill_columns(waves);
         return (unsigned)(((long long)max_q_len * G + columns - 1) / columns);
     }
-    long long prefill_workgroups(int max_q_len) const {          // of the matrix-core kernel, unsplit
-        return (long long)prefill_blocks(max_q_len) * d.num_kv_heads * d.batch;
-    }
-    int prefill_splits(int max_q_len) const {
-        if (!prefill_mfma() || tune_prefill_splits == 1) return 1;
-        const long long wgs = prefill_workgroups(max_q_len);
+    long long prefill_workgroups(int max_q_len, int waves) const { return (long long)prefill_blocks(max_q_len, waves) * d.num_kv_heads * d.batch; }
+    // A split fills `slots` places for workgroups where the unsplit launch fills at most half of them: as many parts as it
+    // takes, at most 16 and no more than the longest context the handle allows can use.  1 = no split.
+    int prefill_splits(long long workgroups, int slots) const {
+        if (tune_prefill_splits == 1) return 1;
         const int by_ctx = (max_ctx + 2 * kTile - 1) / (2 * kTile) / (tune_prefill_min_split / (2 * kTile));
-        int ns = tune_prefill_splits > 1 ? tune_prefill_splits : (wgs > 128 ? 1 : (int)(256 / wgs));
+        int ns = tune_prefill_splits > 1 ? tune_prefill_splits : (workgroups > slots / 2 ? 1 : (int)(slots / workgroups));
         if (ns > 16) ns = 16;
         if (ns > by_ctx) ns = by_ctx;            // no context the handle allows would use more
         return ns < 1 ? 1 : ns;
+    }
+    // 128-dim heads: eight waves per workgroup, one workgroup per compute unit, stage a tile for 256 columns; four waves, two
+    // workgroups, stage it for 128.  Measured over group sizes 1, 7 and 16, 1 .. 64 requests, chunks of 16 .. 1024 tokens and
+    // contexts of 256 .. 16384 (8 waves / 4 waves), four waves are taken
+    //  - where eight would leave half of the compute units without a workgroup: twice as many share the columns (one request,
+    //    28/4 heads, 64 tokens of 2048: 22.4 / 18.9 us; 16 requests of 256: 16.5 / 14.2 us; but 64 tokens of 2048 for four
+    //    requests, where eight waves fill the units with a split, 30.2 / 31.2 us);
+    //  - where no chunk has more than 128 columns, of which eight waves would compute on four at most, if two workgroups per
+    //    unit have something to do: more than 256 of them (64 requests, 8/8 heads, 16 tokens of 2048: 111 / 87 us; 28/4 heads,
+    //    256 of them, 45.4 / 52.2 us), or contexts long enough for more parts of 1024 tokens and over (16 requests, 28/4
+    //    heads, 16 tokens of 16384: 134 / 110 us; but 2048: 24.0 / 29.6 us).
+    PrefillShape prefill_shape(int max_q_len) const {
+        if (!prefill_mfma()) return {kWaves, 1};
+        if (d.head_dim == 64) return {kPrefillExactWaves, prefill_splits(prefill_workgroups(max_q_len, kPrefillExactWaves), 256)};
+        const long long wg8 = prefill_workgroups(max_q_len, 8), wg4 = prefill_workgroups(max_q_len, 4);
+        const int ns8 = prefill_splits(wg8, 256);
+        if (wg4 > wg8) return wg8 * ns8 <= 128 ? PrefillShape{4, prefill_splits(wg4, 256)} : PrefillShape{8, ns8};
+        const int ns4 = prefill_splits(wg4, 512);
+        return wg4 > 256 || (ns4 > ns8 && max_ctx / ns4 >= 1024) ? PrefillShape{4, ns4} : PrefillShape{8, ns8};
     }
     static size_t prefill_ml_bytes(const omni_attn_desc_t &d, int max_q_len, int ns) {
         return align256((size_t)d.batch * max_q_len * d.num_q_heads * ns * sizeof(float2));
     }
     // The requests are ranked by context length where the call has more than one round of workgroups.
     bool prefill_ranks(int max_q_len) const {
-        return prefill_mfma() && tune_prefill_sort != 0 && d.batch > 1 && d.batch <= kPrefillOrderMax && prefill_workgroups(max_q_len) > 256;
+        if (!prefill_mfma() || tune_prefill_sort == 0 || d.batch <= 1 || d.batch > kPrefillOrderMax) return false;
+        const int waves = prefill_shape(max_q_len).waves;
+        return prefill_workgroups(max_q_len, waves) > (d.head_dim == 128 && waves == 4 ? 512 : 256);
     }
     size_t prefill_order_bytes(int max_q_len) const { return prefill_ranks(max_q_len) ? align256((size_t)d.batch * sizeof(int32_t)) : 0; }
     // Where the multi-token call's part of the workspace begins.  With 64-dim heads behind the decode calls' part: a program
@@ -105,7 +126,7 @@ struct omni_handle_s {
     // the chunks came to use the workspace.  With 128-dim heads the two have always shared it.
     size_t prefill_ws_begin() const { return d.head_dim == 64 ? ws_bytes : 0; }
     size_t prefill_ws_bytes(int max_q_len) const {
-        const int ns = prefill_splits(max_q_len);
+        const int ns = prefill_shape(max_q_len).splits;
         const size_t order = d.head_dim == 64 ? prefill_order_bytes(max_q_len) : 0;
         if (ns <= 1) return order ? prefill_ws_begin() + order : 0;
         return prefill_ws_begin() + order + prefill_ml_bytes(d, max_q_len, ns) +
@@ -299,6 +320,17 @@ void launch_valu(const AttnParams &p, dim3 grid, size_t dyn, hipStream_t s) {
     else if (p.G <= 4) decode_valu_kernel<T, D, 4><<<grid, kThreads, dyn, s>>>(p);
     else if (p.G <= 8) decode_valu_kernel<T, D, 8><<<grid, kThreads, dyn, s>>>(p);
     else decode_valu_kernel<T, D, 16><<<grid, kThreads, dyn, s>>>(p);
+}
+
+template <int W>
+void launch_prefill_mfma(const PrefillParams &p, dim3 grid, bool ps16, bool fp8, hipStream_t s) {
+    if (fp8) {
+        if (ps16) prefill_mfma_kernel<16, true, W><<<grid, 64 * W, 0, s>>>(p);
+        else prefill_mfma_kernel<32, true, W><<<grid, 64 * W, 0, s>>>(p);
+    } else {
+        if (ps16) prefill_mfma_kernel<16, false, W><<<grid, 64 * W, 0, s>>>(p);
+        else prefill_mfma_kernel<32, false, W><<<grid, 64 * W, 0, s>>>(p);
+    }
 }
 
 // The variant of the matrix-core kernel a handle launches: page size, cache format, K staging, query tokens per request.
@@ -737,16 +769,17 @@ static omni_status_t launch_prefill(omni_handle_t h, const void *q, const void *
     size_t order_bytes = mfma && h->ws ? h->prefill_order_bytes(max_q_len) : 0;
     if (d64 && h->ws_given < h->prefill_ws_begin() + order_bytes) order_bytes = 0;
     const bool sorted = order_bytes > 0;
-    int ns = mfma ? h->prefill_splits(max_q_len) : 1;
+    const omni_handle_s::PrefillShape shape = h->prefill_shape(max_q_len);
+    int ns = mfma ? shape.splits : 1;
     if (ns > 1 && (!h->ws || h->ws_given < h->prefill_ws_bytes(max_q_len) + (d64 ? 0 : order_bytes))) ns = 1;
     char *ws = reinterpret_cast<char *>(h->ws) + (h->ws ? h->prefill_ws_begin() : 0);
     p.order = sorted ? reinterpret_cast<const int32_t *>(ws) : nullptr;
     p.B = d.batch;
-    p.num_splits = ns; p.max_q_len = max_q_len;
+    p.num_splits = ns; p.max_q_len = max_q_len; p.columns = prefill_columns(shape.waves);
     p.min_split_steps = h->tune_prefill_min_split / (2 * kTile);
     p.part_ml = ns > 1 ? reinterpret_cast<float2 *>(ws + order_bytes) : nullptr;
     p.part_o = ns > 1 ? reinterpret_cast<float *>(ws + order_bytes + omni_handle_s::prefill_ml_bytes(d, max_q_len, ns)) : nullptr;
-    const unsigned blocks = mfma ? h->prefill_blocks(max_q_len) : (unsigned)(((long long)max_q_len + kWaves - 1) / kWaves);
+    const unsigned blocks = mfma ? h->prefill_blocks(max_q_len, shape.waves) : (unsigned)(((long long)max_q_len + kWaves - 1) / kWaves);
     const dim3 grid(blocks * (unsigned)ns, (unsigned)d.num_kv_heads, (unsigned)d.batch);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     (void)hipGetLastError();
@@ -755,15 +788,13 @@ static omni_status_t launch_prefill(omni_handle_t h, const void *q, const void *
         if (hipGetLastError() != hipSuccess) return OMNI_ERR_HIP;
     }
     if (mfma) {
-        if (fp8) {
-            if (d.page_size == 16) prefill_mfma_kernel<16, true><<<grid, kPrefillThreads, 0, s>>>(p);
-            else prefill_mfma_kernel<32, true><<<grid, kPrefillThreads, 0, s>>>(p);
-        } else if (d64) {
+        if (d64) {
             if (d.page_size == 16) prefill_exact_kernel<16><<<grid, kPrefillExactThreads, 0, s>>>(p);
             else prefill_exact_kernel<32><<<grid, kPrefillExactThreads, 0, s>>>(p);
+        } else if (shape.waves == 8) {
+            launch_prefill_mfma<8>(p, grid, d.page_size == 16, fp8, s);
         } else {
-            if (d.page_size == 16) prefill_mfma_kernel<16><<<grid, kPrefillThreads, 0, s>>>(p);
-            else prefill_mfma_kernel<32><<<grid, kPrefillThreads, 0, s>>>(p);
+            launch_prefill_mfma<4>(p, grid, d.page_size == 16, fp8, s);
         }
         if (ns > 1) {
             if (hipGetLastError() != hipSuccess) return OMNI_ERR_HIP;

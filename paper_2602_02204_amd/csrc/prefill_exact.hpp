@@ -29,7 +29,7 @@
 
 namespace omni {
 
-constexpr int kPrefillExactThreads = 2 * prefill_columns(64);      // 32 columns per wave
+constexpr int kPrefillExactWaves = 4, kPrefillExactThreads = 64 * kPrefillExactWaves;
 constexpr float kPrefillExactLimit = 256.f;                        // sum of a lane's 16 weights of a tile beyond which the reference moves
 
 template <int PS>
@@ -49,7 +49,7 @@ __global__ __launch_bounds__(kPrefillExactThreads, 3) void prefill_exact_kernel(
     const int G = p.G, head0 = kvh * G;
     const int n_q = min(p.q_lens[b], L);
     const int n_live = min(n_q, p.max_q_len);                    // a chunk longer than the grid's bound is cut off there
-    constexpr int kColumns = prefill_columns(D);
+    constexpr int kColumns = prefill_columns(kPrefillExactWaves);
     const int NS = p.num_splits;
     const int split = NS > 1 ? at.block % NS : 0;
     const int c0 = (NS > 1 ? at.block / NS : at.block) * kColumns;     // first column of this workgroup

@@ -3,9 +3,9 @@
 // tokens 0 .. p (causal inside the chunk).
 //
 // The (query token, query head of the group) pairs of a request's chunk and one KV head are its "columns", in token-major
-// order; a workgroup (8 waves, two per SIMD) owns 256 consecutive ones, wherever that cuts a token's heads (512 tokens of
-// 7 heads are 14 workgroups; whole tokens only would make them 15), a wave 32 of them = the columns of one 32x32x16 matrix
-// instruction.  Per 32-token tile:
+// order; a workgroup (8 waves, two per SIMD; 4 waves and two workgroups per compute unit where there are few columns) owns
+// 256 (128) consecutive ones, wherever that cuts a token's heads (512 tokens of 7 heads are 14 workgroups; whole tokens only
+// would make them 15), a wave 32 of them = the columns of one 32x32x16 matrix instruction.  Per 32-token tile:
 //   S^T = K Q^T     (A = K rows from shared memory, B = the wave's queries, held in registers for the whole kernel)
 //   O^T += V^T P^T  (A = V transposed, B = the softmax weights; both as fp16: V is converted once per workgroup on
 //                    its way into shared memory, exactly for 2^-14 <= |V| <= 65504, and fp16 weights carry 11
@@ -13,7 +13,7 @@
 // so every lane owns one column (the two halves of a wave hold its even and odd groups of four tokens): running reference,
 // sum and rescale never cross lanes on the common path.
 // What differs from decode is reuse: K/V tiles are fetched once per workgroup into shared memory (double buffered,
-// one barrier per 64 tokens) and feed 256 columns, and V^T comes out of shared memory through transposing reads.
+// one barrier per 64 tokens) and feed all its columns, and V^T comes out of shared memory through transposing reads.
 // That makes the path a dense contraction, not a stream.  The three pieces of a tile's work are software-pipelined
 // across tiles, so that a wave has matrix-core and vector-ALU instructions to issue side by side.
 // What bounds it: the clock the chip holds under this load (1.7 - 1.85 GHz of 2.4), at which the matrix cores are busy
@@ -31,8 +31,6 @@
 
 namespace omni {
 
-constexpr int kPrefillThreads = 512;                  // 8 waves = 2 per SIMD share one K/V tile in shared memory
-constexpr int kPrefillWaves = kPrefillThreads / 64;
 constexpr int kPrefillRowBytes = 256 + 16;            // a 256-byte K row plus padding: conflict-free 16-byte LDS reads
 constexpr int kPrefillVRowBytes = 256 + 64;           // V rows: conflict-free 8-byte transposing reads (4 rows x 64 B)
 constexpr float kPrefillBias = 6.f;                   // a moved reference sits this many log2 units below the maximum
@@ -112,6 +110,7 @@ struct PrefillParams {
     int num_splits;                   // 1: no split, results go straight to out
     int min_split_steps;              // fewest 64-token steps a split's share may have
     int max_q_len;
+    int columns;                      // (query token, head) pairs per workgroup
     float *part_o;                    // [B, max_q_len, Hq, num_splits, D]
     float2 *part_ml;                  // [B, max_q_len, Hq, num_splits]
     const int32_t *order;             // null, or [B]: the requests by descending context length (blockIdx.z -> request)
@@ -125,9 +124,9 @@ __device__ __forceinline__ int prefill_effective_splits(int num_splits, int n_st
     return max(1, min(num_splits, n_steps / min_split_steps));
 }
 
-// Columns of a workgroup: the (query token, head) pairs of a chunk and one KV head, in token-major order, are cut into runs
-// of this many, and those into runs of 32 for the waves.
-__host__ __device__ constexpr int prefill_columns(int D) { return D == 64 ? 128 : 32 * kPrefillWaves; }
+// The (query token, head) pairs of a chunk and one KV head, in token-major order, are cut into runs of 32 per wave of a
+// workgroup.
+constexpr int prefill_columns(int waves) { return 32 * waves; }
 // The chunk's last query token that the workgroup with first column c0 has a column of (n_live tokens are live).
 __host__ __device__ inline int prefill_last_token(int c0, int columns, int G, int n_live) {
     const int t = (c0 + columns - 1) / G;
@@ -169,15 +168,16 @@ __device__ __forceinline__ PrefillPlace prefill_place(const PrefillParams &p) {
 // (exact) and V times its page's scale to fp16 (one rounding, 2^-12 relative: the size of the weights' own rounding) on
 // the way into shared memory, so the products are the 16-bit ones; the K scale of each 16-token half of a tile joins
 // the softmax scale in the exponent's multiply-add.
-template <int PS, bool KV8 = false>
-__global__ __launch_bounds__(kPrefillThreads, 1) void prefill_mfma_kernel(PrefillParams p) {
+// W: waves per workgroup, 8 (one workgroup per compute unit) or 4 (two).
+template <int PS, bool KV8, int W>
+__global__ __launch_bounds__(64 * W, 2) void prefill_mfma_kernel(PrefillParams p) {
     constexpr int D = 128;
     constexpr int ES = KV8 ? 1 : 2;                              // bytes per cache element
     constexpr int kLog2Ps = (PS == 16) ? 4 : 5;
     constexpr int kStep = 2 * kTile;                             // tokens staged at a time
-    constexpr int kColumns = prefill_columns(D);
+    constexpr int kColumns = prefill_columns(W);
     constexpr int kKRow = kPrefillRowBytes, kVRow = kPrefillVRowBytes;
-    constexpr int kTokStride = kPrefillThreads / 16;             // a thread stages one of a row's 16 pieces of every
+    constexpr int kTokStride = 64 * W / 16;                      // a thread stages one of a row's 16 pieces of every
     constexpr int NP = kStep / kTokStride;                       // kTokStride-th token of a step
     __shared__ __align__(16) char k_lds[2][kStep * kKRow];
     __shared__ __align__(16) char v_lds[2][kStep * kVRow];
@@ -235,7 +235,7 @@ __global__ __launch_bounds__(kPrefillThreads, 1) void prefill_mfma_kernel(Prefil
     const int lds_off_v = st_tok * kVRow + st_chunk * 16;
     const int n_steps = (n_tiles + 1) >> 1;
     // this workgroup's share of the steps: [s_begin, s_end), all of them without a split.  The launch provides NS
-    // workgroups per 256 columns; how many of them share the work depends on their context.
+    // workgroups per run of columns; how many of them share the work depends on their context.
     const int ns_eff = prefill_effective_splits(NS, n_steps, p.min_split_steps);
     if (split >= ns_eff) return;
     const int s_begin = (int)((long long)n_steps * split / ns_eff);
@@ -514,9 +514,8 @@ __global__ __launch_bounds__(kThreads) void prefill_merge_kernel(PrefillParams p
     const int n_live = min(n_q, p.max_q_len);
     if (qi >= n_live) return;
     // the split count of the row's workgroup, as the attention kernel derived it
-    constexpr int kColumns = prefill_columns(D);
     const int c = (int)qi * p.G + head % p.G;
-    const int wg_last = prefill_last_token(c - c % kColumns, kColumns, p.G, n_live);
+    const int wg_last = prefill_last_token(c - c % p.columns, p.columns, p.G, n_live);
     const int n_tiles = (L - n_q + wg_last) / kTile + 1;
     const int ns_eff = prefill_effective_splits(p.num_splits, (n_tiles + 1) >> 1, p.min_split_steps);
     if (ns_eff == 1) return;                                     // written by the attention kernel itself

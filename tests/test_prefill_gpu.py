@@ -97,6 +97,18 @@ def test_every_column_runs_once_however_workgroups_are_dealt_to_the_dies(Hkv, G,
     check_chunk(wl, ch, tuning={omni.OMNI_TUNE_PREFILL_SPLITS: 1})
 
 
+@pytest.mark.parametrize("B,longest,q_len,Hkv,G,ps", [(140, 190, 20, 2, 4, 16), (300, 90, 8, 1, 16, 32),      # many short contexts
+                                                      (5, 13000, 16, 8, 1, 16), (12, 5200, 9, 4, 7, 32)])     # long ones, split
+def test_short_chunks_two_workgroups_per_compute_unit(B, longest, q_len, Hkv, G, ps):
+    """Chunks of at most 128 (token, head) columns: more than 256 workgroups, or contexts long enough for more parts."""
+    rng = np.random.default_rng(740 + B)
+    lens = np.concatenate([[longest, 1, 0], rng.integers(1, longest // (1 if B > 20 else 4), size=B - 3)]).astype(np.int64)
+    q_lens = np.minimum(lens, rng.integers(1, q_len + 1, size=B)).astype(np.int64)
+    q_lens[0] = q_len
+    wl = W.build("short", 741, lens, Hq=G * Hkv, Hkv=Hkv, D=128, ps=ps, dtype=W.BF16)
+    check_chunk(wl, W.add_chunk(wl, q_lens, 742, in_cache=True, gap=1), split_workspace=True)
+
+
 @pytest.mark.parametrize("dtype,D,G,Hkv,ps", [(W.F32, 64, 2, 2, 16), (W.F32, 64, 7, 1, 32), (W.F32, 128, 4, 2, 16),
                                               (W.BF16, 64, 5, 2, 16), (W.BF16, 64, 16, 1, 32)])
 def test_chunks_on_every_other_dtype_and_head_size(dtype, D, G, Hkv, ps):
