@@ -523,19 +523,42 @@ __global__ __launch_bounds__(kThreads) void prefill_merge_kernel(PrefillParams p
     const size_t pi = (((size_t)b * p.max_q_len + qi) * p.Hq + head) * NS;
     float M = -INFINITY, den = 0.f;
     float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int s = 0; s < ns_eff; ++s) {
-        const float2 ml = p.part_ml[pi + s];
-        if (ml.y != 0.f) {                                       // also a NaN: a piece with a NaN score must show
-            const float4 o = *reinterpret_cast<const float4 *>(p.part_o + (pi + s) * D + 4 * d4);
-            const float Mn = fmaxf(M, ml.x);
-            const float a = fast_exp2(M - Mn);                   // 0 while M is still -inf
-            const float w = fast_exp2(ml.x - Mn);
-            num.x = num.x * a + w * o.x; num.y = num.y * a + w * o.y;
-            num.z = num.z * a + w * o.z; num.w = num.w * a + w * o.w;
-            den = den * a + w * ml.y;
-            M = Mn;
+    // All loads of a round are issued before any is used: one piece after the other, each behind a test of its sum, made the
+    // launch a chain of two trips to memory per piece (one request, 28/4 heads, 16 tokens of 16384, 16 pieces: 27.9 -> 21.0 us a
+    // call; 8/8 heads, four requests of 2048, 8 pieces: 18.1 -> 15.1 us).
+    auto round = [&](auto size, int s0) __attribute__((always_inline)) {
+        constexpr int R = decltype(size)::value;
+        float2 ml[R];
+        float4 o[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const size_t at = pi + min(s0 + r, ns_eff - 1);
+            ml[r] = p.part_ml[at];
+            o[r] = *reinterpret_cast<const float4 *>(p.part_o + at * D + 4 * d4);
         }
-    }
+        float Mn = M;
+        bool has[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            has[r] = s0 + r < ns_eff && ml[r].y != 0.f;          // also a NaN: a piece with a NaN score must show
+            if (has[r]) Mn = fmaxf(Mn, ml[r].x);
+        }
+        const float a = M > -INFINITY ? fast_exp2(M - Mn) : 0.f;
+        num.x *= a; num.y *= a; num.z *= a; num.w *= a;
+        den *= a;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (has[r]) {
+                const float w = fast_exp2(ml[r].x - Mn);
+                num.x += w * o[r].x; num.y += w * o[r].y; num.z += w * o[r].z; num.w += w * o[r].w;
+                den += w * ml[r].y;
+            }
+        }
+        M = Mn;
+    };
+    if (ns_eff <= 4) round(std::integral_constant<int, 4>{}, 0);
+    else
+        for (int s0 = 0; s0 < ns_eff; s0 += 8) round(std::integral_constant<int, 8>{}, s0);
     const float inv = 1.f / den;                                 // the split that holds the token's own position has l > 0
     const size_t at = ((size_t)(p.q_offsets[b] + qi) * p.Hq + head) * D + 4 * d4;
     if (p.out_bf16) {
