@@ -104,7 +104,15 @@ struct omni_handle_s {
     //    heads, 16 tokens of 16384: 134 / 110 us; but 2048: 24.0 / 29.6 us).
     PrefillShape prefill_shape(int max_q_len) const {
         if (!prefill_mfma()) return {kWaves, 1};
-        if (d.head_dim == 64) return {kPrefillExactWaves, prefill_splits(prefill_workgroups(max_q_len, kPrefillExactWaves), 256)};
+        if (d.head_dim == 64) {
+            // Three workgroups run on a compute unit, but a second and third pay for the pieces they bring only with parts
+            // of 1024 tokens and more: 16 requests, 8/8 heads, 16 tokens of 16384 183 us with parts for one per unit, 113
+            // for three; 28/4 heads, 64 tokens of 2048 for four requests 22.7 us, and 28.9 with parts of 256 tokens.
+            const long long wgs = prefill_workgroups(max_q_len, kPrefillExactWaves);
+            const int one = prefill_splits(wgs, 256), three = prefill_splits(wgs, 768), by_part = max_ctx / 1024;
+            const int more = three < by_part ? three : by_part;
+            return {kPrefillExactWaves, one > more ? one : more};
+        }
         const long long wg8 = prefill_workgroups(max_q_len, 8), wg4 = prefill_workgroups(max_q_len, 4);
         const int ns8 = prefill_splits(wg8, 256);
         if (wg4 > wg8) return wg8 * ns8 <= 128 ? PrefillShape{4, prefill_splits(wg4, 256)} : PrefillShape{8, ns8};
