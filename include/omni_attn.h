@@ -147,7 +147,10 @@ omni_status_t omni_set_workspace(omni_handle_t h, void *dev_ptr, size_t bytes);
  * Accumulation is fp32.  The batch's context, laid end to end in 32-token tiles, is cut on the device into equal
  * ranges, one per workgroup (split-context / flash-decoding with an online softmax per piece); a request that is cut
  * by a range boundary is put together again by a log-sum-exp merge.  Both are exact re-associations of the definition
- * above.  Two kernel launches (attention, merge).  Writes `out` and the workspace, nothing else.
+ * above.  Two kernel launches (attention, merge).  Where no request can be long (max_context_hint, or else
+ * max_blocks_per_seq pages: up to 768 - 1152 tokens, 256 - 512 over fp32 caches, by the number of requests and KV heads) and
+ * no plan is tuned, a workgroup takes one request and KV head whole and the merge is left out.  Writes `out` and the
+ * workspace, nothing else.
  * For a fixed handle and tuning the result is bit-identical from run to run and under any physical page permutation.
  * Several query tokens per request (speculative decoding, multi-token prediction; OMNI_TUNE_QUERY_TOKENS = T > 1): q
  * and out are [batch, T, num_q_heads, head_dim]; the T tokens are the LAST T of the context_lens[b] tokens (their K/V
@@ -330,7 +333,7 @@ omni_status_t omni_kv_append_chunk(omni_handle_t h, const void *k_new, const voi
 /* Host-known part of the launch plan: the precision of the softmax weights (kernel: 2 = kept to 2^-16, 1 = fp32-exact; which
  * units compute is omni_get_kernel's to say), the data-independent grid (workgroups) of the attention kernel, the
  * (request, KV head) pairs the merge kernel that follows it runs over (its workgroups: that many for each 1024 output
- * elements of a pair), the number of partial-result slots the workspace is sized for, and threads per workgroup.  The range
+ * elements of a pair), both where requests are cut into ranges, the number of partial-result slots the workspace is sized for, and threads per workgroup.  The range
  * length itself is chosen on the device from context_lens; omni_debug_last_plan reads it back. */
 omni_status_t omni_get_plan(omni_handle_t h, int32_t *kernel, int32_t *partition_grid, int32_t *merge_grid,
                             int32_t *max_request_parts, int32_t *threads_per_workgroup);
@@ -365,7 +368,8 @@ void omni_graph_destroy(omni_graph_t g);
 /* ---- test / debugging aids: these synchronise the stream and copy to HOST memory ---- */
 
 /* After an omni_paged_decode_attn call on `stream`: host_out[0] = range length (tokens) the device chose,
- * host_out[1] = number of ranges, host_out[2] = total context tokens, host_out[3] = reserved. */
+ * host_out[1] = number of ranges, host_out[2] = total context tokens, host_out[3] = reserved.  Where every request is
+ * taken whole: the longest context the handle allows, and the batch. */
 omni_status_t omni_debug_last_plan(omni_handle_t h, int32_t host_out[4], void *stream);
 
 /* Dense copy of one request's rows of `cache` (k_cache or v_cache), in token order, into DEVICE buffer
@@ -381,7 +385,8 @@ omni_status_t omni_debug_gather(omni_handle_t h, const void *cache, const int32_
 omni_status_t omni_debug_stream_read(const void *a, size_t a_bytes, const void *b, size_t b_bytes, void *sink,
                                      void *stream);
 
-/* Host-only: the shared-memory layout the matrix-core kernel of this handle is launched with.  host_out[0] = bytes of
+/* Host-only: the shared-memory layout the matrix-core kernel of this handle is launched with where requests are cut into
+ * ranges.  host_out[0] = bytes of
  * dynamic shared memory, [1] = bytes of the kernel variant's static K staging area, [2] = online-softmax states the
  * ring holds (4 .. 16), [3] = 1 if K
  * tiles are staged through shared memory, [4] = 1 if two workgroups fit one compute unit's 160 KB, [5] = the most

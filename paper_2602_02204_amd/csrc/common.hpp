@@ -213,6 +213,15 @@ __device__ __forceinline__ void wg_coords(const AttnParams &p, int *w, int *kvh)
     }
 }
 
+// The same where a workgroup takes one request whole: w = request.  A request's KV heads go to different dies, so that a long
+// one does not make one die late, and which head a die gets of a request rotates.
+__device__ __forceinline__ void wg_coords_whole(const AttnParams &p, int *w, int *kvh) {
+    constexpr int kDies = 8;
+    const int bid = blockIdx.x;
+    *w = bid / p.Hkv;
+    *kvh = (bid - *w * p.Hkv + *w / max(1, kDies / p.Hkv)) % p.Hkv;
+}
+
 // Prologue shared by the partition kernels: build the plan in shared memory, write the all-zero rows of empty
 // requests (first workgroup of each KV head) and the plan words (first workgroup of the grid).
 template <int D>

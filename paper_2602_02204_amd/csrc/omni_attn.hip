@@ -61,6 +61,8 @@ struct omni_handle_s {
     int r_cap = 0;               // bound on partial-result slots (range index + request index)
     size_t off_ml = 0, off_o = 0, off_e = 0, ws_bytes = 0;
     MfmaLds lds{};               // shared-memory layout of the matrix-core kernel
+    MfmaLds lds_whole{};         // the same where every request is taken whole
+    bool whole = false;          // a workgroup takes one request whole (short contexts), no merge launch
     bool k_staged = true;        // K tiles through shared memory (matrix-core kernel)
     bool lds_attr_set = false;   // the kernel has been told how much dynamic shared memory it may get
     void *ws = nullptr;
@@ -141,6 +143,23 @@ struct omni_handle_s {
                align256((size_t)d.batch * max_q_len * d.num_q_heads * ns * d.head_dim * sizeof(float));
     }
 
+    // Short contexts: one workgroup per (request, KV head) and no merge launch, instead of equal ranges.  The longest request
+    // then decides when the launch ends, so the bound on its length decides; a tuned plan stays a plan.  Measured with
+    // lengths of 1/16 .. 1, 9/10 .. 1 of the bound and one long request in ten, 1 .. 4096 workgroups, 28/4, 16/2, 8/8 and
+    // 4/1 heads (plan / whole, us per step): 16- and 8-bit caches up to 768 tokens 1.04 - 2 times as fast (four requests,
+    // 28/4 heads, 512 tokens 11.1 / 8.0; 512 requests, 4/1 heads, 256 tokens 17.3 / 9.4), from 256 workgroups on also 1024
+    // (256 requests, 16/2 heads 31.2 / 28.5; 64-dim heads 20.7 / 15.9; but 64 workgroups 13.0 / 12.9 .. 11.7 / 13.6), from
+    // 512 on 1152 (1536: 41.9 / 41.7 .. 29.2 / 32.1).  fp32 tiles take longer: 256 tokens (11.5 / 8.3; 512: 11.6 / 12.0), from
+    // 512 workgroups on 512 (23.6 / 19.2), and with more than 1024 of the shortest contexts the plan is ahead (21.8 / 24.2).
+    bool takes_requests_whole() const {
+        if (!mfma || !lds_whole.two_per_cu || tune_target_wgs != kDefaultTargetWorkgroups ||
+            tune_min_partition != kDefaultMinPartition || tune_force_partition > 0)
+            return false;
+        const long long wgs = (long long)d.batch * d.num_kv_heads;
+        if (d.kv_dtype == OMNI_F32) return wgs <= 1024 && max_ctx <= (wgs >= 512 ? 512 : 256);
+        return max_ctx <= (wgs >= 512 ? 1152 : wgs >= 256 ? 1024 : 768);
+    }
+
     void derive() {
         G = d.num_q_heads / d.num_kv_heads;
         const long long cap_ctx = (long long)d.max_blocks_per_seq * d.page_size;
@@ -167,6 +186,8 @@ struct omni_handle_s {
         k_staged = staged.two_per_cu && staged.ring_states >= kWaves + 1;
         lds = k_staged ? staged : plain;
         lds_attr_set = false;
+        lds_whole = mfma_lds_layout(1, Gq, d.head_dim, d.head_dim * elem_bytes(d.kv_dtype), true, mt, kWaves);
+        whole = takes_requests_whole();
         long long ranges = nw;
         if (tune_force_partition > 0) {
             const long long tiles = (long long)d.batch * ((max_ctx + kTile - 1) / kTile);
@@ -347,7 +368,19 @@ const void *mfma_variant_of(bool ps16, bool staged) {
     return ps16 ? (staged ? (const void *)&decode_mfma_kernel<16, F, true, MT> : (const void *)&decode_mfma_kernel<16, F, false, MT>)
                 : (staged ? (const void *)&decode_mfma_kernel<32, F, true, MT> : (const void *)&decode_mfma_kernel<32, F, false, MT>);
 }
+template <CacheFormat F, bool MT>
+const void *mfma_whole_variant_of(bool ps16) {
+    return ps16 ? (const void *)&decode_mfma_kernel<16, F, true, MT, true> : (const void *)&decode_mfma_kernel<32, F, true, MT, true>;
+}
+const void *mfma_whole_variant(const omni_handle_s *h) {
+    const bool ps16 = h->d.page_size == 16, d64 = h->d.head_dim == 64, mt = h->tune_query_tokens > 1;
+    if (h->d.kv_dtype == OMNI_FP8_E4M3) return mt ? mfma_whole_variant_of<kFp8D128, true>(ps16) : mfma_whole_variant_of<kFp8D128, false>(ps16);
+    if (h->d.kv_dtype == OMNI_F32) return d64 ? mfma_whole_variant_of<kF32D64, false>(ps16) : mfma_whole_variant_of<kF32D128, false>(ps16);
+    if (d64) return mfma_whole_variant_of<kBf16D64, false>(ps16);
+    return mt ? mfma_whole_variant_of<kBf16D128, true>(ps16) : mfma_whole_variant_of<kBf16D128, false>(ps16);
+}
 const void *mfma_variant(const omni_handle_s *h) {
+    if (h->whole) return mfma_whole_variant(h);
     const bool ps16 = h->d.page_size == 16, st = h->k_staged, d64 = h->d.head_dim == 64, mt = h->tune_query_tokens > 1;
     if (h->d.kv_dtype == OMNI_FP8_E4M3) return mt ? mfma_variant_of<kFp8D128, true>(ps16, st) : mfma_variant_of<kFp8D128, false>(ps16, st);
     if (h->d.kv_dtype == OMNI_F32) return d64 ? mfma_variant_of<kF32D64, false>(ps16, st) : mfma_variant_of<kF32D128, false>(ps16, st);
@@ -405,7 +438,8 @@ static omni_status_t launch_attention(omni_handle_t h, const void *q, const void
     p.Tq = h->tune_query_tokens;
     p.log2_ps = ilog2(d.page_size);
     p.out_bf16 = d.out_dtype == OMNI_BF16;
-    p.lds = h->lds;
+    p.lds = h->whole ? h->lds_whole : h->lds;
+    if (h->whole) p.plan.s_force = (d.max_blocks_per_seq * d.page_size + kTile - 1) / kTile;
 
     // Several query tokens per request: one pass (attention + merge) per pass_tokens of them; the new rows of a fused
     // step are all written by the first pass.
@@ -414,7 +448,7 @@ static omni_status_t launch_attention(omni_handle_t h, const void *q, const void
         p.T = p.Tq - t_off < h->pass_tokens ? p.Tq - t_off : h->pass_tokens;
         p.Gq = p.T * h->G;
         if (t_off > 0) { p.k_new = nullptr; p.v_new = nullptr; }
-        const dim3 grid((unsigned)(h->nw * d.num_kv_heads));
+        const dim3 grid((unsigned)((h->whole ? d.batch : h->nw) * d.num_kv_heads));
         const size_t dyn = (size_t)(2 * d.batch + 1) * sizeof(int);     // tile offsets and lengths of the plan
         (void)hipGetLastError();
         const bool prof = (size_t)(2 * h->prof_used + 1) < h->prof_events.size() && (h->prof_calls++ % h->prof_stride) == 0;
@@ -427,7 +461,7 @@ static omni_status_t launch_attention(omni_handle_t h, const void *q, const void
             if (!h->lds_attr_set) {          // more than the default 64 KB of dynamic shared memory: the setting belongs to
                                              // the kernel, not to the handle, so every handle asks for the same bound (what
                                              // any layout may use) and none lowers what another one needs
-                if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, max_dynamic_lds(h->lds.static_bytes)) != hipSuccess) {
+                if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, max_dynamic_lds(p.lds.static_bytes)) != hipSuccess) {
                     (void)hipGetLastError();
                     return OMNI_ERR_HIP;
                 }
@@ -435,9 +469,9 @@ static omni_status_t launch_attention(omni_handle_t h, const void *q, const void
             }
             void *args[] = {&p};
             const hipError_t le = prof_in_dispatch
-                ? hipExtLaunchKernel(fn, grid, dim3(kThreads), args, (size_t)h->lds.total, s, h->prof_events[2 * h->prof_used],
+                ? hipExtLaunchKernel(fn, grid, dim3(kThreads), args, (size_t)p.lds.total, s, h->prof_events[2 * h->prof_used],
                                      h->prof_events[2 * h->prof_used + 1], 0)
-                : hipLaunchKernel(fn, grid, dim3(kThreads), args, (size_t)h->lds.total, s);
+                : hipLaunchKernel(fn, grid, dim3(kThreads), args, (size_t)p.lds.total, s);
             if (le != hipSuccess) {
                 (void)hipGetLastError();
                 return OMNI_ERR_HIP;
@@ -455,6 +489,7 @@ static omni_status_t launch_attention(omni_handle_t h, const void *q, const void
             ++h->prof_used;
         }
 
+        if (h->whole) continue;          // no request was cut
         // Whether any request was cut by a range boundary is known only on the device: the merge kernel always runs, and
         // its workgroups return at once for requests that the attention kernel finished.
         const dim3 mgrid((unsigned)(d.batch * d.num_kv_heads), (unsigned)((p.Gq * d.head_dim + 4 * kThreads - 1) / (4 * kThreads)));
@@ -612,7 +647,7 @@ omni_status_t omni_debug_kernel_resources(omni_handle_t h, int32_t which, int32_
     if (which == 0) {
         if (!h->mfma) return OMNI_ERR_UNSUPPORTED;
         fn = mfma_variant(h);
-        dyn = h->lds.total;
+        dyn = h->whole ? h->lds_whole.total : h->lds.total;
     } else if (which == 1) {
         fn = h->d.head_dim == 128 ? (const void *)&merge_kernel<128> : (const void *)&merge_kernel<64>;
         dyn = 0;
