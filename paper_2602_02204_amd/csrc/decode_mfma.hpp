@@ -324,7 +324,8 @@ __device__ __forceinline__ void split_weights(const float (&pw)[8], uint4 (&P)[k
 // t1: the request's length; t1col: tokens this lane's column may see (t1 less the query tokens after its own; = t1 in
 // plain decode); t1min: the smallest t1col of the wave's columns.
 // kMulti (several query tokens per request): the three differ; otherwise all are t1.
-template <CacheFormat F, bool kMulti>
+// kAllBits: weights keep 24 bits whatever the format.
+template <CacheFormat F, bool kMulti, bool kAllBits>
 __device__ __forceinline__ void mfma_softmax_pv(float (&sv)[8], uint32_t (&V)[8][CacheTraits<F>::kVWide], MfmaState<F> &st,
                                                 int tb, int t1, int t1col, int t1min, int j, float vs0, float vs1) {
 #pragma clang fp contract(off)
@@ -381,7 +382,7 @@ __device__ __forceinline__ void mfma_softmax_pv(float (&sv)[8], uint32_t (&V)[8]
             if constexpr (C::D == 128) { if (e & 1) asm volatile("" : "+v"(st.acc[e]), "+v"(st.acc[e - 1])); }   // two blocks at a time
         }
     } else {
-        constexpr int kParts = C::D == 64 ? 3 : 2;
+        constexpr int kParts = C::D == 64 || kAllBits ? 3 : 2;
         uint4 P[kParts];
         split_weights<kParts, true>(pw, P);
         if constexpr (kParts == 2) {
@@ -521,6 +522,11 @@ template <int PS, CacheFormat F, bool KST, bool MT, bool WHOLE = false>
 __global__ __launch_bounds__(kThreads, WHOLE ? whole_workgroups_per_cu(F) : 2) void decode_mfma_kernel(AttnParams p) {
     using C = CacheTraits<F>;
     constexpr int D = C::D, RB = C::kRowBytes;
+    // A request's largest weights are exactly one in every state that holds them, so the fewer states of a whole request made
+    // 16-bit weights 1.02 - 1.15 times as far from 64 bits over contexts of 17 .. 760 tokens.  All 24 bits instead: 0.08 -
+    // 0.76 times as far, for 1 % (256 requests of 129 .. 1025 tokens 29.35 -> 29.72 us) to 6 % (few of 512) of the step.  Over
+    // an 8-bit cache a page's scale multiplies the weights first and the distance stays what it was (0.97 - 1.01).
+    constexpr bool kAllBits = WHOLE && !C::kFp8;
     constexpr int kLog2Ps = (PS == 16) ? 4 : 5;
     __shared__ PlanSmem ps;
     extern __shared__ __align__(16) int E[];                 // E[B + 1] tile offsets, then Lc[B] lengths, then the ring
@@ -913,9 +919,9 @@ __global__ __launch_bounds__(kThreads, WHOLE ? whole_workgroups_per_cu(F) : 2) v
                         V[r][0] = x.x; V[r][1] = x.y; V[r][2] = x.z; V[r][3] = x.w;
                     }
                     request_next();                              // the raw V bytes are consumed: request the next ones
-                    mfma_softmax_pv<F, MT>(sv, V, st, cur.tile * kTile, seg.L, seg.L - col_back, t1min, j, v0, v1);
+                    mfma_softmax_pv<F, MT, kAllBits>(sv, V, st, cur.tile * kTile, seg.L, seg.L - col_back, t1min, j, v0, v1);
                 } else {
-                    mfma_softmax_pv<F, MT>(sv, Vr, st, cur.tile * kTile, seg.L, seg.L - col_back, t1min, j, 1.f, 1.f);
+                    mfma_softmax_pv<F, MT, kAllBits>(sv, Vr, st, cur.tile * kTile, seg.L, seg.L - col_back, t1min, j, 1.f, 1.f);
                     request_next();
                 }
                 ++s; cur = nxt;
