@@ -186,3 +186,21 @@ def test_graph_rejects_the_null_stream():
     assert L.omni_graph_begin(None) == 4
     assert L.omni_graph_launch(None, None) == 1
     L.omni_graph_destroy(None)
+
+
+def test_calls_without_a_stream_run_on_the_threads_current_one():
+    import threading
+    side, got = torch.cuda.Stream(), {}
+
+    def look(name):
+        got[name] = (omni._stream(None) or 0, torch.cuda.current_stream().cuda_stream)
+
+    look("default")
+    with torch.cuda.stream(side):
+        look("side")
+        t = threading.Thread(target=look, args=("thread",))                  # a thread starts on the default stream
+        t.start()
+        t.join()
+    look("after")
+    assert all(a == b for a, b in got.values()), got
+    assert got["side"][0] == side.cuda_stream and got["thread"][0] == got["default"][0] == got["after"][0]
