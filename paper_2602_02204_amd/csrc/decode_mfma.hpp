@@ -349,8 +349,7 @@ __device__ __forceinline__ void mfma_softmax_pv(float (&sv)[8], uint32_t (&V)[8]
     float tmax = sv[0];
 #pragma unroll
     for (int r = 1; r < 8; ++r) tmax = fmaxf(tmax, sv[r]);
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 16));
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
+    tmax = across_lane_groups(tmax, [](float a, float b) { return fmaxf(a, b); });
     // finite: in plain decode every tile holds a live token; with several query tokens a column may see none of a
     // tile's, and then keeps a finite stand-in
     const float mn = kMulti ? fmaxf(fmaxf(st.m, tmax), kNoTokenReference) : fmaxf(st.m, tmax);
@@ -592,7 +591,7 @@ __global__ __launch_bounds__(kThreads, WHOLE ? whole_workgroups_per_cu(F) : 2) v
         unsigned long long T = 0;
         const bool first = blockIdx.x == 0 && wave == 0;
         pl = plan_build_wave(p.context_lens, p.plan, E, E + p.plan.B + 1, &wp, w == 0 && wave == 0,
-                             [&](int b) { wave_zero_rows<D>(p, b, kvh); }, T);
+                             [&](int b) { wave_zero_rows<D>(p, b, kvh); }, first, T);
         if (first && lane == 0) {
             p.ws.plan_words[0] = pl.S * kTile; p.ws.plan_words[1] = pl.nranges;
             p.ws.plan_words[2] = (int)(T & 0xffffffffULL); p.ws.plan_words[3] = (int)(T >> 32);
@@ -928,8 +927,7 @@ __global__ __launch_bounds__(kThreads, WHOLE ? whole_workgroups_per_cu(F) : 2) v
             }
 
             // ---- end of the wave's share of this request: it leaves its state in shared memory and goes on
-            st.l += __shfl_xor(st.l, 16);                        // per-lane sums of the four lane groups; m is common
-            st.l += __shfl_xor(st.l, 32);
+            st.l = across_lane_groups(st.l, [](float a, float b) { return a + b; });     // per-lane sums of the four groups; m is common
             float *state = ring + (size_t)(wbase + nstate) * state_floats;
             ++nstate;
             if (col < Gq) {

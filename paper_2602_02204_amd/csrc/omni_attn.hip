@@ -431,6 +431,7 @@ static omni_status_t launch_attention(omni_handle_t h, const void *q, const void
     p.ws.merge_rec = reinterpret_cast<int2 *>(ws + h->off_e);
     p.plan.B = d.batch;
     p.plan.nw = h->nw;
+    p.plan.nw_inverse = h->nw > 1 ? (unsigned)((1ull << 32) / (unsigned)h->nw) : 0xffffffffu;
     p.plan.s_min = h->tune_min_partition / kTile;
     p.plan.s_force = h->tune_force_partition / kTile;
     p.scale_log2 = scale * kLog2e;

@@ -24,6 +24,7 @@ constexpr int kLog2Tile = 5;
 struct PlanParams {
     int B;
     int nw;              // workgroups per KV head
+    unsigned nw_inverse; // floor(2^32 / nw), 2^32 - 1 for nw = 1
     int s_min;           // smallest range length in tiles the plan may pick (>= 1)
     int s_force;         // > 0: use exactly this range length in tiles
 };
@@ -48,6 +49,29 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Inclusive scan over the 64 lanes of a wave: within rows of 16, then the rows' totals (six vector instructions; as shuffles
+// through shared memory six trips of about a hundred cycles, in front of every wave's first table read).
+__device__ __forceinline__ int wave_inclusive_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);          // row_shr:1, 2, 4, 8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);          // row_bcast:15 into rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);          // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
+// Lane l's value and those of lanes l ^ 16, l ^ 32, l ^ 48 combined, the nearer pair first: every lane gets the result.
+template <typename Op>
+__device__ __forceinline__ float across_lane_groups(float v, Op op) {
+    const unsigned a = __float_as_uint(v);
+    const auto r = __builtin_amdgcn_permlane16_swap(a, a, false, false);     // even rows twice, odd rows twice
+    const float x = op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    const unsigned b = __float_as_uint(x);
+    const auto q = __builtin_amdgcn_permlane32_swap(b, b, false, false);     // lower half twice, upper half twice
+    return op(__uint_as_float(q[0]), __uint_as_float(q[1]));
+}
+
 // Shared-memory part of the plan.  The dynamic shared memory of the kernel holds E[0..B] (exclusive prefix of tile
 // counts, E[B] = C) followed by Lc[0..B) (context lengths clamped at 0).
 struct PlanSmem {
@@ -66,7 +90,12 @@ struct Plan {
 __device__ __forceinline__ Plan plan_cut(const PlanParams &pp, int C) {
     Plan pl;
     pl.C = C;
-    const int S = pp.s_force > 0 ? pp.s_force : max(pp.s_min, ceil_div(C, pp.nw));
+    // C / nw by the reciprocal, which is at most one too few for C < 2^31: in front of every wave's first load a division is long
+    const unsigned c = (unsigned)C, n = (unsigned)pp.nw;
+    unsigned q = __umulhi(c, pp.nw_inverse);
+    if (c - q * n >= n) ++q;
+    if (c - q * n > 0) ++q;                          // rounded up
+    const int S = pp.s_force > 0 ? pp.s_force : max(pp.s_min, (int)q);
     pl.S = max(S, 1);
     pl.nranges = ceil_div(C, pl.S);
     return pl;
@@ -75,11 +104,7 @@ __device__ __forceinline__ Plan plan_cut(const PlanParams &pp, int C) {
 // Inclusive scan over the 256 threads of the workgroup (two shared-memory barriers).
 __device__ __forceinline__ int block_inclusive_scan(int v, PlanSmem *ps, int *total) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int t = __shfl_up(v, off);
-        if (lane >= off) v += t;
-    }
+    v = wave_inclusive_scan(v);
     lds_barrier();                         // wave_tot may still be read from the previous round
     if (lane == 63) ps->wave_tot[wave] = v;
     lds_barrier();
@@ -141,11 +166,11 @@ struct WavePlan {
 };
 
 // `zero_row(b)` is called, by all lanes of the wave together, for each request of length <= 0 if `zero_rows`;
-// `total_tokens` receives the sum of the lengths (in every lane).
+// `total_tokens` receives the sum of the lengths (in every lane) if `want_total`.
 template <typename ZeroRow>
 __device__ __forceinline__ Plan plan_build_wave(const int32_t *__restrict__ lens, const PlanParams &pp, int *E, int *Lc,
                                                 WavePlan *wp, bool zero_rows, ZeroRow zero_row,
-                                                unsigned long long &total_tokens) {
+                                                bool want_total, unsigned long long &total_tokens) {
     const int lane = threadIdx.x & 63;
     int L[4], c[4], incl[4];
     if ((reinterpret_cast<uintptr_t>(lens) & 15) == 0 && 4 * lane + 3 < pp.B) {   // one 16-byte load where it may be:
@@ -171,12 +196,7 @@ __device__ __forceinline__ Plan plan_build_wave(const int32_t *__restrict__ lens
         run += c[i];
         incl[i] = run;
     }
-    int scan = run;                              // inclusive scan of the lanes' totals
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int t = __shfl_up(scan, off);
-        if (lane >= off) scan += t;
-    }
+    const int scan = wave_inclusive_scan(run);   // of the lanes' totals
     const int before = scan - run;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -188,9 +208,11 @@ __device__ __forceinline__ Plan plan_build_wave(const int32_t *__restrict__ lens
     wp->owns = (c[0] > 0 ? 1 : 0) | (c[1] > 0 ? 2 : 0) | (c[2] > 0 ? 4 : 0) | (c[3] > 0 ? 8 : 0);
     const int C = __builtin_amdgcn_readlane(scan, 63);
     if (lane == 0) E[pp.B] = C;
+    if (want_total) {
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) tokens += __shfl_xor(tokens, off);
-    total_tokens = tokens;
+        for (int off = 32; off > 0; off >>= 1) tokens += __shfl_xor(tokens, off);
+        total_tokens = tokens;
+    }
     return plan_cut(pp, C);
 }
 
