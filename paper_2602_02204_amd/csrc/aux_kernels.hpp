@@ -197,62 +197,52 @@ struct PackParams {
                                      // and dense row token_offsets[b] holds the first of them
     int max_tokens;                  // with q_lens: at most this many tokens of a request move (the grid's bound)
     int Hkv, MB, log2_ps, row_vecs;
+    int tokens;                       // a workgroup moves at a time
 };
 
-constexpr int kPackTokens = 32;      // tokens per workgroup
+// Dense <-> paged copy of whole requests, bit for bit: dense row (token_offsets[b] + t) holds the Hkv rows of token t back to
+// back, the pool keeps them in page block_table[b][t / ps], slot t % ps.  Consecutive threads take consecutive 16-byte pieces of
+// the dense side, so dense traffic is fully coalesced and pool traffic comes in whole 128- to 512-byte rows.
+// Bound by HBM on large batches, by the chain length -> table -> rows on small ones.  A workgroup moves as many tokens as give
+// every thread one piece of K and one of V and is done: four such rounds in one workgroup waited for each other's table entries
+// and rows (64 requests of 512 .. 4096 tokens, 28/4 heads, pack and unpack 204 -> 184 us = 6.5 TB/s read and written; 64
+// requests of up to 512 tokens 37.6 -> 27.9 us).  Half as many pieces per workgroup, or twice as many, are 1 - 7 % slower.
+// Workgroups beyond a request's length cost 0.6 ns each, so where the bound on the lengths asks for more than
+// kPackWorkgroups the grid is that large and a workgroup takes every gridDim.x-th part (64 requests, one in ten of 16384 ..
+// 32768 tokens and the others of up to 512: 241 us before, 364 with a workgroup per part, 240; 16384 as the bound on the
+// grid costs the large batches 2 - 4 %).
+constexpr int kPackPieces = kThreads;                        // of K, and of V, per workgroup and part
+constexpr int kPackWorkgroups = 32768;
 
-// Dense <-> paged copy of whole requests, bit for bit.  Workgroup (x, b) moves tokens [32x, 32x + 32) of request b:
-// dense row (token_offsets[b] + t) holds the Hkv rows of token t back to back, the pool keeps them in page
-// block_table[b][t / ps], slot t % ps.  A thread moves 16-byte pieces, two of K and two of V in flight at a time
-// (more per thread, or more tokens per workgroup, measured slower: 4.6 TB/s read + written at 32 tokens and two
-// pieces against 3.2 at eight pieces).
-// Consecutive threads take consecutive pieces of the dense side, so dense traffic is fully coalesced and pool traffic
-// comes in whole 256- or 512-byte rows.
 template <bool kUnpack>
 __global__ __launch_bounds__(kThreads) void kv_pack_kernel(PackParams p) {
-    constexpr int kU = 2;                                    // pieces of K and of V a thread keeps in flight
     const int b = blockIdx.y;
     const int L = p.context_lens[b];
     const int n_move = p.q_lens ? max(0, min(p.q_lens[b], L)) : L;
     const int first = L - n_move;                                          // first token that moves
     const int end = p.q_lens ? first + min(n_move, p.max_tokens) : L;      // one past the last (a longer chunk is cut off)
-    const int t0 = first + blockIdx.x * kPackTokens;
+    if (p.token_offsets[b] < 0) return;
     const long long off = p.token_offsets[b] - first;                      // dense row of token 0 (may be virtual)
-    if (p.token_offsets[b] < 0 || t0 >= end) return;
     const int log2_rv = 31 - __clz(p.row_vecs);              // row_vecs is 8, 16 or 32
     const int vecs_per_token = p.Hkv << log2_rv;
-    const int total = min(kPackTokens, end - t0) * vecs_per_token;
     const int32_t *bt = p.block_table + (size_t)b * p.MB;
     const uint4 *ks = reinterpret_cast<const uint4 *>(p.k_src), *vs = reinterpret_cast<const uint4 *>(p.v_src);
     uint4 *kd = reinterpret_cast<uint4 *>(p.k_dst), *vd = reinterpret_cast<uint4 *>(p.v_dst);
-    for (int i0 = threadIdx.x; i0 < total; i0 += kU * kThreads) {
-        size_t src[kU], dst[kU];
-        uint4 kv[kU], vv[kU];
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            const int i = i0 + u * kThreads;
-            src[u] = dst[u] = 0;
-            if (i < total) {
-                const int tok = i / vecs_per_token, r = i - tok * vecs_per_token;
-                const int g = r >> log2_rv, c = r & (p.row_vecs - 1);
-                const int t = t0 + tok;
-                const int page = bt[t >> p.log2_ps], slot = t & ((1 << p.log2_ps) - 1);
-                const size_t paged = (((((size_t)page * p.Hkv + g) << p.log2_ps) + slot) << log2_rv) + c;
-                const size_t dense = (size_t)(off + t) * vecs_per_token + r;
-                src[u] = kUnpack ? dense : paged;
-                dst[u] = kUnpack ? paged : dense;
-            }
+    for (int t0 = first + blockIdx.x * p.tokens; t0 < end; t0 += gridDim.x * p.tokens) {
+        const int total = min(p.tokens, end - t0) * vecs_per_token;
+        for (int i = threadIdx.x; i < total; i += kThreads) {
+            const int tok = i / vecs_per_token, r = i - tok * vecs_per_token;
+            const int g = r >> log2_rv, c = r & (p.row_vecs - 1);
+            const int t = t0 + tok;
+            const int page = bt[t >> p.log2_ps], slot = t & ((1 << p.log2_ps) - 1);
+            const size_t paged = (((((size_t)page * p.Hkv + g) << p.log2_ps) + slot) << log2_rv) + c;
+            const size_t dense = (size_t)(off + t) * vecs_per_token + r;
+            const size_t src = kUnpack ? dense : paged, dst = kUnpack ? paged : dense;
+            const uint4 kv = nt_load16(ks + src), vv = nt_load16(vs + src);
+            // measured: scattered 4 KB pieces into the pools go faster as non-temporal stores, a dense buffer does not
+            if (kUnpack) { nt_store16(kd + dst, kv); nt_store16(vd + dst, vv); }
+            else { kd[dst] = kv; vd[dst] = vv; }
         }
-#pragma unroll
-        for (int u = 0; u < kU; ++u)
-            if (i0 + u * kThreads < total) { kv[u] = nt_load16(ks + src[u]); vv[u] = nt_load16(vs + src[u]); }
-#pragma unroll
-        for (int u = 0; u < kU; ++u)
-            if (i0 + u * kThreads < total) {
-                // measured: scattered 4 KB pieces into the pools go faster as non-temporal stores, a dense buffer does not
-                if (kUnpack) { nt_store16(kd + dst[u], kv[u]); nt_store16(vd + dst[u], vv[u]); }
-                else { kd[dst[u]] = kv[u]; vd[dst[u]] = vv[u]; }
-            }
     }
 }
 

@@ -747,7 +747,11 @@ static omni_status_t launch_pack(omni_handle_t h, bool unpack, const void *k_src
     p.Hkv = d.num_kv_heads; p.MB = d.max_blocks_per_seq; p.log2_ps = ilog2(d.page_size);
     p.row_vecs = d.head_dim * elem_bytes(d.kv_dtype) / 16;
     const int span = q_lens ? max_tokens : h->max_ctx;                     // tokens per request the grid must cover
-    const dim3 grid((unsigned)((span + kPackTokens - 1) / kPackTokens), (unsigned)d.batch);
+    p.tokens = kPackPieces / (d.num_kv_heads * p.row_vecs);
+    if (p.tokens < 1) p.tokens = 1;
+    const long long parts = (span + (long long)p.tokens - 1) / p.tokens;
+    const long long rounds = (parts * d.batch + kPackWorkgroups - 1) / kPackWorkgroups;
+    const dim3 grid((unsigned)((parts + rounds - 1) / rounds), (unsigned)d.batch);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     (void)hipGetLastError();
     if (unpack) kv_pack_kernel<true><<<grid, kThreads, 0, s>>>(p);

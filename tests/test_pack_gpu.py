@@ -106,3 +106,28 @@ def test_pack_full_thinker_batch():
     torch.cuda.synchronize()
     assert np.array_equal(bits_of(kd), oracle.kv_pack(wl.k_cache, wl.block_table, wl.context_lens, offs, total))
     assert np.array_equal(bits_of(vd), oracle.kv_pack(wl.v_cache, wl.block_table, wl.context_lens, offs, total))
+
+
+@pytest.mark.parametrize("Hkv,D,ps", [(8, 128, 16), (1, 64, 32)])
+def test_more_parts_than_workgroups(Hkv, D, ps):
+    """A table far wider than the requests: the grid is cut and a workgroup moves several parts of a longer request."""
+    rng = np.random.default_rng(6)
+    lens = rng.integers(0, 24, size=512)
+    lens[[3, 100, 511]] = 333, 1000, 700
+    wl = W.build("wide", 61, lens, Hq=Hkv, Hkv=Hkv, D=D, ps=ps, dtype=W.BF16, extra_table_cols=8192 * 2 // ps if Hkv > 1 else 65536 // ps)
+    offs, total = layout(wl, rng)
+    dev, offs_d = DeviceBatch(wl), torch.from_numpy(offs).cuda()
+    kd, vd = (torch.zeros((total, Hkv, D), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    dev.h.omni_kv_pack(dev.k_cache, dev.v_cache, dev.block_table, dev.context_lens, offs_d, kd, vd)
+    k2, v2 = torch.zeros_like(dev.k_cache), torch.zeros_like(dev.v_cache)
+    dev.h.omni_kv_unpack(kd, vd, k2, v2, dev.block_table, dev.context_lens, offs_d)
+    torch.cuda.synchronize()
+    for dense, pool, cache in ((kd, k2, wl.k_cache), (vd, v2, wl.v_cache)):
+        want = oracle.kv_pack(cache, wl.block_table, wl.context_lens, offs, total)
+        owned = np.zeros(total, dtype=bool)
+        for o, n in zip(offs, wl.context_lens):
+            owned[o:o + n] = True
+        assert np.array_equal(as_bytes(bits_of(dense)[owned]), as_bytes(want[owned])) and not bits_of(dense)[~owned].any()
+        back = np.zeros_like(cache)
+        oracle.kv_unpack(bits_of(dense), back, wl.block_table, wl.context_lens, offs)
+        assert np.array_equal(as_bytes(bits_of(pool)), as_bytes(back))
