@@ -128,7 +128,12 @@ struct omni_handle_s {
     bool prefill_ranks(int max_q_len) const {
         if (!prefill_mfma() || tune_prefill_sort == 0 || d.batch <= 1 || d.batch > kPrefillOrderMax) return false;
         const int waves = prefill_shape(max_q_len).waves;
-        return prefill_workgroups(max_q_len, waves) > (d.head_dim == 128 && waves == 4 ? 512 : 256);
+        const long long wgs = prefill_workgroups(max_q_len, waves);
+        // Short workgroups and four rounds of them even out by themselves: the ranking launch takes 5 us and wins less (256
+        // requests of up to 512 tokens, 16/2 heads, chunks of 64: 82.7 us ranked, 79.7 not; 64-dim heads 53.7 / 51.6; but 32
+        // requests, two rounds, 36.1 / 38.3, and 128 of up to 1024 tokens 57.4 / 66.0).
+        if (max_ctx <= 512 && wgs >= 1024) return false;
+        return wgs > (d.head_dim == 128 && waves == 4 ? 512 : 256);
     }
     size_t prefill_order_bytes(int max_q_len) const { return prefill_ranks(max_q_len) ? align256((size_t)d.batch * sizeof(int32_t)) : 0; }
     // Where the multi-token call's part of the workspace begins.  With 64-dim heads behind the decode calls' part: a program
