@@ -18,22 +18,23 @@ namespace omni {
 // KV head (several query tokens), each further 1024 are a workgroup of their own.  Measured together: 1 - 2 % of a step of one
 // request (12.7 -> 12.55 us) or of two query tokens per request (60.1 -> 59.2 us), at the edge of what boxes and runs differ
 // by; nothing elsewhere.  Workgroups of one wave or rounds of 32 pieces cost a single request 0.6 - 1.0 us.
+struct MergeSum { float M, den; float4 num; };
+
+// Pieces [j0, j_end) of the request's four output elements from column `g` on, in rounds of kRound.
 template <int D, int kRound>
-__device__ __forceinline__ void merge_request(const AttnParams &p, int b, int kvh, int idx, int slot_first, int n) {
-    const int g = idx / D;                                                // column: (query token, head)
-    const size_t out0 = out_row(p, b, kvh, g) * D + (idx - g * D);
+__device__ __forceinline__ MergeSum merge_pieces(const AttnParams &p, int kvh, int g, int d, int slot_first, int j0, int j_end) {
     float M = -INFINITY, den = 0.f;
     float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int j0 = 0; j0 < n; j0 += kRound) {
+    for (; j0 < j_end; j0 += kRound) {
         float2 ml[kRound];
         float4 oj[kRound];
 #pragma unroll
         for (int u = 0; u < kRound; ++u) {
             ml[u] = make_float2(0.f, 0.f); oj[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (j0 + u < n) {
+            if (j0 + u < j_end) {
                 const size_t pi = partial_row(p, slot_first + j0 + u, kvh, g);
                 ml[u] = p.ws.part_ml[pi];
-                oj[u] = *reinterpret_cast<const float4 *>(p.ws.part_o + pi * D + (idx - g * D));
+                oj[u] = *reinterpret_cast<const float4 *>(p.ws.part_o + pi * D + d);
             }
         }
         float Mn = M;
@@ -53,9 +54,14 @@ __device__ __forceinline__ void merge_request(const AttnParams &p, int b, int kv
             }
         }
     }
+    return MergeSum{M, den, num};
+}
+
+template <int D>
+__device__ __forceinline__ void merge_store(const AttnParams &p, int b, int kvh, int g, int d, float den, const float4 &num) {
     const bool live = den > 0.f;
-    store_out4(p, out0, make_float4(live ? num.x / den : 0.f, live ? num.y / den : 0.f, live ? num.z / den : 0.f,
-                                    live ? num.w / den : 0.f));
+    store_out4(p, out_row(p, b, kvh, g) * D + d, make_float4(live ? num.x / den : 0.f, live ? num.y / den : 0.f,
+                                                             live ? num.z / den : 0.f, live ? num.w / den : 0.f));
 }
 
 template <int D>
@@ -66,10 +72,87 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(AttnParams p) {
     const int idx = 4 * (int)(blockIdx.y * kThreads + threadIdx.x);
     if (n < 2 || idx >= p.Gq * D) return;                    // no tile (its zero row is written) or finished already
     const int slot_first = __builtin_amdgcn_readfirstlane(rec.x);
+    const int g = idx / D, d = idx - g * D;                  // column: (query token, head)
     // 4, 8 or 16 pieces per round, so that a request cut into many pieces still costs few dependent trips to memory
-    if (n <= 4) merge_request<D, 4>(p, b, kvh, idx, slot_first, n);
-    else if (n <= 8) merge_request<D, 8>(p, b, kvh, idx, slot_first, n);
-    else merge_request<D, 16>(p, b, kvh, idx, slot_first, n);
+    const MergeSum r = n <= 4   ? merge_pieces<D, 4>(p, kvh, g, d, slot_first, 0, n)
+                       : n <= 8 ? merge_pieces<D, 8>(p, kvh, g, d, slot_first, 0, n)
+                                : merge_pieces<D, 16>(p, kvh, g, d, slot_first, 0, n);
+    merge_store<D>(p, b, kvh, g, d, r.den, r.num);
+}
+
+// The same where a request may be cut into many pieces: the W waves of a workgroup take consecutive shares of the pieces of 256
+// output elements and put their sums together through shared memory.  With all pieces in one thread's hands the launch
+// was a chain of trips to memory, one for every 16 pieces, on the few compute units that hold the requests (28/4 heads, one
+// request: 4096 tokens in 32 pieces 11.95 -> 10.3 us a step, 16384 in 128 pieces 25.2 -> 14.2; 16/1 heads, 32768 in 256 pieces 37.3
+// -> 14.9).  merge_waves() has the rule.
+template <int D, int W>
+__global__ __launch_bounds__(64 * W) void merge_shared_kernel(AttnParams p) {
+    __shared__ float2 ml[W][64];
+    __shared__ float4 o[W][64];
+    const int b = blockIdx.x / p.Hkv, kvh = blockIdx.x - b * p.Hkv;
+    const int2 rec = p.ws.merge_rec[b];
+    const int n = __builtin_amdgcn_readfirstlane(rec.y);
+    if (n < 2) return;                                       // the whole workgroup
+    const int slot_first = __builtin_amdgcn_readfirstlane(rec.x);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int idx = 4 * (int)(blockIdx.y * 64 + lane);
+    const bool mine = idx < p.Gq * D;
+    const int g = idx / D, d = idx - g * D;
+    if (n <= 8) {                                            // one round: nothing to share.  As a case of its own, with rounds
+        if (wave > 0 || !mine) return;                       // of 4 too, as fast as above; through the code below 3 % slower
+        const MergeSum r = n <= 4 ? merge_pieces<D, 4>(p, kvh, g, d, slot_first, 0, n)
+                                  : merge_pieces<D, 8>(p, kvh, g, d, slot_first, 0, n);
+        merge_store<D>(p, b, kvh, g, d, r.den, r.num);
+        return;
+    }
+    const int share = (n + W - 1) / W, j0 = wave * share, j_end = min(n, j0 + share);
+    MergeSum r{-INFINITY, 0.f, make_float4(0.f, 0.f, 0.f, 0.f)};
+    if (mine) r = share <= 8 ? merge_pieces<D, 8>(p, kvh, g, d, slot_first, j0, j_end)
+                             : merge_pieces<D, 16>(p, kvh, g, d, slot_first, j0, j_end);
+    ml[wave][lane] = make_float2(r.M, r.den);
+    o[wave][lane] = r.num;
+    __syncthreads();
+    if (wave > 0 || !mine) return;
+    float M = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < W; ++w) M = fmaxf(M, ml[w][lane].x);
+    float den = 0.f;
+    float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        const float2 s = ml[w][lane];
+        if (s.y > 0.f) {                                     // a wave without pieces left no sum
+            const float a = fast_exp2(s.x - M);
+            const float4 v = o[w][lane];
+            num.x += a * v.x; num.y += a * v.y; num.z += a * v.z; num.w += a * v.w;
+            den += a * s.y;
+        }
+    }
+    merge_store<D>(p, b, kvh, g, d, den, num);
+}
+
+// The merge kernel of a head dimension for `waves` = 0, 4 or 8 waves that share a request's pieces.
+inline const void *merge_variant(int head_dim, int waves) {
+    if (head_dim == 128)
+        return waves == 8 ? (const void *)&merge_shared_kernel<128, 8>
+                          : waves == 4 ? (const void *)&merge_shared_kernel<128, 4> : (const void *)&merge_kernel<128>;
+    return waves == 8 ? (const void *)&merge_shared_kernel<64, 8>
+                      : waves == 4 ? (const void *)&merge_shared_kernel<64, 4> : (const void *)&merge_kernel<64>;
+}
+
+template <int D>
+inline void launch_merge_of(const AttnParams &p, int waves, hipStream_t s) {
+    const unsigned rows = (unsigned)(p.plan.B * p.Hkv);
+    const int elements = p.Gq * D, per_wg = waves ? 256 : 4 * kThreads;
+    const dim3 grid(rows, (unsigned)((elements + per_wg - 1) / per_wg));
+    if (waves == 8) merge_shared_kernel<D, 8><<<grid, 512, 0, s>>>(p);
+    else if (waves == 4) merge_shared_kernel<D, 4><<<grid, 256, 0, s>>>(p);
+    else merge_kernel<D><<<grid, kThreads, 0, s>>>(p);
+}
+
+inline void launch_merge(const AttnParams &p, int head_dim, int waves, hipStream_t s) {
+    if (head_dim == 128) launch_merge_of<128>(p, waves, s);
+    else launch_merge_of<64>(p, waves, s);
 }
 
 struct AppendParams {

@@ -165,6 +165,18 @@ struct omni_handle_s {
         return max_ctx <= (wgs >= 512 ? 1152 : wgs >= 256 ? 1024 : 768);
     }
 
+    // Waves that share the pieces of a request in the merge behind a decode pass; 0: every thread goes through all of them
+    // (aux_kernels.hpp).  A request of average length is cut into about nw / batch pieces, of which one round loads eight:
+    // from there on sharing them wins (28/4 heads, 8 pieces on average, 16 requests: 14.6 -> 14.5 us; 16 pieces, 8/8 heads: 13.0 ->
+    // 11.9; 32 pieces, 28/4: 14.9 -> 12.8), below it the workgroups, four times as many, cost more (64 requests, two
+    // pieces: 31.0 -> 31.8).  Eight waves where a request may have more than 64 pieces: 128 of them 14.8 -> 14.2 us, 512
+    // 16.9 -> 15.2, but 40 .. 64 pieces 10.3 -> 10.4.
+    int merge_waves() const {
+        if (nw < 8LL * d.batch) return 0;
+        const int s = (tune_force_partition > 0 ? tune_force_partition : tune_min_partition) / kTile;
+        return nw > 64 && max_ctx / kTile / s > 64 ? 8 : 4;
+    }
+
     void derive() {
         G = d.num_q_heads / d.num_kv_heads;
         const long long cap_ctx = (long long)d.max_blocks_per_seq * d.page_size;
@@ -498,9 +510,7 @@ static omni_status_t launch_attention(omni_handle_t h, const void *q, const void
         if (h->whole) continue;          // no request was cut
         // Whether any request was cut by a range boundary is known only on the device: the merge kernel always runs, and
         // its workgroups return at once for requests that the attention kernel finished.
-        const dim3 mgrid((unsigned)(d.batch * d.num_kv_heads), (unsigned)((p.Gq * d.head_dim + 4 * kThreads - 1) / (4 * kThreads)));
-        if (d.head_dim == 128) merge_kernel<128><<<mgrid, kThreads, 0, s>>>(p);
-        else merge_kernel<64><<<mgrid, kThreads, 0, s>>>(p);
+        launch_merge(p, d.head_dim, h->merge_waves(), s);
         if (hipGetLastError() != hipSuccess) return OMNI_ERR_HIP;
     }
 
@@ -655,7 +665,7 @@ omni_status_t omni_debug_kernel_resources(omni_handle_t h, int32_t which, int32_
         fn = mfma_variant(h);
         dyn = h->whole ? h->lds_whole.total : h->lds.total;
     } else if (which == 1) {
-        fn = h->d.head_dim == 128 ? (const void *)&merge_kernel<128> : (const void *)&merge_kernel<64>;
+        fn = merge_variant(h->d.head_dim, h->merge_waves());
         dyn = 0;
     } else {
         return OMNI_ERR_SHAPE;
@@ -666,7 +676,8 @@ omni_status_t omni_debug_kernel_resources(omni_handle_t h, int32_t which, int32_
         return OMNI_ERR_HIP;
     }
     host_out[0] = a.numRegs; host_out[1] = (int32_t)a.sharedSizeBytes; host_out[2] = dyn;
-    host_out[3] = a.maxThreadsPerBlock; host_out[4] = (int32_t)a.localSizeBytes; host_out[5] = kThreads;
+    host_out[3] = a.maxThreadsPerBlock; host_out[4] = (int32_t)a.localSizeBytes;
+    host_out[5] = which == 1 && h->merge_waves() ? 64 * h->merge_waves() : kThreads;
     return OMNI_OK;
 }
 
