@@ -22,7 +22,7 @@
 // 4 (4kk + j) + e and in step r of V^T P^T token slot_token(j, r), so it loads and stages exactly as the 16-bit caches
 // do and V needs no transposing at all.
 // Measured against the vector-ALU kernel (fp32 FMAs and cross-lane sums: bound by the vector ALUs from four heads per KV
-// head on, by a barrier per request below): 256 requests of a speech-token stage with 64-dim bf16 heads 81.2 -> 22.2 us per
+// head on, by a barrier per request below), with ranges as the unit of work (whole requests: at decode_mfma_kernel): 256 requests of a speech-token stage with 64-dim bf16 heads 81.2 -> 22.2 us per
 // step (76 MB), four short fp32 requests 15.4 -> 10.9 us; fp32, 64 requests of 512 .. 4096 tokens (one pool): 16/4 heads of
 // 128 dims 265.7 -> 109.3 us (K staged; 606 MB, 5.5 TB/s), 32/4 heads 390.2 -> 121.9 us (K not staged), 32/4 heads of 64
 // dims 184.3 -> 57.0 us (303 MB, 5.3 TB/s).

@@ -17,7 +17,8 @@
 // as 16-column ones) and three
 // independent workgroups per compute unit: their barriers do not meet, so one's matrix work hides another's weights.
 // Measured with the append, 24 requests of 129 .. 2049 tokens with chunks of 1 .. 1024, 16/2 heads: vector-ALU kernel
-// 2010 us, this one 115 us; 32 requests with 512-token chunks (137 GFLOP) 310 us = 440 TFLOP/s.  Taken back: 8 waves per
+// 2010 us, this one 115 us, 111 us with the workgroups of a KV head on one die; 32 requests with 512-token chunks (137 GFLOP) 310
+// -> 304 us = 450 TFLOP/s.  Taken back: 8 waves per
 // workgroup (174 us, 330 us), the tiles' work software-pipelined as in prefill_mfma.hpp at two waves per SIMD (143 us, 331 us),
 // four waves per SIMD (231 us: 128 registers do not hold it).  v_dot2_f32_bf16 for the split's subtractions (one instruction
 // for two) gained nothing: it does not run at the full rate.  Distance from 64 bits against the vector-ALU kernel's: 1.05 - 1.17
